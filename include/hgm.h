@@ -20,6 +20,14 @@
  * order, so there is one correct output per (instance, seed).  opts->reseed
  * instead draws the tie-breaking priority afresh every round.
  *
+ * Which rounds run.  A call that wants only the matching (stats NULL, no
+ * reseed, max_rounds or validate, not HGM_VARIANT_CREW, tail_pins and
+ * bin_shift not set to a positive value) admits the edges in steps of the
+ * order, the highest keys first: the same matching with far fewer incidences
+ * visited.  Its rounds are edge-centric and read only the edge side (the bins
+ * of bin_shift, and the check that comes with them, do not run).  Every other
+ * call runs its rounds over all live edges, as the paper counts them.
+ *
  * Conventions for every entry point:
  *  - All array pointers inside hgm_csr, the output bitmap and the workspace
  *    are DEVICE pointers owned by the caller; the library allocates nothing.

@@ -795,6 +795,118 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
 }
 
 
+// Pinned host memory that kernels write a call's last words to: a copy to
+// pageable memory takes about 20 us more.  One page per process, allocated on
+// the first call that may allocate and kept until the process ends, in slots
+// that a call holds while it runs; a call that finds no slot copies instead.
+class HostSlot {
+  public:
+    static constexpr int kSlots = 32;
+    static constexpr size_t kBytes = 4096;
+    explicit HostSlot(bool may_allocate) {
+        std::lock_guard<std::mutex> lk(mu());
+        Pool &P = pool();
+        if (!P.page && may_allocate && !P.failed) {
+            void *p = nullptr;
+            if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable | hipHostMallocMapped) ==
+                hipSuccess) {
+                P.page = (char *)p;
+            } else {
+                P.failed = true;
+                (void)hipGetLastError();
+            }
+        }
+        for (int i = 0; P.page && i < kSlots && at_ < 0; ++i)
+            if (!(P.used >> i & 1)) {
+                P.used |= 1u << i;
+                at_ = i;
+                host_ = P.page + i * kBytes;
+            }
+    }
+    ~HostSlot() {
+        if (at_ < 0) return;
+        std::lock_guard<std::mutex> lk(mu());
+        pool().used &= ~(1u << at_);
+    }
+    HostSlot(const HostSlot &) = delete;
+    HostSlot &operator=(const HostSlot &) = delete;
+    // NULL: none free.  Valid on the device under the same address.
+    void *get() const { return host_; }
+
+  private:
+    struct Pool {
+        char *page = nullptr;
+        bool failed = false;
+        uint32_t used = 0;
+    };
+    static Pool &pool() {
+        static Pool p;
+        return p;
+    }
+    static std::mutex &mu() {
+        static std::mutex m;
+        return m;
+    }
+    int at_ = -1;
+    char *host_ = nullptr;
+};
+
+// Rounds by admission (staged.hip): calls that want only the matching.
+int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t seed,
+               uint32_t *bits, const BatchIn *batch, bool may_allocate) {
+    // Its own edge grid: a wave's lists stay below index m whatever the grid.
+    const int64_t chunks = ((int64_t)g.m + kBlock - 1) / kBlock;
+    const int64_t most = o.edge_grid ? o.edge_grid : kStagedGrid;
+    s.region = (int)((chunks + most - 1) / most) * kBlock;
+    s.grid = (int)((chunks * kBlock + s.region - 1) / s.region);
+    if (batch) HGM_TRY(launch_batch_setup(L, g, *batch, s));
+    HGM_TRY(launch_staged_setup(L, g, s, seed, bits));
+    // Round 0 admits up to the first threshold with at least kStagedFirstEdges
+    // edges above it.
+    const double part[kStagedSteps - 1] = {1.0 / 2700, 1.0 / 250, 1.0 / 33, 0.1, 0.2, 0.5};
+    int first = 0;
+    while (first < kStagedSteps - 1 && part[first] * (double)g.m < (double)kStagedFirstEdges)
+        ++first;
+    const int admitted = kStagedSteps - first;  // rounds with an admission
+    HostSlot slot(may_allocate);
+    int64_t copy[2] = {0, 0};
+    int64_t *report = slot.get() ? (int64_t *)slot.get() : (int64_t *)(s.hot + kSub / 2);
+    HGM_TRY(launch_staged_join(L, g, s, 0, first, seed));
+    int launched = 0;
+    // About 1 in 20 edges is live in the round of the last step and a tenth as
+    // many in each round after it, so that the tail's bound is met in that
+    // round, or one later for every 16 times as many edges.
+    int plan = admitted - 1;
+    for (int64_t m = g.m; m > kStagedTailEdges; m /= 16) ++plan;
+    for (int more = 4;; more = std::min(2 * more, kAdaptiveMaxBatch)) {
+        int rounds = plan;
+        if (!o.adaptive) rounds = std::min(rounds, o.rounds_per_sync);
+        for (int b = 0; b < rounds; ++b) {
+            HGM_TRY(launch_staged_test(L, g, s, launched, bits));
+            launched += 1;
+            HGM_TRY(launch_staged_join(L, g, s, launched, first, seed));
+        }
+        if (launched < admitted - 1) {  // a small rounds_per_sync
+            plan -= rounds;
+            HGM_TRY(hipStreamSynchronize(L.stream));
+            continue;
+        }
+        HGM_TRY(launch_staged_tail(L, g, s, launched, bits, report));
+        if (!slot.get())
+            HGM_TRY(hipMemcpyAsync(copy, report, sizeof(copy), hipMemcpyDeviceToHost, L.stream));
+        HGM_TRY(hipStreamSynchronize(L.stream));
+        if (slot.get()) memcpy(copy, report, sizeof(copy));
+        if (copy[0]) return HGM_OK;
+        plan = more;
+    }
+}
+
+// Whether a call's result does not depend on the round an edge is matched in.
+bool staged_call(const Opts &o, const hgm_stats *stats) {
+    return !stats && !o.reseed && o.max_rounds == 0 && !o.validate &&
+           o.variant != HGM_VARIANT_CREW && o.tail_pins <= 0 && o.bin_shift <= 0;
+}
+
 // Workspace of hgm_match_noalloc: one array per GPU in the library's device
 // memory, held until the process ends.  In host code `scratch` names a host
 // stand-in, not the device array, so the array is only ever used through the
@@ -823,7 +935,8 @@ void *scratch_address() {
 
 // Shared body of hgm_match and hgm_match_noalloc.
 int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *workspace,
-              size_t ws_bytes, const hgm_opts *opts, void *stream, hgm_stats *stats) {
+              size_t ws_bytes, const hgm_opts *opts, void *stream, hgm_stats *stats,
+              bool may_allocate) {
     Opts o;
     int rc = resolve_opts(opts, &o);
     if (rc != HGM_OK) return rc;
@@ -854,6 +967,8 @@ int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *w
     L.grid = device_cus() * o.blocks_per_cu;
     L.stream = (hipStream_t)stream;
     if (L.grid <= 0) return HGM_E_HIP;
+    if (g.m > 0 && staged_call(o, stats))
+        return run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate);
     return run_rounds(g, o, lay, s, L, seed, matched_bits, stats, nullptr);
 }
 
@@ -890,7 +1005,7 @@ size_t hgm_workspace_size(const hgm_csr *g, const hgm_opts *opts) {
 
 int hgm_match(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *workspace,
               size_t ws_bytes, const hgm_opts *opts, void *stream, hgm_stats *stats) {
-    return match_one(gin, seed, matched_bits, workspace, ws_bytes, opts, stream, stats);
+    return match_one(gin, seed, matched_bits, workspace, ws_bytes, opts, stream, stats, true);
 }
 
 size_t hgm_noalloc_max_bytes(void) { return kScratchBytes; }
@@ -910,7 +1025,7 @@ int hgm_match_noalloc(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits,
     if (need > kScratchBytes) return HGM_E_SIZE;
     void *ws = scratch_address();
     if (!ws) return HGM_E_HIP;
-    return match_one(gin, seed, matched_bits, ws, kScratchBytes, opts, stream, stats);
+    return match_one(gin, seed, matched_bits, ws, kScratchBytes, opts, stream, stats, false);
 }
 
 size_t hgm_batch_workspace_size(const hgm_batch *b, const hgm_opts *opts) {
@@ -938,6 +1053,7 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
     const State s = carve(workspace, lay, o);
     char *base = (char *)workspace;
     BatchIn in;
+    memset(&in, 0, sizeof(in));
     in.count = b->count;
     in.v_base = b->v_base;
     in.e_base = b->e_base;
@@ -986,6 +1102,8 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         sa.max_verts = solo_verts_for(sa.lds_bytes, kSoloMaxTiles);
         sa.max_rounds = o.max_rounds;
     }
+    if (b->m_total > 0 && staged_call(o, stats) && !s.explicit0)
+        return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     return run_rounds(g, o, lay, s, L, 0, matched_bits, stats, &in, &sa);
 }
 

@@ -215,6 +215,8 @@ __host__ __device__ __forceinline__ bool solo_instance(int64_t n_i, int64_t kapp
     return kappa_i <= a.max_kappa && n_i <= a.max_verts;
 }
 
+constexpr int kStagedSteps = 7;  // admission steps of staged.hip
+
 struct Launch {
     int grid;            // persistent workgroup count for vertex / setup kernels
     hipStream_t stream;
@@ -252,6 +254,18 @@ hipError_t launch_max0(const Launch &L, const Graph &g, const State &s, uint32_t
 constexpr int kClearNone = 0, kClearAll = 1, kClearPins = 2;
 hipError_t launch_test(const Launch &L, const Graph &g, const State &s, int round, int clear,
                        uint32_t *bits, uint32_t kseed);
+// Rounds by admission (staged.hip).  `first`: the admission step of round 0.
+hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
+                               uint32_t *bits);
+hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, int round,
+                              int first, uint32_t seed);
+hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, int round,
+                              uint32_t *bits);
+// After the join of `round`: its live edges, when few, are matched to the end
+// by one workgroup.  report (device or pinned host): {1 when none is left,
+// live edges left}.
+hipError_t launch_staged_tail(const Launch &L, const Graph &g, const State &s, int round,
+                              uint32_t *bits, int64_t *report);
 // One workgroup checks round `round`'s live counts and, when they are within
 // the tail's bounds, runs every remaining round of the instance (one
 // instance, offset or pair layout; seed and reseed as for the other kernels).

@@ -38,6 +38,15 @@ inline int64_t solo_auto_bound(int64_t kappa_total) {
     const int64_t b = kappa_total / kSoloAutoDivisor;
     return b < kSoloAutoMin ? kSoloAutoMin : b > kSoloAutoMax ? kSoloAutoMax : b;
 }
+// Rounds by admission: workgroups of the join and the test (at 1536: power-law
+// 444 against 377 us, hub-stress 562 against 497, RGG 453 against 429).
+constexpr int kStagedGrid = 1024;
+// Rounds by admission: round 0 starts with the first step expected to admit
+// at least this many edges (fewer leave the grid idle for a whole round).
+constexpr int64_t kStagedFirstEdges = 1024;
+// The tail follows in the round of the last admission for instances of at most
+// this many edges (up to 2^19 edges: one round later, and so on).
+constexpr int64_t kStagedTailEdges = (int64_t)1 << 15;
 // One instance: the tail workgroup takes over a round with at most this many
 // live pins (and at most 65536 live edges).  Off unless asked for: on the
 // synthetic workloads a round in one workgroup costs as much as a round of

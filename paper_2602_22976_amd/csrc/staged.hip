@@ -1,0 +1,551 @@
+// Rounds by admission over the whole grid, for gfx950: hgm_match and
+// hgm_match_batch calls that want only the matching.
+//
+// The order of the edges is fixed, so the edges whose keys reach a threshold
+// form a prefix of it, and an edge of the prefix that holds the maximum at all
+// its pins among the prefix's live edges holds it among all live edges: every
+// edge left out ranks below it.  So round 0 need not form the maximum over
+// every pin.  The rounds start with the top edges and each of the first rounds
+// admits the next part of the order; by the time most edges are admitted one
+// of their pins is done, which the edge's first pins show.  What reaches the
+// maximum, and with it the random reads and device atomics that bound the
+// rounds over all edges, falls from 38M incidences to 0.6M on the power-law
+// instance (29.8M pins) and from 52M to 1.8M on the hub-stress one (36M), at
+// the same number of rounds; the passes over the weights and the first pins
+// that remain are streams.  Per-round counts, priorities redrawn every round
+// and a round limit depend on the round an edge is matched in: those calls
+// run the rounds of kernels.hip.
+//
+// A round is two launches:
+//   join   the survivors of the last round's live list and the edges admitted
+//          this round, those with no done pin, form the round's list and
+//          raise best[round & 1] at their pins; best[(round - 1) & 1] goes
+//          back to zero at the pins of the last round's list, so no pass over
+//          the vertices is needed
+//   test   an edge that equals best at all its pins is matched: its bit is
+//          set and its pins are marked done
+// Each wave owns a range of edge ids and keeps its live edges in its own range
+// of the lists: compaction is a ballot, with no barrier and no atomic.  Done
+// marks are bits (n / 8 bytes stay in every XCD's L2 beside the streams).
+#include <atomic>
+
+#include "internal.h"
+#include "wave.h"
+
+namespace hgm {
+namespace {
+
+constexpr int kWaves = kBlock / kWave;
+constexpr int kKeepPins = 8;  // blocks of pins kept in registers (flat_edges)
+
+// Thresholds by sampling, in one workgroup: 256 groups of 16 keys.  The largest
+// of each group gives 256 maxima, of which the one of rank r has about
+// (1 - r / 256)^(1/16) of all keys below it; the first key of each group
+// gives plain quantiles.  Parts of about 1/2700, 1/250, 1/33, 1/10, 1/5 and
+// 1/2 of the edges.
+constexpr int kSamplesPerGroup = 16;
+constexpr int kThresholds = kStagedSteps - 1;
+constexpr int kFromMaxima = 3;
+__device__ constexpr int kRank[kThresholds] = {1, 16, 98, 25, 51, 128};
+
+template <bool kB>
+__device__ __forceinline__ uint64_t staged_key(const Graph &g, const State &s, uint32_t seed,
+                                               int e) {
+    if constexpr (kB) return s.key[e];
+    return ((uint64_t)g.w[e] << 32) | priority_hash(seed, (uint32_t)e);
+}
+
+__device__ __forceinline__ uint32_t *done_bits(const State &s) {
+    return reinterpret_cast<uint32_t *>(s.done);
+}
+
+// Per-wave live counts sit at the front of rec_c, which these rounds do not
+// otherwise use; behind those of rec_c[0], the admission step of every edge.
+__device__ __forceinline__ uint8_t *step_bytes(const State &s) {
+    return reinterpret_cast<uint8_t *>(s.rec_c[0] + (int64_t)s.grid * kWaves);
+}
+
+constexpr int kSetupThreads = 1024, kSampleGroups = 256;
+constexpr int kSetupParts = kSetupThreads / kSampleGroups;  // threads per sample group
+
+// Rank of group i's key among the 256 groups' (the group decides between equal
+// keys: a batch's instances can share one); each of a group's threads compares
+// a part of them.
+__device__ __forceinline__ int rank_of(const uint64_t *keys, int i, int part) {
+    const uint64_t mine = keys[i];
+    int rank = 0;
+#pragma unroll 8
+    for (int q = part; q < kSampleGroups; q += kSetupParts)
+        rank += keys[q] > mine || (keys[q] == mine && q < i) ? 1 : 0;
+#pragma unroll
+    for (int o = 1; o < kSetupParts; o <<= 1) rank += __shfl_xor(rank, o, kWave);
+    return rank;
+}
+
+// Clears the state; workgroup 0 clears the counters and draws the thresholds.
+template <bool kB>
+__global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s, uint32_t seed,
+                                                                uint32_t *bits) {
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        __shared__ uint64_t top[kSampleGroups], one[kSampleGroups];
+        constexpr int kOwn = kSamplesPerGroup / kSetupParts;
+        const int i = tid / kSetupParts, part = tid % kSetupParts;
+        uint64_t key[kOwn], most = 0;
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+            const uint32_t at = (uint32_t)(q * kSetupThreads + tid);
+            const int64_t lo = (int64_t)g.m * at / (kSetupThreads * kOwn);
+            const int64_t hi = (int64_t)g.m * (at + 1) / (kSetupThreads * kOwn);
+            const uint32_t width = hi > lo ? (uint32_t)(hi - lo) : 1u;
+            const int64_t e = lo + priority_hash(seed, 0x5eedu + at) % width;
+            key[q] = e < g.m ? staged_key<kB>(g, s, seed, (int)e) : 0;
+        }
+        if (part == 0) one[i] = key[0];
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) most = key[q] > most ? key[q] : most;
+#pragma unroll
+        for (int o = 1; o < kSetupParts; o <<= 1) {
+            const uint64_t other = __shfl_xor((unsigned long long)most, o, kWave);
+            most = other > most ? other : most;
+        }
+        if (part == 0) top[i] = most;
+        for (int j = tid; j < s.ring * kSub; j += kSetupThreads)
+            s.stats[j / kSub].live[j % kSub] = 0;
+        __syncthreads();
+        const int r0 = rank_of(top, i, part), r1 = rank_of(one, i, part);
+#pragma unroll
+        for (int q = 0; q < kThresholds; ++q)
+            if (part == 0 && (q < kFromMaxima ? r0 : r1) == kRank[q])
+                s.hot[q] = q < kFromMaxima ? top[i] : one[i];
+        return;
+    }
+    const int64_t stride = (int64_t)(gridDim.x - 1) * kSetupThreads;
+    const int64_t at = (int64_t)(blockIdx.x - 1) * kSetupThreads + tid;
+    // The arrays start at 256-byte boundaries and are padded to them.
+    for (int64_t i = at; i < (g.n + 1) / 2; i += stride) {
+        reinterpret_cast<ulonglong2 *>(s.best[0])[i] = make_ulonglong2(0, 0);
+        reinterpret_cast<ulonglong2 *>(s.best[1])[i] = make_ulonglong2(0, 0);
+    }
+    uint32_t *done = done_bits(s);
+    for (int64_t i = at; i < (g.n + 31) / 32; i += stride) done[i] = 0;
+    for (int64_t i = at; i < g.words; i += stride) bits[i] = 0;
+}
+
+// The live list of wave `wave`: its edge range [lo, lo + per) and its slots.
+struct WaveRange {
+    int64_t lo;
+    int per, wave;
+};
+
+__device__ __forceinline__ WaveRange wave_range(const State &s) {
+    WaveRange r;
+    r.per = s.region / kWaves;
+    r.wave = xcd_share(blockIdx.x, gridDim.x) * kWaves + threadIdx.x / kWave;
+    r.lo = (int64_t)r.wave * r.per;
+    return r;
+}
+
+// Live edges of round r (its join is finished; every lane gets the sum).
+__device__ __forceinline__ int64_t live_edges(const State &s, int r) {
+    unsigned long long v = s.stats[r % s.ring].live[lane_id()];
+    static_assert(kSub == kWave, "one counter per lane");
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return (int64_t)v;
+}
+
+// How best[r & 1] goes back to zero before round r + 2 raises it: a round with
+// many live edges by one pass over the array, one with few by a store at each
+// of its pins; either in the join of round r + 1.  Scattered stores run at
+// about 30 G/s.
+__device__ __forceinline__ bool clears_by_pass(const Graph &g, int64_t live) {
+    return live * 64 >= g.n;
+}
+
+// The grid's side of join_wave.
+template <bool kPairs, bool kB>
+struct GridJoin {
+    const Graph &g;
+    const State &s;
+    const uint32_t *done;
+    uint64_t *best, *old;
+    uint32_t seed;
+    bool lowering;
+    __device__ __forceinline__ uint32_t done_word(int v) const { return done[v >> 5]; }
+    __device__ __forceinline__ void lower(int v) const {
+        if (lowering) old[v] = 0;
+    }
+    // A plain read first skips the atomic where the entry already holds more
+    // (best only grows during the pass, a stale read is a lower bound).
+    __device__ __forceinline__ uint64_t peek(int v) const {
+        return __hip_atomic_load(&best[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void raise(int v, uint64_t k, uint64_t now) const {
+        if (now < k)
+            __hip_atomic_fetch_max(&best[v], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint64_t key(int e) const { return staged_key<kB>(g, s, seed, e); }
+    __device__ __forceinline__ uint64_t again(int, uint64_t k) const { return k; }
+    __device__ __forceinline__ void place(int e, int &base, int &len, int &vb) const {
+        base = kPairs ? 2 * e : g.e_off[e];
+        len = kPairs ? 2 : g.e_off[e + 1] - base;
+        vb = kB ? g.vbase[e] : 0;
+    }
+    __device__ __forceinline__ void sort(int e, uint32_t &w, uint64_t &k) const {
+        if constexpr (kB)
+            k = s.key[e];
+        else
+            w = g.w[e];
+    }
+    __device__ __forceinline__ uint64_t exact_sort(int e, uint32_t w) const {
+        return (uint64_t)w << 32 | priority_hash(seed, (uint32_t)e);
+    }
+    __device__ __forceinline__ void entered(int) const {}
+};
+
+__device__ __forceinline__ WaveLists lists(const State &s, int k) {
+    return {s.list[k], s.rec_a[k], s.rec_b[k], s.rec_vb[k], s.rec_key[k]};
+}
+
+// Round `round` admits step first + round.
+template <bool kPairs, bool kB>
+__global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int round, int first,
+                                                        uint32_t seed) {
+    __shared__ WaveScratch scratch[kWaves];
+    __shared__ int queue[kWaves][kCand];
+    const int wid = threadIdx.x / kWave;
+    const WaveRange range = wave_range(s);
+    const int to = round & 1, from = to ^ 1;
+    GridJoin<kPairs, kB> m{g, s, done_bits(s), s.best[to], s.best[from], seed, round > 0};
+    if (round > 0 && clears_by_pass(g, live_edges(s, round - 1))) {
+        m.lowering = false;
+        ulonglong2 *all = reinterpret_cast<ulonglong2 *>(s.best[from]);
+        const int64_t stride = (int64_t)gridDim.x * kBlock;
+        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < (g.n + 1) / 2; i += stride)
+            all[i] = make_ulonglong2(0, 0);
+    }
+    const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
+    const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps>(
+        m, scratch[wid], queue[wid], g.e_pins, lists(s, from), lists(s, to), range.lo, end,
+        round > 0 ? s.rec_c[from][range.wave] : 0, round == 0, first + round, step_bytes(s),
+        reinterpret_cast<const uint64_t *>(s.hot));
+    if (lane_id() == 0) {
+        s.rec_c[to][range.wave] = kept;
+        if (kept > 0)
+            atomicAdd(&s.stats[round % s.ring].live[range.wave % kSub], (unsigned long long)kept);
+    }
+}
+
+template <bool kPairs, bool kB>
+__global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int round,
+                                                        uint32_t *bits) {
+    __shared__ WaveScratch scratch[kWaves];
+    const int lane = lane_id();
+    WaveScratch &W = scratch[threadIdx.x / kWave];
+    const WaveRange range = wave_range(s);
+    const int k = round & 1;
+    if (blockIdx.x == 0 && threadIdx.x < kSub)
+        s.stats[(round + 1) % s.ring].live[threadIdx.x] = 0;
+    const int n = s.rec_c[k][range.wave];
+    const uint64_t *best = s.best[k];
+    uint32_t *done = done_bits(s);
+    for (int i0 = 0; i0 < n; i0 += kWave) {
+        const int i = i0 + lane;
+        int e = 0, base = 0, len = 0, vb = 0;
+        uint64_t key = 0;
+        if (i < n) {
+            const int64_t at = range.lo + i;
+            e = s.list[k][at];
+            if constexpr (kPairs) {
+                base = 2 * e;
+                len = 2;
+            } else {
+                base = s.rec_a[k][at];
+                len = s.rec_b[k][at];
+                if constexpr (kB) vb = s.rec_vb[k][at];
+            }
+            key = s.rec_key[k][at];
+        }
+        flat_edges<kPairs, kB, kKeepPins>(
+            W, g.e_pins, base, len, key, [&](int v) { return best[v]; },
+            [](int, uint64_t key, uint64_t b) { return b != key; },
+            [&](bool lost) {
+                if (i < n && !lost) {
+                    const int bit = kB ? e + g.bitoff[e] : e;
+                    atomicOr(&bits[bit >> 5], 1u << (bit & 31));
+                }
+                return key;
+            },
+            NoRead(), [&](int v, uint64_t, int) { atomicOr(&done[v >> 5], 1u << (v & 31)); }, vb);
+    }
+}
+
+// The last rounds in one workgroup.  Late rounds have few live edges, and two
+// launches a round then cost far more than their work.  After the join of
+// `round`, when at most kEndEdges edges with at most kEndPins pins are left,
+// one workgroup gathers them, numbers their vertices through a hash table and
+// runs every remaining round in LDS: a round is a handful of barriers.  The
+// waves' counts are zeroed, so that rounds enqueued behind it find nothing.
+// report: {1 when no live edge is left, else 0; live edges left}.
+constexpr int kEndThreads = 1024, kEndEdges = 2048, kEndPins = 8192, kEndSlots = 12288;
+constexpr int kEndPerThread = kEndPins / kEndThreads;
+struct TailShared {
+    union {
+        unsigned long long best[kEndSlots];
+        int id[kEndSlots];  // while the vertices are numbered
+    };
+    uint64_t key[kEndEdges];
+    int start[kEndEdges];   // first pin of the edge among the gathered pins
+    int base[kEndEdges];    // offset of its pins less start
+    int vb[kEndEdges];
+    uint32_t flag[kEndEdges];  // kLost, kDead
+    uint32_t done[kEndSlots / 32];
+    int sum[kEndThreads / kWave];
+    int live;
+};
+
+__device__ __forceinline__ int tail_scan(int v, int *sum, int *total) {
+    const int wid = threadIdx.x / kWave, incl = wave_inclusive_sum(v);
+    if (lane_id() == kWave - 1) sum[wid] = incl;
+    __syncthreads();
+    int off = 0, all = 0;
+    for (int i = 0; i < kEndThreads / kWave; ++i) {
+        off += i < wid ? sum[i] : 0;
+        all += sum[i];
+    }
+    __syncthreads();
+    *total = all;
+    return off + incl - v;
+}
+
+template <bool kPairs, bool kB>
+__global__ void __launch_bounds__(kEndThreads) k_staged_tail(Graph g, State s, int round,
+                                                              uint32_t *bits, int64_t *report) {
+    extern __shared__ __align__(16) unsigned char tail_lds[];
+    TailShared &S = *reinterpret_cast<TailShared *>(tail_lds);
+    const int tid = threadIdx.x, k = round & 1;
+    const int64_t live = live_edges(s, round);
+    if (live == 0 || live > kEndEdges) {
+        if (tid == 0) {
+            report[0] = live == 0;
+            report[1] = live;
+        }
+        return;
+    }
+    // Gather: each thread takes the lists of consecutive waves.
+    const int waves = s.grid * kWaves, per = (waves + kEndThreads - 1) / kEndThreads;
+    const int64_t range = s.region / kWaves;
+    const int w0 = tid * per, w1 = min(w0 + per, waves);
+    int mine = 0, E;
+    for (int w = w0; w < w1; ++w) mine += s.rec_c[k][w];
+    int at = tail_scan(mine, S.sum, &E);
+    for (int w = w0; w < w1 && mine > 0; ++w) {
+        const int n = s.rec_c[k][w];
+        for (int i = 0; i < n; ++i, ++at) {
+            const int64_t from = w * range + i;
+            const int e = s.list[k][from];
+            S.key[at] = s.rec_key[k][from];
+            S.base[at] = kPairs ? 2 * e : s.rec_a[k][from];
+            S.start[at] = kPairs ? 2 : s.rec_b[k][from];  // the count, until the scan below
+            S.vb[at] = kB ? s.rec_vb[k][from] : 0;
+            S.flag[at] = (uint32_t)e;
+        }
+    }
+    __syncthreads();
+    constexpr int kOwn = kEndEdges / kEndThreads;  // edges per thread
+    int e[kOwn], len[kOwn], pins = 0;
+    bool alive[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const int j = tid * kOwn + q;
+        alive[q] = j < E;
+        e[q] = j < E ? (int)S.flag[j] : 0;
+        len[q] = j < E ? S.start[j] : 0;
+        pins += len[q] < kEndPins ? len[q] : kEndPins + 1;
+        pins = pins < kEndPins ? pins : kEndPins + 1;
+    }
+    int total;
+    int first = tail_scan(pins, S.sum, &total);
+    if (total > kEndPins) {  // left to the grid's rounds
+        if (tid == 0) {
+            report[0] = 0;
+            report[1] = live;
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const int j = tid * kOwn + q;
+        if (j < E) {
+            S.start[j] = first;
+            S.base[j] -= first;
+            S.flag[j] = 0;
+        } else {
+            S.start[j] = total;
+        }
+        first += len[q];
+    }
+    for (int i = tid; i < kEndSlots; i += kEndThreads) S.id[i] = -1;
+    for (int i = tid; i < kEndSlots / 32; i += kEndThreads) S.done[i] = 0;
+    for (int w = w0; w < w1; ++w) s.rec_c[k][w] = 0;
+    __syncthreads();
+    // This thread's pins: their edge and their vertex's slot.
+    int own[kEndPerThread], v[kEndPerThread];
+#pragma unroll
+    for (int i = 0; i < kEndPerThread; ++i) {
+        const int t = i * kEndThreads + tid;
+        own[i] = -1;
+        v[i] = 0;
+        if (t < total) {
+            int j = 0;  // the last edge that starts at or before t (empty ones end where they start)
+#pragma unroll
+            for (int step = kEndEdges / 2; step > 0; step >>= 1)
+                if (S.start[j + step] <= t) j += step;
+            own[i] = j;
+            v[i] = g.e_pins[S.base[j] + t] + (kB ? S.vb[j] : 0);
+        }
+    }
+    int slot[kEndPerThread];
+#pragma unroll
+    for (int i = 0; i < kEndPerThread; ++i) {
+        slot[i] = 0;
+        if (own[i] >= 0) {  // at most kEndPins of kEndSlots are taken: a free one is found
+            uint32_t h = __umulhi((uint32_t)v[i] * 0x9E3779B1u, (uint32_t)kEndSlots);
+            for (;;) {
+                const int id = atomicCAS(&S.id[h], -1, v[i]);
+                if (id == -1 || id == v[i]) break;
+                h = h + 1 < kEndSlots ? h + 1 : 0;
+            }
+            slot[i] = (int)h;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < kEndSlots; i += kEndThreads) S.best[i] = 0;
+    __syncthreads();
+    constexpr uint32_t kLost = 1, kDead = 2, kWon = 4;
+    uint32_t open = 0;  // this thread's pins whose edge is alive
+#pragma unroll
+    for (int i = 0; i < kEndPerThread; ++i) open |= own[i] >= 0 ? 1u << i : 0;
+    for (;;) {
+#pragma unroll
+        for (int i = 0; i < kEndPerThread; ++i)
+            if (open >> i & 1) atomicMax(&S.best[slot[i]], (unsigned long long)S.key[own[i]]);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kEndPerThread; ++i)
+            if ((open >> i & 1) && S.best[slot[i]] != S.key[own[i]]) atomicOr(&S.flag[own[i]], kLost);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+            const int j = tid * kOwn + q;
+            if (alive[q]) {
+                if (S.flag[j] & kLost) {
+                    S.flag[j] = 0;
+                } else {
+                    const int bit = kB ? e[q] + g.bitoff[e[q]] : e[q];
+                    atomicOr(&bits[bit >> 5], 1u << (bit & 31));
+                    S.flag[j] = kWon;
+                    alive[q] = false;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kEndPerThread; ++i)
+            if (open >> i & 1) {
+                S.best[slot[i]] = 0;
+                if (S.flag[own[i]] & kWon) {
+                    atomicOr(&S.done[slot[i] >> 5], 1u << (slot[i] & 31));
+                    open &= ~(1u << i);
+                }
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kEndPerThread; ++i)
+            if ((open >> i & 1) && (S.done[slot[i] >> 5] >> (slot[i] & 31) & 1))
+                atomicOr(&S.flag[own[i]], kDead);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kEndPerThread; ++i)
+            if ((open >> i & 1) && (S.flag[own[i]] & kDead)) open &= ~(1u << i);
+        int left = 0;
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+            alive[q] = alive[q] && !(S.flag[tid * kOwn + q] & kDead);
+            left |= alive[q];
+        }
+        if (!__syncthreads_or(left)) break;
+    }
+    if (tid == 0) {
+        report[0] = 1;
+        report[1] = 0;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
+                               uint32_t *bits) {
+    const dim3 grid(L.grid / 4 + 2), block(kSetupThreads);
+    if (g.vbase)
+        hipLaunchKernelGGL(k_staged_setup<true>, grid, block, 0, L.stream, g, s, seed, bits);
+    else
+        hipLaunchKernelGGL(k_staged_setup<false>, grid, block, 0, L.stream, g, s, seed, bits);
+    return hipGetLastError();
+}
+
+hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, int round,
+                              int first, uint32_t seed) {
+    const dim3 grid(s.grid), block(kBlock);
+    if (g.pairs)
+        hipLaunchKernelGGL((k_staged_join<true, false>), grid, block, 0, L.stream, g, s, round,
+                           first, seed);
+    else if (g.vbase)
+        hipLaunchKernelGGL((k_staged_join<false, true>), grid, block, 0, L.stream, g, s, round,
+                           first, seed);
+    else
+        hipLaunchKernelGGL((k_staged_join<false, false>), grid, block, 0, L.stream, g, s, round,
+                           first, seed);
+    return hipGetLastError();
+}
+
+hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, int round,
+                              uint32_t *bits) {
+    const dim3 grid(s.grid), block(kBlock);
+    if (g.pairs)
+        hipLaunchKernelGGL((k_staged_test<true, false>), grid, block, 0, L.stream, g, s, round,
+                           bits);
+    else if (g.vbase)
+        hipLaunchKernelGGL((k_staged_test<false, true>), grid, block, 0, L.stream, g, s, round,
+                           bits);
+    else
+        hipLaunchKernelGGL((k_staged_test<false, false>), grid, block, 0, L.stream, g, s, round,
+                           bits);
+    return hipGetLastError();
+}
+
+template <bool kPairs, bool kB>
+static hipError_t launch_tail_as(const Launch &L, const Graph &g, const State &s, int round,
+                                 uint32_t *bits, int64_t *report) {
+    static std::atomic<bool> allowed{false};
+    if (!allowed.load(std::memory_order_relaxed)) {
+        const hipError_t rc =
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_staged_tail<kPairs, kB>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TailShared));
+        if (rc != hipSuccess) return rc;
+        allowed.store(true, std::memory_order_relaxed);
+    }
+    hipLaunchKernelGGL((k_staged_tail<kPairs, kB>), dim3(1), dim3(kEndThreads),
+                       sizeof(TailShared), L.stream, g, s, round, bits, report);
+    return hipGetLastError();
+}
+
+hipError_t launch_staged_tail(const Launch &L, const Graph &g, const State &s, int round,
+                              uint32_t *bits, int64_t *report) {
+    if (g.pairs) return launch_tail_as<true, false>(L, g, s, round, bits, report);
+    if (g.vbase) return launch_tail_as<false, true>(L, g, s, round, bits, report);
+    return launch_tail_as<false, false>(L, g, s, round, bits, report);
+}
+
+}  // namespace hgm
