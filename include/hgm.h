@@ -125,9 +125,15 @@ typedef struct hgm_opts {
                                 matched whole by one workgroup each, every
                                 round inside it, with their per-vertex state
                                 in LDS; the others go through the round
-                                kernels together.  0 = library default
-                                (the batch's kappa_total / 1024, clamped to
-                                [2^12, 2^20]), -1 = none. */
+                                kernels together.  0 = library default (calls
+                                that want only the matching: 2^20, or none
+                                where the longest instance would outlast the
+                                round kernels on the whole batch; others: the
+                                batch's kappa_total / 1024, clamped to
+                                [2^12, 2^20]), -1 = none.
+                                hgm_match: an instance of at most 1024 edges
+                                and this many pins is matched by one
+                                workgroup (0 = 2^17, -1 = never). */
     /* Schedule (any value gives the same result; hgm_tune picks them per
      * shape).  0 = library default for each. */
     int32_t edge_grid;       /* workgroups of the edge-centric kernels, each

@@ -380,13 +380,8 @@ int device_cus() {
     return cus;
 }
 
-// Workgroups of the solo kernel: one per compute unit (each holds up to the
-// whole LDS of its unit).
-int solo_workgroups() { return std::max(1, device_cus()); }
-
-// Dynamic LDS of a solo workgroup on the current device: all a workgroup may
-// hold less the solo kernel's own shared variables (a multiple of 256).
-int solo_lds_bytes() {
+// LDS a workgroup may hold on the current device (0 on a HIP error).
+int device_lds() {
     static std::atomic<int> cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
@@ -397,11 +392,21 @@ int solo_lds_bytes() {
     int bytes = 0;
     if (hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
             hipSuccess ||
-        bytes <= kSoloStaticLds + 16384)
+        bytes <= 0)
         return 0;
-    const int dyn = (bytes - kSoloStaticLds) & ~255;
-    if (dev >= 0 && dev < 64) cached[dev].store(dyn, std::memory_order_relaxed);
-    return dyn;
+    if (dev >= 0 && dev < 64) cached[dev].store(bytes, std::memory_order_relaxed);
+    return bytes;
+}
+
+// Workgroups of the solo kernel: one per compute unit (each holds up to the
+// whole LDS of its unit).
+int solo_workgroups() { return std::max(1, device_cus()); }
+
+// Dynamic LDS of a solo workgroup on the current device: all a workgroup may
+// hold less the solo kernel's own shared variables (a multiple of 256).
+int solo_lds_bytes() {
+    const int bytes = device_lds();
+    return bytes > kSoloStaticLds + 16384 ? (bytes - kSoloStaticLds) & ~255 : 0;
 }
 
 // Best-tile vertices of an instance with nv vertices (k_solo's layout: the
@@ -860,7 +865,7 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
     s.region = (int)((chunks + most - 1) / most) * kBlock;
     s.grid = (int)((chunks * kBlock + s.region - 1) / s.region);
     if (batch) HGM_TRY(launch_batch_setup(L, g, *batch, s));
-    HGM_TRY(launch_staged_setup(L, g, s, seed, bits));
+    HGM_TRY(launch_staged_setup(L, g, s, seed, bits, batch));
     // Round 0 admits up to the first threshold with at least kStagedFirstEdges
     // edges above it.
     const double part[kStagedSteps - 1] = {1.0 / 2700, 1.0 / 250, 1.0 / 33, 0.1, 0.2, 0.5};
@@ -933,6 +938,82 @@ void *scratch_address() {
     return p;
 }
 
+// The lists of a solo job, in the call's workspace.
+void solo_lists(SoloJob *J, const State &s) {
+    for (int k = 0; k < 2; ++k) {
+        J->list[k] = s.list[k];
+        J->rec_a[k] = s.rec_a[k];
+        J->rec_b[k] = s.rec_b[k];
+        J->rec_c[k] = s.rec_c[k];
+        J->rec_key[k] = s.rec_key[k];
+    }
+}
+
+// One instance in one workgroup (solo.hip): small instances, where a round
+// costs barriers instead of two launches.  *ran = false: not for this call.
+// With statistics or priorities redrawn every round the rounds are exact.
+int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
+               hipStream_t stream, uint32_t seed, uint32_t *bits, hgm_stats *stats, bool *ran) {
+    *ran = false;
+    const int64_t bound = o.solo_max_kappa ? o.solo_max_kappa : kSoloOneKappa;
+    if (g.m == 0 || g.m > kSoloOneThreads || g.kappa > bound || o.variant == HGM_VARIANT_CREW ||
+        o.validate || o.max_rounds > 0 || o.tail_pins > 0 || o.bin_shift > 0 ||
+        (stats && stats->timing))
+        return HGM_OK;
+    const int lds = device_lds();
+    if (g.n > solo_one_max_verts(lds, stats || o.reseed)) return HGM_OK;
+    SoloJob J;
+    memset(&J, 0, sizeof(J));
+    J.n = g.n;
+    J.m = g.m;
+    J.e_off = g.e_off;
+    J.e_pins = g.e_pins;
+    J.w = g.w;
+    J.seed = seed;
+    J.bits = bits;
+    J.exact = stats || o.reseed ? 1 : 0;
+    J.reseed = o.reseed ? 1 : 0;
+    J.ctl = (unsigned long long *)s.stats;
+    J.rows = J.ctl + kSoloJobHeader;
+    J.row_cap = (int)((sizeof(RoundStats) / 8 * (size_t)lay.ring - kSoloJobHeader) / 5);
+    solo_lists(&J, s);
+    HGM_TRY(launch_solo_one(stream, J, g.pairs != 0, lds));
+    if (!stats) {
+        HGM_TRY(hipStreamSynchronize(stream));
+        *ran = true;
+        return HGM_OK;
+    }
+    std::vector<unsigned long long> head(kSoloJobHeader + 5 * (size_t)std::min(kSoloRowsFirst,
+                                                                               J.row_cap));
+    HGM_TRY(hipMemcpyAsync(head.data(), J.ctl, 8 * head.size(), hipMemcpyDeviceToHost, stream));
+    HGM_TRY(hipStreamSynchronize(stream));
+    const int64_t rounds = (int64_t)head[kSoloJobRounds];
+    if (rounds > J.row_cap) return HGM_OK;  // more rounds than rows: the round kernels count them
+    const size_t need = kSoloJobHeader + 5 * (size_t)rounds;
+    if (need > head.size()) {
+        head.resize(need);
+        HGM_TRY(hipMemcpyAsync(head.data(), J.ctl, 8 * need, hipMemcpyDeviceToHost, stream));
+        HGM_TRY(hipStreamSynchronize(stream));
+    }
+    stats->rounds = (int32_t)rounds;
+    stats->matched = (int64_t)head[kSoloJobMatched];
+    stats->weight = head[kSoloJobWeight];
+    for (int c = 0; c < HGM_K_CLASSES; ++c) {
+        stats->kernel_ms[c] = 0.0;
+        stats->kernel_launches[c] = 0;
+    }
+    for (int r = 0; r < rounds && r < stats->cap; ++r) {
+        const unsigned long long *row = &head[kSoloJobHeader + 5 * (size_t)r];
+        if (stats->live_edges) stats->live_edges[r] = (int64_t)row[0];
+        if (stats->live_pins) stats->live_pins[r] = (int64_t)row[1];
+        if (stats->matched_per_round) stats->matched_per_round[r] = (int64_t)row[2];
+        if (stats->matched_pins) stats->matched_pins[r] = (int64_t)row[4];
+        if (stats->round_ms) stats->round_ms[r] = 0.f;
+    }
+    *ran = true;
+    return HGM_OK;
+}
+
 // Shared body of hgm_match and hgm_match_noalloc.
 int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *workspace,
               size_t ws_bytes, const hgm_opts *opts, void *stream, hgm_stats *stats,
@@ -967,6 +1048,9 @@ int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *w
     L.grid = device_cus() * o.blocks_per_cu;
     L.stream = (hipStream_t)stream;
     if (L.grid <= 0) return HGM_E_HIP;
+    bool ran = false;
+    rc = match_solo(g, o, lay, s, L.stream, seed, matched_bits, stats, &ran);
+    if (rc != HGM_OK || ran) return rc;
     if (g.m > 0 && staged_call(o, stats))
         return run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate);
     return run_rounds(g, o, lay, s, L, seed, matched_bits, stats, nullptr);
@@ -1102,7 +1186,50 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         sa.max_verts = solo_verts_for(sa.lds_bytes, kSoloMaxTiles);
         sa.max_rounds = o.max_rounds;
     }
-    if (b->m_total > 0 && staged_call(o, stats) && !s.explicit0)
+    // Calls that want only the matching run the solo part by admission
+    // (solo.hip), unless the mean instance alone is too long for it.
+    const size_t order_room = s.solo ? 40 * (size_t)lay.solo_rounds : 0;
+    const bool too_long = o.solo_max_kappa == 0 && b->count > 0 &&
+                          b->kappa_total / b->count > kSoloShort + b->kappa_total / kSoloShare;
+    if (s.explicit0 && staged_call(o, stats) && b->m_total > 0 && !too_long &&
+        4 * (size_t)b->count <= order_room) {
+        SoloJob J;
+        memset(&J, 0, sizeof(J));
+        J.e_off = b->e_off;
+        J.e_pins = b->e_pins;
+        J.w = b->w;
+        J.bits = matched_bits;
+        J.count = b->count;
+        J.v_base = b->v_base;
+        J.e_base = b->e_base;
+        J.pin_base = b->pin_base;
+        J.word_base = b->word_base;
+        J.seeds = b->seeds;
+        J.max_kappa = o.solo_max_kappa ? o.solo_max_kappa : kSoloBatchKappa;
+        J.max_verts = sa.max_verts;
+        J.ctl = s.solo;
+        J.order = (int32_t *)(s.solo + kSoloJobHeader);
+        solo_lists(&J, s);
+        J.choose = o.solo_max_kappa == 0 ? 1 : 0;
+        HostSlot slot(true);
+        int64_t listed[2] = {0, 0};  // in the solo part, left to the round kernels
+        J.report = slot.get() ? (int64_t *)slot.get() : (int64_t *)(s.hot + kSub / 2);
+        const bool all = b->kappa_total <= (J.choose ? kSoloShort : J.max_kappa) &&
+                         b->n_total <= J.max_verts;
+        if (!all) HGM_TRY(launch_zero(L, matched_bits, b->words_total));
+        HGM_TRY(launch_solo_batch(L.stream, J, b->n_total, device_cus(), device_lds()));
+        if (!slot.get())
+            HGM_TRY(hipMemcpyAsync(listed, J.report, sizeof(listed), hipMemcpyDeviceToHost,
+                                   L.stream));
+        HGM_TRY(hipStreamSynchronize(L.stream));
+        if (slot.get()) memcpy(listed, J.report, sizeof(listed));
+        if (listed[1] == 0) return HGM_OK;
+        in.mark_done = listed[0] > 0;
+        in.solo_max_kappa = J.max_kappa;
+        in.solo_max_verts = J.max_verts;
+        return run_staged(g, o, s, L, 0, matched_bits, &in, true);
+    }
+    if (b->m_total > 0 && staged_call(o, stats) && (!s.explicit0 || too_long))
         return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     return run_rounds(g, o, lay, s, L, 0, matched_bits, stats, &in, &sa);
 }

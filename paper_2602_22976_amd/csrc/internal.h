@@ -90,6 +90,9 @@ struct BatchIn {
     int32_t *bitoff;          // out [m_total]
     int32_t *gvoff;           // out [n_total + 1] (NULL: no vertex side)
     int32_t *ebase;           // out [n_total]
+    int32_t mark_done;        // the solo part has matched the instances within these
+    int64_t solo_max_kappa;   // bounds: their bits stand, their vertices are done
+    int32_t solo_max_verts;   // (rounds by admission)
 };
 
 // Device state of one hgm_match call, carved out of the caller's workspace.
@@ -215,6 +218,55 @@ __host__ __device__ __forceinline__ bool solo_instance(int64_t n_i, int64_t kapp
     return kappa_i <= a.max_kappa && n_i <= a.max_verts;
 }
 
+// Work of the one-workgroup kernels of solo.hip: one instance (the first
+// group) or the solo instances of a batch (count and the base arrays, the
+// caller's; e_off and the ids are local to an instance).  The lists are the
+// State's, at each instance's edge range, and free until the round kernels
+// start.
+constexpr int kSoloOneThreads = 1024;  // one instance
+// Batches: threads of a workgroup and workgroups per compute unit, for the
+// instances whose maxima fit a small workgroup's share of LDS and the others.
+constexpr int kSoloSmallThreads = 256, kSoloSmallPerCu = 4;
+constexpr int kSoloWideThreads = 1024, kSoloWidePerCu = 1;
+// Words of SoloJob::ctl.  Batch: the next small instance to take, the solo
+// instances listed, the wide instances listed (they come first) and the next of
+// them to take.  Exact calls: rounds run, edges matched, their weight.
+constexpr int kSoloJobNextSmall = 0, kSoloJobCount = 1, kSoloJobNextWide = 2, kSoloJobWide = 3,
+              kSoloJobRounds = 4, kSoloJobMatched = 5, kSoloJobWeight = 6, kSoloJobHeader = 8;
+struct SoloJob {
+    int32_t n, m;
+    const int32_t *e_off, *e_pins;
+    const uint32_t *w;
+    uint32_t seed;
+    uint32_t *bits;
+    int32_t exact;       // every edge in round 0; rounds counted
+    int32_t reseed;      // priorities redrawn every round (with exact)
+    int32_t lds_bytes;   // dynamic LDS of a workgroup: done bits, then maxima
+    int32_t row_cap;     // rounds whose counts fit rows (exact)
+    unsigned long long *ctl, *rows;
+    int32_t *list[2], *rec_a[2], *rec_b[2], *rec_c[2];
+    uint64_t *rec_key[2];
+    int32_t count;
+    const int64_t *v_base, *e_base, *pin_base, *word_base;
+    const uint32_t *seeds;
+    int32_t *order;      // [count] solo instances, longest first
+    int64_t max_kappa;
+    int32_t max_verts, small_verts;
+    int64_t *report;     // {instances listed, instances left to the round kernels}
+    int32_t choose;      // leave the solo part out where the round kernels are faster
+};
+// The solo part runs when its longest instance has at most kSoloShort pins and
+// a kSoloShare-th of the batch's.
+constexpr int64_t kSoloShort = 24 * 1024, kSoloShare = 128;
+// LDS of the done bits of n vertices; the maxima follow when they fit.
+__host__ __device__ __forceinline__ int64_t solo_done_bytes(int64_t n) {
+    return (4 * ((n + 31) / 32) + 15) & ~(int64_t)15;
+}
+// lds: LDS of a compute unit.  Most vertices of one instance (exact: a slot each):
+int solo_one_max_verts(int lds, bool exact);
+hipError_t launch_solo_one(hipStream_t stream, SoloJob J, bool pairs, int lds);
+hipError_t launch_solo_batch(hipStream_t stream, SoloJob J, int64_t n_total, int cus, int lds);
+
 constexpr int kStagedSteps = 7;  // admission steps of staged.hip
 
 struct Launch {
@@ -238,6 +290,7 @@ hipError_t launch_batch_setup(const Launch &L, const Graph &g, const BatchIn &b,
 // Solo part of a batch, then the explicit round-0 list of the other instances.
 hipError_t launch_solo(const Launch &L, const Graph &g, const State &s, const SoloArgs &a,
                        uint32_t *bits, int rekey, int workgroups);
+hipError_t launch_zero(const Launch &L, uint32_t *p, int64_t words);
 hipError_t launch_live0(const Launch &L, const Graph &g, const State &s, const SoloArgs &a);
 hipError_t launch_validate(const Launch &L, const Graph &g, const State &s, int check_dual);
 hipError_t launch_scatter(const Launch &L, const Graph &g, const State &s, uint32_t kseed);
@@ -256,7 +309,7 @@ hipError_t launch_test(const Launch &L, const Graph &g, const State &s, int roun
                        uint32_t *bits, uint32_t kseed);
 // Rounds by admission (staged.hip).  `first`: the admission step of round 0.
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
-                               uint32_t *bits);
+                               uint32_t *bits, const BatchIn *batch);
 hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, int round,
                               int first, uint32_t seed);
 hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, int round,

@@ -2187,6 +2187,11 @@ hipError_t launch_tail(const Launch &L, const Graph &g, const State &s, int roun
     return hipGetLastError();
 }
 
+hipError_t launch_zero(const Launch &L, uint32_t *p, int64_t words) {
+    hipLaunchKernelGGL(k_zero_words, dim3(L.grid), dim3(kBlock), 0, L.stream, p, words);
+    return hipGetLastError();
+}
+
 hipError_t launch_validate(const Launch &L, const Graph &g, const State &s, int check_dual) {
     if (check_dual)
         hipLaunchKernelGGL(k_zero_words, dim3(L.grid), dim3(kBlock), 0, L.stream, s.vbits,

@@ -38,6 +38,11 @@ inline int64_t solo_auto_bound(int64_t kappa_total) {
     const int64_t b = kappa_total / kSoloAutoDivisor;
     return b < kSoloAutoMin ? kSoloAutoMin : b > kSoloAutoMax ? kSoloAutoMax : b;
 }
+// Calls that want only the matching: the solo part takes instances of a batch
+// up to kSoloBatchKappa pins, and hgm_match runs an instance of at most 1,024
+// edges and kSoloOneKappa pins in one workgroup (tiny: 50 -> 28 us).
+constexpr int64_t kSoloBatchKappa = (int64_t)1 << 20;
+constexpr int64_t kSoloOneKappa = (int64_t)1 << 17;
 // Rounds by admission: workgroups of the join and the test (at 1536: power-law
 // 444 against 377 us, hub-stress 562 against 497, RGG 453 against 429).
 constexpr int kStagedGrid = 1024;

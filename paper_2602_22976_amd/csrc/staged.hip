@@ -37,6 +37,7 @@ namespace {
 
 constexpr int kWaves = kBlock / kWave;
 constexpr int kKeepPins = 8;  // blocks of pins kept in registers (flat_edges)
+constexpr int kFill = 16;     // chunks of edges looked at in one step (join_wave)
 
 // Thresholds by sampling, in one workgroup: 256 groups of 16 keys.  The largest
 // of each group gives 256 maxima, of which the one of rank r has about
@@ -85,7 +86,7 @@ __device__ __forceinline__ int rank_of(const uint64_t *keys, int i, int part) {
 // Clears the state; workgroup 0 clears the counters and draws the thresholds.
 template <bool kB>
 __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s, uint32_t seed,
-                                                                uint32_t *bits) {
+                                                                uint32_t *bits, int keep_bits) {
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
         __shared__ uint64_t top[kSampleGroups], one[kSampleGroups];
@@ -129,7 +130,24 @@ __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s
     }
     uint32_t *done = done_bits(s);
     for (int64_t i = at; i < (g.n + 31) / 32; i += stride) done[i] = 0;
-    for (int64_t i = at; i < g.words; i += stride) bits[i] = 0;
+    if (!keep_bits)
+        for (int64_t i = at; i < g.words; i += stride) bits[i] = 0;
+}
+
+// Marks every vertex of the instances the solo part has matched.
+__global__ void __launch_bounds__(kBlock) k_staged_mark_solo(State s, BatchIn b) {
+    uint32_t *done = done_bits(s);
+    for (int i = blockIdx.x; i < b.count; i += gridDim.x) {
+        const int64_t v0 = b.v_base[i], v1 = b.v_base[i + 1];
+        if (v1 - v0 > b.solo_max_verts || b.pin_base[i + 1] - b.pin_base[i] > b.solo_max_kappa)
+            continue;
+        for (int64_t w = (v0 >> 5) + threadIdx.x; w * 32 < v1; w += kBlock) {
+            uint32_t m = 0xFFFFFFFFu;
+            if (w * 32 < v0) m &= 0xFFFFFFFFu << (v0 & 31);
+            if (w * 32 + 32 > v1) m &= 0xFFFFFFFFu >> (32 - (v1 & 31));
+            atomicOr(&done[w], m);  // neighbouring instances share words
+        }
+    }
 }
 
 // The live list of wave `wave`: its edge range [lo, lo + per) and its slots.
@@ -213,7 +231,7 @@ template <bool kPairs, bool kB>
 __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int round, int first,
                                                         uint32_t seed) {
     __shared__ WaveScratch scratch[kWaves];
-    __shared__ int queue[kWaves][kCand];
+    __shared__ int queue[kWaves][cand_size(kFill)];
     const int wid = threadIdx.x / kWave;
     const WaveRange range = wave_range(s);
     const int to = round & 1, from = to ^ 1;
@@ -226,7 +244,7 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
             all[i] = make_ulonglong2(0, 0);
     }
     const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
-    const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps>(
+    const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
         m, scratch[wid], queue[wid], g.e_pins, lists(s, from), lists(s, to), range.lo, end,
         round > 0 ? s.rec_c[from][range.wave] : 0, round == 0, first + round, step_bytes(s),
         reinterpret_cast<const uint64_t *>(s.hot));
@@ -486,12 +504,15 @@ __global__ void __launch_bounds__(kEndThreads) k_staged_tail(Graph g, State s, i
 }  // namespace
 
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
-                               uint32_t *bits) {
+                               uint32_t *bits, const BatchIn *batch) {
     const dim3 grid(L.grid / 4 + 2), block(kSetupThreads);
+    const int keep = batch && batch->mark_done;
     if (g.vbase)
-        hipLaunchKernelGGL(k_staged_setup<true>, grid, block, 0, L.stream, g, s, seed, bits);
+        hipLaunchKernelGGL(k_staged_setup<true>, grid, block, 0, L.stream, g, s, seed, bits, keep);
     else
-        hipLaunchKernelGGL(k_staged_setup<false>, grid, block, 0, L.stream, g, s, seed, bits);
+        hipLaunchKernelGGL(k_staged_setup<false>, grid, block, 0, L.stream, g, s, seed, bits, keep);
+    if (keep)
+        hipLaunchKernelGGL(k_staged_mark_solo, dim3(L.grid), dim3(kBlock), 0, L.stream, s, *batch);
     return hipGetLastError();
 }
 

@@ -247,9 +247,9 @@ struct WaveLists {
 // key) (the key of a listed edge this round), place(e, base, len, vb), sort(e,
 // w, k) / exact_sort(e, w) (weight or key that the thresholds are compared
 // with), entered(len).
-constexpr int kFill = 16;  // chunks of 64 edges looked at in one step, at most
-constexpr int kCand = (kFill + 1) * kWave;
-template <bool kPairs, bool kB, int kKeep, int kSteps, class M>
+// kFill: chunks of 64 edges looked at in one step, at most (a multiple of 4).
+constexpr int cand_size(int fill) { return (fill + 1) * kWave; }
+template <bool kPairs, bool kB, int kKeep, int kSteps, int kFill, class M>
 __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const int32_t *e_pins,
                                          const WaveLists &from, const WaveLists &to, int64_t lo,
                                          int64_t end, int listed, bool first_round, int step,
