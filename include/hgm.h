@@ -155,8 +155,10 @@ typedef struct hgm_opts {
                                 35 for graphs; at most 400) */
     int32_t tail_pins;       /* hgm_match: once a round has at most this many
                                 live pins (and at most 65536 live edges), one
-                                workgroup runs every remaining round
-                                (0 = library default: never; -1 = never) */
+                                workgroup runs every remaining round.
+                                0 = library default: at most 2048 edges with
+                                8192 pins, their state in LDS (not with
+                                stats->timing); -1 = never */
     int32_t bin_shift;       /* hgm_match, AUTO with the vertex side, offset
                                 layout: the next round's per-vertex maximum
                                 by propagation blocking instead of atomics,

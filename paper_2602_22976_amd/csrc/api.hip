@@ -7,6 +7,7 @@
 #include <atomic>
 #include <cmath>
 #include <mutex>
+#include <optional>
 #include <vector>
 
 #include "hgm.h"
@@ -66,6 +67,7 @@ struct Opts {
     int64_t solo_max_kappa;  // batches: solo part bound (-1: no solo part, 0: by size)
     int edge_grid, blocks_per_cu, clear_ratio, hot_degree, first_batch_pct;  // 0 = per kind
     int64_t tail_pins;  // one instance: tail bound (-1: no tail)
+    bool ending;        // the last rounds in one workgroup (ending.hip)
     int bin_shift;      // binned maximum: log2 vertices per bin, 0 automatic, -1 off
     bool reseed;            // priorities redrawn every round (round_seed)
     bool pairs;             // graph: two pins per edge at e_pins[2e], no offsets
@@ -106,6 +108,7 @@ int resolve_opts(const hgm_opts *in, Opts *o) {
     o->first_batch_pct = d.first_batch_pct;  // 0: resolved per instance (graphs differ)
     if (d.tail_pins < -1) return HGM_E_ARG;
     o->tail_pins = d.tail_pins == 0 ? kDefaultTailPins : d.tail_pins;
+    o->ending = d.tail_pins == 0;
     if (d.bin_shift != -1 && d.bin_shift != 0 &&
         (d.bin_shift < kBinMinShift || d.bin_shift > kBinMaxShift))
         return HGM_E_ARG;
@@ -515,6 +518,76 @@ struct KernelTimer {
         if ((expr) != hipSuccess) return HGM_E_HIP;     \
     } while (0)
 
+// Pinned host memory that kernels write a call's last words to: a copy to
+// pageable memory takes about 20 us more.  One page per process, allocated on
+// the first call that may allocate and kept until the process ends, in slots
+// that a call holds while it runs; a call that finds no slot copies instead.
+class HostSlot {
+  public:
+    static constexpr int kSlots = 32;
+    static constexpr size_t kBytes = 4096;
+    explicit HostSlot(bool may_allocate) {
+        std::lock_guard<std::mutex> lk(mu());
+        Pool &P = pool();
+        if (!P.page && may_allocate && !P.failed) {
+            void *p = nullptr;
+            if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable | hipHostMallocMapped) ==
+                hipSuccess) {
+                P.page = (char *)p;
+            } else {
+                P.failed = true;
+                (void)hipGetLastError();
+            }
+        }
+        for (int i = 0; P.page && i < kSlots && at_ < 0; ++i)
+            if (!(P.used >> i & 1)) {
+                P.used |= 1u << i;
+                at_ = i;
+                host_ = P.page + i * kBytes;
+            }
+    }
+    ~HostSlot() {
+        if (at_ < 0) return;
+        std::lock_guard<std::mutex> lk(mu());
+        pool().used &= ~(1u << at_);
+    }
+    HostSlot(const HostSlot &) = delete;
+    HostSlot &operator=(const HostSlot &) = delete;
+    // NULL: none free.  Valid on the device under the same address.
+    void *get() const { return host_; }
+
+  private:
+    struct Pool {
+        char *page = nullptr;
+        bool failed = false;
+        uint32_t used = 0;
+    };
+    static Pool &pool() {
+        static Pool p;
+        return p;
+    }
+    static std::mutex &mu() {
+        static std::mutex m;
+        return m;
+    }
+    int at_ = -1;
+    char *host_ = nullptr;
+};
+
+// Rows of a round's counts that fit a slot behind the report's header.
+constexpr int kSlotRows = (int)((HostSlot::kBytes / 8 - kEndHeader) / 5);
+
+EndArgs end_args(const State &s, unsigned long long *report) {
+    EndArgs a;
+    memset(&a, 0, sizeof(a));
+    a.report = report;
+    a.run = 1;
+    for (int k = 0; k < 2; ++k) a.counts[k] = s.cnt[k];
+    a.lists = s.grid;
+    a.stride = s.region;
+    return a;
+}
+
 // Enqueues setup and rounds, checking termination on the host every batch of
 // rounds; shared by the single-instance and the batched entry point.
 int solo_workgroups();
@@ -525,7 +598,7 @@ constexpr int kSoloRowsFirst = 64;
 
 int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s, const Launch &L,
                uint32_t seed, uint32_t *matched_bits, hgm_stats *stats, const BatchIn *batch,
-               const SoloArgs *solo = nullptr) {
+               const SoloArgs *solo = nullptr, bool may_allocate = true) {
     int init_flags = 0;
     if (uses_live_key(o)) init_flags |= kInitLiveKey | (o.reseed ? kInitLiveMark : 0);
     // Priority seed of round r.
@@ -614,8 +687,22 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     const bool tail_on = s.tail != nullptr;
     bool tail_missed = false;
     std::vector<unsigned long long> tail_head(kTailHeader + 5 * (size_t)kTailRowsFirst, 0);
+    // One instance: the last rounds run in one workgroup, which leaves the
+    // counts in pinned host memory.  The first batch of rounds goes on until
+    // that workgroup is expected to take over.
+    const bool graph = g.kappa == 2 * (int64_t)g.m;
+    std::optional<HostSlot> slot;
+    if (o.ending && !g.vbase && !T.on && !finished) slot.emplace(may_allocate);
+    unsigned long long *report = slot ? (unsigned long long *)slot->get() : nullptr;
     while (!finished) {
-        int batch = next_batch(o, launched, live_p, g.kappa == 2 * (int64_t)g.m);
+        int batch = next_batch(o, launched, live_p, graph);
+        if (report && o.adaptive && launched == 0) {
+            const double pins = (double)g.kappa;
+            const double most =
+                std::max(1.0, pins / std::min(kEndingPins, kEndingEdges * pins / (double)g.m));
+            batch = std::max(1, std::min(kAdaptiveMaxBatch,
+                                         (int)std::ceil(std::log(most) / (graph ? 1.45 : 1.3))));
+        }
         if (o.max_rounds > 0) batch = std::min(batch, o.max_rounds - launched);
         if (batch <= 0) return HGM_E_ROUND_LIMIT;
         const int first = launched;
@@ -650,6 +737,74 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
                 tail_launched = true;
                 if (!tail_missed) break;
             }
+        }
+        if (report && batch < kSlotRows) {
+            memset(report, 0, 8 * kEndHeader);
+            EndArgs a = end_args(s, report);
+            a.first = first;
+            a.round = launched;
+            a.seed = seed;
+            a.reseed = o.reseed ? 1 : 0;
+            a.max_rounds = o.max_rounds;
+            a.counting = 1;
+            a.rows = kSlotRows;
+            HGM_TRY(launch_end(L, g, s, a, matched_bits));
+            HGM_TRY(hipStreamSynchronize(L.stream));
+            if (report[kEndOverflow]) return HGM_E_CSR;
+            const unsigned long long *rows = report + kEndHeader;
+            auto take = [&](const unsigned long long *row) {
+                matched_r.push_back((int64_t)row[2]);
+                weight_r.push_back(row[3]);
+                matched_p.push_back((int64_t)row[4]);
+            };
+            for (int r = first; r < launched && !finished; ++r) {
+                take(rows + 5 * (r - first));
+                const unsigned long long *next = rows + 5 * (r + 1 - first);
+                if (next[0] == 0) {
+                    finished = true;
+                    rounds = r + 1;
+                } else {
+                    live_e.push_back((int64_t)next[0]);
+                    live_p.push_back((int64_t)next[1]);
+                }
+            }
+            const int end = (int)report[kEndRounds];
+            if (!finished && report[kEndFinished]) {
+                // Rounds launched .. end - 1 ran in the one workgroup.
+                const int n = end - launched;
+                std::vector<unsigned long long> packed, weights;
+                if (end - first > kSlotRows) {
+                    packed.resize(n);
+                    weights.resize(n);
+                    HGM_TRY(hipMemcpyAsync(packed.data(), s.rec_key[launched & 1], 8 * (size_t)n,
+                                           hipMemcpyDeviceToHost, L.stream));
+                    HGM_TRY(hipMemcpyAsync(weights.data(), s.rec_key[(launched & 1) ^ 1],
+                                           8 * (size_t)n, hipMemcpyDeviceToHost, L.stream));
+                    HGM_TRY(hipStreamSynchronize(L.stream));
+                }
+                for (int r = launched; r < end; ++r) {
+                    unsigned long long row[5];
+                    if (r - first < kSlotRows) {
+                        memcpy(row, rows + 5 * (r - first), sizeof(row));
+                    } else {
+                        const unsigned long long x = packed[r - launched];
+                        row[0] = x & 0xFFFF;
+                        row[1] = x >> 16 & 0xFFFF;
+                        row[2] = x >> 32 & 0xFFFF;
+                        row[3] = weights[r - launched];
+                        row[4] = x >> 48;
+                    }
+                    if (r > launched) {
+                        live_e.push_back((int64_t)row[0]);
+                        live_p.push_back((int64_t)row[1]);
+                    }
+                    take(row);
+                }
+                finished = true;
+                rounds = end;
+            }
+            if (!finished && o.max_rounds > 0 && end >= o.max_rounds) return HGM_E_ROUND_LIMIT;
+            continue;
         }
         // Copy the slots of rounds first .. launched (at most two ranges of the ring).
         for (int r = first; r <= launched;) {
@@ -800,62 +955,6 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
 }
 
 
-// Pinned host memory that kernels write a call's last words to: a copy to
-// pageable memory takes about 20 us more.  One page per process, allocated on
-// the first call that may allocate and kept until the process ends, in slots
-// that a call holds while it runs; a call that finds no slot copies instead.
-class HostSlot {
-  public:
-    static constexpr int kSlots = 32;
-    static constexpr size_t kBytes = 4096;
-    explicit HostSlot(bool may_allocate) {
-        std::lock_guard<std::mutex> lk(mu());
-        Pool &P = pool();
-        if (!P.page && may_allocate && !P.failed) {
-            void *p = nullptr;
-            if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable | hipHostMallocMapped) ==
-                hipSuccess) {
-                P.page = (char *)p;
-            } else {
-                P.failed = true;
-                (void)hipGetLastError();
-            }
-        }
-        for (int i = 0; P.page && i < kSlots && at_ < 0; ++i)
-            if (!(P.used >> i & 1)) {
-                P.used |= 1u << i;
-                at_ = i;
-                host_ = P.page + i * kBytes;
-            }
-    }
-    ~HostSlot() {
-        if (at_ < 0) return;
-        std::lock_guard<std::mutex> lk(mu());
-        pool().used &= ~(1u << at_);
-    }
-    HostSlot(const HostSlot &) = delete;
-    HostSlot &operator=(const HostSlot &) = delete;
-    // NULL: none free.  Valid on the device under the same address.
-    void *get() const { return host_; }
-
-  private:
-    struct Pool {
-        char *page = nullptr;
-        bool failed = false;
-        uint32_t used = 0;
-    };
-    static Pool &pool() {
-        static Pool p;
-        return p;
-    }
-    static std::mutex &mu() {
-        static std::mutex m;
-        return m;
-    }
-    int at_ = -1;
-    char *host_ = nullptr;
-};
-
 // Rounds by admission (staged.hip): calls that want only the matching.
 int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t seed,
                uint32_t *bits, const BatchIn *batch, bool may_allocate) {
@@ -874,8 +973,13 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
         ++first;
     const int admitted = kStagedSteps - first;  // rounds with an admission
     HostSlot slot(may_allocate);
-    int64_t copy[2] = {0, 0};
-    int64_t *report = slot.get() ? (int64_t *)slot.get() : (int64_t *)(s.hot + kSub / 2);
+    unsigned long long copy[kEndHeader] = {0};
+    unsigned long long *report = (unsigned long long *)slot.get();
+    if (!report) report = s.hot + kSub / 2;
+    EndArgs end = end_args(s, report);
+    for (int k = 0; k < 2; ++k) end.counts[k] = s.rec_c[k];
+    end.lists = s.grid * (kBlock / kStagedWave);
+    end.stride = s.region / (kBlock / kStagedWave);
     HGM_TRY(launch_staged_join(L, g, s, 0, first, seed));
     int launched = 0;
     // About 1 in 20 edges is live in the round of the last step and a tenth as
@@ -896,12 +1000,13 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
             HGM_TRY(hipStreamSynchronize(L.stream));
             continue;
         }
-        HGM_TRY(launch_staged_tail(L, g, s, launched, bits, report));
+        end.round = launched;
+        HGM_TRY(launch_end(L, g, s, end, bits));
         if (!slot.get())
             HGM_TRY(hipMemcpyAsync(copy, report, sizeof(copy), hipMemcpyDeviceToHost, L.stream));
         HGM_TRY(hipStreamSynchronize(L.stream));
         if (slot.get()) memcpy(copy, report, sizeof(copy));
-        if (copy[0]) return HGM_OK;
+        if (copy[kEndFinished]) return HGM_OK;
         plan = more;
     }
 }
@@ -953,7 +1058,8 @@ void solo_lists(SoloJob *J, const State &s) {
 // costs barriers instead of two launches.  *ran = false: not for this call.
 // With statistics or priorities redrawn every round the rounds are exact.
 int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
-               hipStream_t stream, uint32_t seed, uint32_t *bits, hgm_stats *stats, bool *ran) {
+               hipStream_t stream, uint32_t seed, uint32_t *bits, hgm_stats *stats,
+               bool may_allocate, bool *ran) {
     *ran = false;
     const int64_t bound = o.solo_max_kappa ? o.solo_max_kappa : kSoloOneKappa;
     if (g.m == 0 || g.m > kSoloOneThreads || g.kappa > bound || o.variant == HGM_VARIANT_CREW ||
@@ -976,6 +1082,10 @@ int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     J.ctl = (unsigned long long *)s.stats;
     J.rows = J.ctl + kSoloJobHeader;
     J.row_cap = (int)((sizeof(RoundStats) / 8 * (size_t)lay.ring - kSoloJobHeader) / 5);
+    std::optional<HostSlot> slot;
+    if (stats) slot.emplace(may_allocate);
+    J.host = slot ? (unsigned long long *)slot->get() : nullptr;
+    J.host_rows = kSlotRows;
     solo_lists(&J, s);
     HGM_TRY(launch_solo_one(stream, J, g.pairs != 0, lds));
     if (!stats) {
@@ -983,10 +1093,11 @@ int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
         *ran = true;
         return HGM_OK;
     }
-    std::vector<unsigned long long> head(kSoloJobHeader + 5 * (size_t)std::min(kSoloRowsFirst,
-                                                                               J.row_cap));
-    HGM_TRY(hipMemcpyAsync(head.data(), J.ctl, 8 * head.size(), hipMemcpyDeviceToHost, stream));
+    std::vector<unsigned long long> head(kSoloJobHeader + 5 * (size_t)kSlotRows);
+    if (!J.host)
+        HGM_TRY(hipMemcpyAsync(head.data(), J.ctl, 8 * head.size(), hipMemcpyDeviceToHost, stream));
     HGM_TRY(hipStreamSynchronize(stream));
+    if (J.host) memcpy(head.data(), J.host, 8 * head.size());
     const int64_t rounds = (int64_t)head[kSoloJobRounds];
     if (rounds > J.row_cap) return HGM_OK;  // more rounds than rows: the round kernels count them
     const size_t need = kSoloJobHeader + 5 * (size_t)rounds;
@@ -1049,11 +1160,11 @@ int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *w
     L.stream = (hipStream_t)stream;
     if (L.grid <= 0) return HGM_E_HIP;
     bool ran = false;
-    rc = match_solo(g, o, lay, s, L.stream, seed, matched_bits, stats, &ran);
+    rc = match_solo(g, o, lay, s, L.stream, seed, matched_bits, stats, may_allocate, &ran);
     if (rc != HGM_OK || ran) return rc;
     if (g.m > 0 && staged_call(o, stats))
         return run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate);
-    return run_rounds(g, o, lay, s, L, seed, matched_bits, stats, nullptr);
+    return run_rounds(g, o, lay, s, L, seed, matched_bits, stats, nullptr, nullptr, may_allocate);
 }
 
 }  // namespace

@@ -244,6 +244,8 @@ struct SoloJob {
     int32_t lds_bytes;   // dynamic LDS of a workgroup: done bits, then maxima
     int32_t row_cap;     // rounds whose counts fit rows (exact)
     unsigned long long *ctl, *rows;
+    unsigned long long *host;  // exact: ctl and the first rows again, in pinned host memory
+    int32_t host_rows;
     int32_t *list[2], *rec_a[2], *rec_b[2], *rec_c[2];
     uint64_t *rec_key[2];
     int32_t count;
@@ -268,6 +270,7 @@ hipError_t launch_solo_one(hipStream_t stream, SoloJob J, bool pairs, int lds);
 hipError_t launch_solo_batch(hipStream_t stream, SoloJob J, int64_t n_total, int cus, int lds);
 
 constexpr int kStagedSteps = 7;  // admission steps of staged.hip
+constexpr int kStagedWave = 64;  // threads that share a live list there
 
 struct Launch {
     int grid;            // persistent workgroup count for vertex / setup kernels
@@ -314,11 +317,32 @@ hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, i
                               int first, uint32_t seed);
 hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, int round,
                               uint32_t *bits);
-// After the join of `round`: its live edges, when few, are matched to the end
-// by one workgroup.  report (device or pinned host): {1 when none is left,
-// live edges left}.
-hipError_t launch_staged_tail(const Launch &L, const Graph &g, const State &s, int round,
-                              uint32_t *bits, int64_t *report);
+// The end of a batch of rounds (ending.hip): after the pass that formed the live
+// lists of `round`, the counters of rounds first .. round, and, when `run` and
+// few edges are left, every remaining round.  The lists are `lists` many, list w
+// at slot w * stride with counts[parity][w] edges.
+constexpr int kEndFinished = 0;  // words of the report: 1 when no live edge is left
+constexpr int kEndLive = 1;      // live edges left
+constexpr int kEndRounds = 2;    // rounds run (with edges left: whose test is to come)
+constexpr int kEndOverflow = 3;  // set when a bin overflowed in one of the rounds
+constexpr int kEndForm = 4;      // RoundStats::form, when round 0 is among them
+constexpr int kEndHeader = 8;    // then 5 words a round: live edges and pins, matched
+                                 // edges, their weight and pins
+struct EndArgs {
+    int32_t *counts[2];
+    int32_t lists;
+    int64_t stride;
+    int32_t first, round;
+    uint32_t seed;
+    int32_t reseed, max_rounds;
+    int32_t run;
+    int32_t counting;  // report the rounds' counts (rounds beyond the `rows` that fit:
+    int32_t rows;      // rec_key[round & 1], one word each: live edges, live pins, matched
+                       // edges and their pins in 16 bits each; rec_key[other]: the weight)
+    unsigned long long *report;  // device or pinned host memory, header cleared by the caller
+};
+hipError_t launch_end(const Launch &L, const Graph &g, const State &s, const EndArgs &a,
+                      uint32_t *bits);
 // One workgroup checks round `round`'s live counts and, when they are within
 // the tail's bounds, runs every remaining round of the instance (one
 // instance, offset or pair layout; seed and reseed as for the other kernels).

@@ -43,6 +43,13 @@ inline int64_t solo_auto_bound(int64_t kappa_total) {
 // edges and kSoloOneKappa pins in one workgroup (tiny: 50 -> 28 us).
 constexpr int64_t kSoloBatchKappa = (int64_t)1 << 20;
 constexpr int64_t kSoloOneKappa = (int64_t)1 << 17;
+// Rounds over all edges: the last ones run in one workgroup (ending.hip, up to
+// 2,048 edges and 8,192 pins) after as many rounds as leave about this many
+// live pins (or edges, where those run out first) at the usual shrink per
+// round.  A batch that ends a round early costs a second check (about 20 us)
+// and one a round late two near-empty launches (about 13 us).
+constexpr double kEndingPins = 5000.0;
+constexpr double kEndingEdges = 1400.0;
 // Rounds by admission: workgroups of the join and the test (at 1536: power-law
 // 444 against 377 us, hub-stress 562 against 497, RGG 453 against 429).
 constexpr int kStagedGrid = 1024;

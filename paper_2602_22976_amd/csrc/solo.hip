@@ -470,6 +470,11 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
                 row[0] = (unsigned long long)E;
                 for (int q = 0; q < 4; ++q) row[q + 1] = S.sum[q];
             }
+            if (J.host && r < J.host_rows) {
+                unsigned long long *row = J.host + kSoloJobHeader + 5 * (int64_t)r;
+                row[0] = (unsigned long long)E;
+                for (int q = 0; q < 4; ++q) row[q + 1] = S.sum[q];
+            }
             tot_m += S.sum[1];
             tot_w += S.sum[2];
             for (int q = 0; q < 4; ++q) S.sum[q] = 0;
@@ -584,6 +589,11 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
                 if ((open >> i & 1) && (S.end.flag[own[i]] & kWon)) m.mark(v[i]);
             __syncthreads();
         }
+    }
+    if (exact && tid == 0 && J.host) {
+        J.host[kSoloJobRounds] = (unsigned long long)r;
+        J.host[kSoloJobMatched] = tot_m;
+        J.host[kSoloJobWeight] = tot_w;
     }
     if (exact && tid == 0) {
         J.ctl[kSoloJobRounds] = (unsigned long long)r;

@@ -27,8 +27,6 @@
 // Each wave owns a range of edge ids and keeps its live edges in its own range
 // of the lists: compaction is a ballot, with no barrier and no atomic.  Done
 // marks are bits (n / 8 bytes stay in every XCD's L2 beside the streams).
-#include <atomic>
-
 #include "internal.h"
 #include "wave.h"
 
@@ -299,208 +297,6 @@ __global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int ro
     }
 }
 
-// The last rounds in one workgroup.  Late rounds have few live edges, and two
-// launches a round then cost far more than their work.  After the join of
-// `round`, when at most kEndEdges edges with at most kEndPins pins are left,
-// one workgroup gathers them, numbers their vertices through a hash table and
-// runs every remaining round in LDS: a round is a handful of barriers.  The
-// waves' counts are zeroed, so that rounds enqueued behind it find nothing.
-// report: {1 when no live edge is left, else 0; live edges left}.
-constexpr int kEndThreads = 1024, kEndEdges = 2048, kEndPins = 8192, kEndSlots = 12288;
-constexpr int kEndPerThread = kEndPins / kEndThreads;
-struct TailShared {
-    union {
-        unsigned long long best[kEndSlots];
-        int id[kEndSlots];  // while the vertices are numbered
-    };
-    uint64_t key[kEndEdges];
-    int start[kEndEdges];   // first pin of the edge among the gathered pins
-    int base[kEndEdges];    // offset of its pins less start
-    int vb[kEndEdges];
-    uint32_t flag[kEndEdges];  // kLost, kDead
-    uint32_t done[kEndSlots / 32];
-    int sum[kEndThreads / kWave];
-    int live;
-};
-
-__device__ __forceinline__ int tail_scan(int v, int *sum, int *total) {
-    const int wid = threadIdx.x / kWave, incl = wave_inclusive_sum(v);
-    if (lane_id() == kWave - 1) sum[wid] = incl;
-    __syncthreads();
-    int off = 0, all = 0;
-    for (int i = 0; i < kEndThreads / kWave; ++i) {
-        off += i < wid ? sum[i] : 0;
-        all += sum[i];
-    }
-    __syncthreads();
-    *total = all;
-    return off + incl - v;
-}
-
-template <bool kPairs, bool kB>
-__global__ void __launch_bounds__(kEndThreads) k_staged_tail(Graph g, State s, int round,
-                                                              uint32_t *bits, int64_t *report) {
-    extern __shared__ __align__(16) unsigned char tail_lds[];
-    TailShared &S = *reinterpret_cast<TailShared *>(tail_lds);
-    const int tid = threadIdx.x, k = round & 1;
-    const int64_t live = live_edges(s, round);
-    if (live == 0 || live > kEndEdges) {
-        if (tid == 0) {
-            report[0] = live == 0;
-            report[1] = live;
-        }
-        return;
-    }
-    // Gather: each thread takes the lists of consecutive waves.
-    const int waves = s.grid * kWaves, per = (waves + kEndThreads - 1) / kEndThreads;
-    const int64_t range = s.region / kWaves;
-    const int w0 = tid * per, w1 = min(w0 + per, waves);
-    int mine = 0, E;
-    for (int w = w0; w < w1; ++w) mine += s.rec_c[k][w];
-    int at = tail_scan(mine, S.sum, &E);
-    for (int w = w0; w < w1 && mine > 0; ++w) {
-        const int n = s.rec_c[k][w];
-        for (int i = 0; i < n; ++i, ++at) {
-            const int64_t from = w * range + i;
-            const int e = s.list[k][from];
-            S.key[at] = s.rec_key[k][from];
-            S.base[at] = kPairs ? 2 * e : s.rec_a[k][from];
-            S.start[at] = kPairs ? 2 : s.rec_b[k][from];  // the count, until the scan below
-            S.vb[at] = kB ? s.rec_vb[k][from] : 0;
-            S.flag[at] = (uint32_t)e;
-        }
-    }
-    __syncthreads();
-    constexpr int kOwn = kEndEdges / kEndThreads;  // edges per thread
-    int e[kOwn], len[kOwn], pins = 0;
-    bool alive[kOwn];
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        const int j = tid * kOwn + q;
-        alive[q] = j < E;
-        e[q] = j < E ? (int)S.flag[j] : 0;
-        len[q] = j < E ? S.start[j] : 0;
-        pins += len[q] < kEndPins ? len[q] : kEndPins + 1;
-        pins = pins < kEndPins ? pins : kEndPins + 1;
-    }
-    int total;
-    int first = tail_scan(pins, S.sum, &total);
-    if (total > kEndPins) {  // left to the grid's rounds
-        if (tid == 0) {
-            report[0] = 0;
-            report[1] = live;
-        }
-        return;
-    }
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        const int j = tid * kOwn + q;
-        if (j < E) {
-            S.start[j] = first;
-            S.base[j] -= first;
-            S.flag[j] = 0;
-        } else {
-            S.start[j] = total;
-        }
-        first += len[q];
-    }
-    for (int i = tid; i < kEndSlots; i += kEndThreads) S.id[i] = -1;
-    for (int i = tid; i < kEndSlots / 32; i += kEndThreads) S.done[i] = 0;
-    for (int w = w0; w < w1; ++w) s.rec_c[k][w] = 0;
-    __syncthreads();
-    // This thread's pins: their edge and their vertex's slot.
-    int own[kEndPerThread], v[kEndPerThread];
-#pragma unroll
-    for (int i = 0; i < kEndPerThread; ++i) {
-        const int t = i * kEndThreads + tid;
-        own[i] = -1;
-        v[i] = 0;
-        if (t < total) {
-            int j = 0;  // the last edge that starts at or before t (empty ones end where they start)
-#pragma unroll
-            for (int step = kEndEdges / 2; step > 0; step >>= 1)
-                if (S.start[j + step] <= t) j += step;
-            own[i] = j;
-            v[i] = g.e_pins[S.base[j] + t] + (kB ? S.vb[j] : 0);
-        }
-    }
-    int slot[kEndPerThread];
-#pragma unroll
-    for (int i = 0; i < kEndPerThread; ++i) {
-        slot[i] = 0;
-        if (own[i] >= 0) {  // at most kEndPins of kEndSlots are taken: a free one is found
-            uint32_t h = __umulhi((uint32_t)v[i] * 0x9E3779B1u, (uint32_t)kEndSlots);
-            for (;;) {
-                const int id = atomicCAS(&S.id[h], -1, v[i]);
-                if (id == -1 || id == v[i]) break;
-                h = h + 1 < kEndSlots ? h + 1 : 0;
-            }
-            slot[i] = (int)h;
-        }
-    }
-    __syncthreads();
-    for (int i = tid; i < kEndSlots; i += kEndThreads) S.best[i] = 0;
-    __syncthreads();
-    constexpr uint32_t kLost = 1, kDead = 2, kWon = 4;
-    uint32_t open = 0;  // this thread's pins whose edge is alive
-#pragma unroll
-    for (int i = 0; i < kEndPerThread; ++i) open |= own[i] >= 0 ? 1u << i : 0;
-    for (;;) {
-#pragma unroll
-        for (int i = 0; i < kEndPerThread; ++i)
-            if (open >> i & 1) atomicMax(&S.best[slot[i]], (unsigned long long)S.key[own[i]]);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kEndPerThread; ++i)
-            if ((open >> i & 1) && S.best[slot[i]] != S.key[own[i]]) atomicOr(&S.flag[own[i]], kLost);
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kOwn; ++q) {
-            const int j = tid * kOwn + q;
-            if (alive[q]) {
-                if (S.flag[j] & kLost) {
-                    S.flag[j] = 0;
-                } else {
-                    const int bit = kB ? e[q] + g.bitoff[e[q]] : e[q];
-                    atomicOr(&bits[bit >> 5], 1u << (bit & 31));
-                    S.flag[j] = kWon;
-                    alive[q] = false;
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kEndPerThread; ++i)
-            if (open >> i & 1) {
-                S.best[slot[i]] = 0;
-                if (S.flag[own[i]] & kWon) {
-                    atomicOr(&S.done[slot[i] >> 5], 1u << (slot[i] & 31));
-                    open &= ~(1u << i);
-                }
-            }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kEndPerThread; ++i)
-            if ((open >> i & 1) && (S.done[slot[i] >> 5] >> (slot[i] & 31) & 1))
-                atomicOr(&S.flag[own[i]], kDead);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kEndPerThread; ++i)
-            if ((open >> i & 1) && (S.flag[own[i]] & kDead)) open &= ~(1u << i);
-        int left = 0;
-#pragma unroll
-        for (int q = 0; q < kOwn; ++q) {
-            alive[q] = alive[q] && !(S.flag[tid * kOwn + q] & kDead);
-            left |= alive[q];
-        }
-        if (!__syncthreads_or(left)) break;
-    }
-    if (tid == 0) {
-        report[0] = 1;
-        report[1] = 0;
-    }
-}
-
 }  // namespace
 
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
@@ -544,29 +340,6 @@ hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, i
         hipLaunchKernelGGL((k_staged_test<false, false>), grid, block, 0, L.stream, g, s, round,
                            bits);
     return hipGetLastError();
-}
-
-template <bool kPairs, bool kB>
-static hipError_t launch_tail_as(const Launch &L, const Graph &g, const State &s, int round,
-                                 uint32_t *bits, int64_t *report) {
-    static std::atomic<bool> allowed{false};
-    if (!allowed.load(std::memory_order_relaxed)) {
-        const hipError_t rc =
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_staged_tail<kPairs, kB>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(TailShared));
-        if (rc != hipSuccess) return rc;
-        allowed.store(true, std::memory_order_relaxed);
-    }
-    hipLaunchKernelGGL((k_staged_tail<kPairs, kB>), dim3(1), dim3(kEndThreads),
-                       sizeof(TailShared), L.stream, g, s, round, bits, report);
-    return hipGetLastError();
-}
-
-hipError_t launch_staged_tail(const Launch &L, const Graph &g, const State &s, int round,
-                              uint32_t *bits, int64_t *report) {
-    if (g.pairs) return launch_tail_as<true, false>(L, g, s, round, bits, report);
-    if (g.vbase) return launch_tail_as<false, true>(L, g, s, round, bits, report);
-    return launch_tail_as<false, false>(L, g, s, round, bits, report);
 }
 
 }  // namespace hgm
