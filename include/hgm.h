@@ -349,9 +349,11 @@ int hgm_tuned_batch_opts(const char *cache, const hgm_batch *b, hgm_opts *opts);
  *
  * The caller gives the server a device arena (its HBM budget).  Requests
  * (host arrays) are queued by hgm_server_submit.  Worker threads, each with
- * its own HIP stream, take turns forming a wave from every queued request
- * that fits the arena's free memory (arrival order, at most max_batch),
- * upload it into one arena block, match it with hgm_match_batch and copy each
+ * its own HIP stream, take turns forming a wave from the queued requests
+ * that fit the arena's free memory (arrival order, at most max_batch, a share
+ * of the queue while other workers are idle), upload it through pinned memory
+ * (64 MB at most, allocated with the server) into one arena block, match it
+ * with hgm_match_batch and copy each
  * request's bitmap back; requests arriving meanwhile go into the next wave,
  * which another worker runs concurrently.  A wave's memory returns to the
  * arena when it completes, admitting waiting requests.  A request's bitmap is

@@ -4,8 +4,9 @@
 // requests as they arrive.
 //
 // Workers (threads, each with its own HIP stream) take turns forming a wave:
-// every queued request that fits the free arena memory, up to max_batch, in
-// arrival order.  A wave is uploaded into one arena block and matched with
+// queued requests that fit the free arena memory, up to max_batch and up to the
+// worker's share among those that are idle, in arrival order.  A wave is
+// uploaded through pinned memory into one arena block and matched with
 // hgm_match_batch on the worker's stream; while it runs, the next worker
 // forms the next wave from requests that arrived meanwhile, so waves overlap
 // on the device.  Memory returns to the arena when a wave's results are
@@ -83,6 +84,107 @@ class Arena {
     std::map<size_t, size_t> free_;  // offset -> length
 };
 
+// A worker's pinned host memory, through which its waves go to the device and
+// their bitmaps come back: kChunks chunks in turn, each copied with one call
+// and filled again when that copy is done.  A wave of 30 requests has 90
+// arrays; copied one by one from pageable memory they cost 20 to 50 us each,
+// in line (3.4 ms for 20 MB), whereas filling a chunk overlaps the copies of
+// the chunks before it.  Without pinned memory (allocation failed) base is
+// NULL and the arrays are copied one by one.
+class Staging {
+  public:
+    static constexpr int kChunks = 4;
+    char *base = nullptr;
+    size_t chunk = 0;
+
+    // memory: kChunks chunks, owned by the caller.
+    bool create(char *memory, size_t chunk_bytes) {
+        for (int i = 0; i < kChunks; ++i) {
+            if (hipEventCreateWithFlags(&ev_[i], hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                destroy();
+                return false;
+            }
+            made_ = i + 1;
+        }
+        base = memory;
+        chunk = chunk_bytes;
+        return true;
+    }
+    void destroy() {
+        for (int i = 0; i < made_; ++i) (void)hipEventDestroy(ev_[i]);
+        made_ = 0;
+        base = nullptr;
+    }
+    // The next chunk, once its last copy is done.
+    hipError_t acquire(char **at) {
+        *at = base + next_ * chunk;
+        if (!busy_[next_]) return hipSuccess;
+        busy_[next_] = false;
+        return hipEventSynchronize(ev_[next_]);
+    }
+    // Copies the chunk's first bytes to dst.
+    hipError_t send(char *dst, size_t bytes, hipStream_t stream) {
+        hipError_t rc = hipMemcpyAsync(dst, base + next_ * chunk, bytes, hipMemcpyHostToDevice,
+                                       stream);
+        if (rc == hipSuccess) rc = hipEventRecord(ev_[next_], stream);
+        busy_[next_] = true;
+        next_ = (next_ + 1) % kChunks;
+        return rc;
+    }
+
+  private:
+    hipEvent_t ev_[kChunks];
+    bool busy_[kChunks] = {false};
+    int made_ = 0, next_ = 0;
+};
+
+// Pinned host memory of a server at most, shared out over its workers' chunks.
+// A burst of 64 requests (57 MB, eight workers): 3.1 ms with chunks of 256 KB
+// (a copy, its event and the wait cost about 20 us), 2.2 ms with 1 MB, 2.1 ms
+// with 2 MB; 3.9 to 4.1 ms with one copy per array and whole queues as waves.
+constexpr size_t kStagingBytes = (size_t)64 << 20;
+constexpr size_t kStagingChunk = (size_t)2 << 20;
+
+// A range of a wave's arena block and the host memory it holds a copy of.
+struct Piece {
+    size_t off;
+    const void *src;
+    size_t bytes;
+};
+
+// Uploads the pieces (by ascending offset; the padding between two that go
+// in one copy is copied, too).
+hipError_t upload(Staging &T, char *blk, const std::vector<Piece> &pieces, hipStream_t stream) {
+    hipError_t rc = hipSuccess;
+    if (!T.base) {
+        for (const Piece &p : pieces)
+            if (rc == hipSuccess && p.bytes)
+                rc = hipMemcpyAsync(blk + p.off, p.src, p.bytes, hipMemcpyHostToDevice, stream);
+        return rc;
+    }
+    char *at = nullptr;  // the chunk being filled: offsets [from, from + fill)
+    size_t from = 0, fill = 0;
+    for (const Piece &p : pieces) {
+        for (size_t done = 0; done < p.bytes;) {
+            if (at && p.off + done - from >= T.chunk) {
+                if ((rc = T.send(blk + from, fill, stream)) != hipSuccess) return rc;
+                at = nullptr;
+            }
+            if (!at) {
+                if ((rc = T.acquire(&at)) != hipSuccess) return rc;
+                from = p.off + done;
+            }
+            const size_t pos = p.off + done - from;
+            const size_t n = std::min(p.bytes - done, T.chunk - pos);
+            memcpy(at + pos, (const char *)p.src + done, n);
+            fill = pos + n;
+            done += n;
+        }
+    }
+    return at ? T.send(blk + from, fill, stream) : hipSuccess;
+}
+
 struct Pending {
     hgm_request req;
     double t_submit;
@@ -110,6 +212,9 @@ struct hgm_server {
     bool forming = false;  // one worker at a time forms a wave, in arrival order
     std::vector<std::thread> workers;
     std::vector<hipStream_t> streams;  // one per worker
+    std::vector<Staging> staging;      // one per worker
+    char *pinned = nullptr;            // their memory
+    int idle = 0;                      // workers that wait for a request
     int64_t submitted = 0, completed = 0;
     int64_t stalls = 0;  // waits for arena memory with requests queued
     double stall_s = 0;
@@ -223,7 +328,7 @@ void finish(hgm_server *S, const std::vector<Pending> &wave, int status, double 
     S->cv_results.notify_all();
 }
 
-int run_wave(hgm_server *S, hipStream_t stream, const std::vector<Pending> &wave, size_t off,
+int run_wave(hgm_server *S, hipStream_t stream, Staging &T, const std::vector<Pending> &wave, size_t off,
              const WaveLayout &L, int64_t n, int64_t m, int64_t kappa, int64_t words) {
     char *blk = S->arena_base + off;
     const int count = (int)wave.size();
@@ -248,34 +353,37 @@ int run_wave(hgm_server *S, hipStream_t stream, const std::vector<Pending> &wave
             return HGM_E_HIP;                            \
         }                                                \
     } while (0)
-    SRV_TRY(hipMemcpyAsync(blk + L.v_base, vb.data(), 8 * (count + 1), hipMemcpyHostToDevice, stream));
-    SRV_TRY(hipMemcpyAsync(blk + L.e_base, eb.data(), 8 * (count + 1), hipMemcpyHostToDevice, stream));
-    SRV_TRY(hipMemcpyAsync(blk + L.pin_base, pb.data(), 8 * (count + 1), hipMemcpyHostToDevice, stream));
-    SRV_TRY(hipMemcpyAsync(blk + L.word_base, wb.data(), 8 * (count + 1), hipMemcpyHostToDevice, stream));
-    SRV_TRY(hipMemcpyAsync(blk + L.seeds, seeds.data(), 4 * count, hipMemcpyHostToDevice, stream));
+    static const int32_t zero = 0;
+    std::vector<Piece> pieces = {{L.v_base, vb.data(), 8 * (size_t)(count + 1)},
+                                 {L.e_base, eb.data(), 8 * (size_t)(count + 1)},
+                                 {L.pin_base, pb.data(), 8 * (size_t)(count + 1)},
+                                 {L.word_base, wb.data(), 8 * (size_t)(count + 1)},
+                                 {L.seeds, seeds.data(), 4 * (size_t)count}};
+    pieces.reserve(5 + 5 * (size_t)count);
     for (int i = 0; i < count; ++i) {
         const hgm_request &q = wave[i].req;
-        if (q.m > 0) {
-            SRV_TRY(hipMemcpyAsync(blk + L.e_off + 4 * (eb[i] + i), q.e_off, 4 * ((size_t)q.m + 1),
-                                   hipMemcpyHostToDevice, stream));
-            SRV_TRY(hipMemcpyAsync(blk + L.w + 4 * eb[i], q.w, 4 * (size_t)q.m,
-                                   hipMemcpyHostToDevice, stream));
-        } else {
-            static const int32_t zero = 0;
-            SRV_TRY(hipMemcpyAsync(blk + L.e_off + 4 * (eb[i] + i), &zero, 4,
-                                   hipMemcpyHostToDevice, stream));
-        }
-        if (q.kappa > 0) {
-            SRV_TRY(hipMemcpyAsync(blk + L.e_pins + 4 * pb[i], q.e_pins, 4 * (size_t)q.kappa,
-                                   hipMemcpyHostToDevice, stream));
-            if (vside)
-                SRV_TRY(hipMemcpyAsync(blk + L.v_edges + 4 * pb[i], q.v_edges,
-                                       4 * (size_t)q.kappa, hipMemcpyHostToDevice, stream));
-        }
-        if (vside)
-            SRV_TRY(hipMemcpyAsync(blk + L.v_off + 4 * (vb[i] + i), q.v_off, 4 * ((size_t)q.n + 1),
-                                   hipMemcpyHostToDevice, stream));
+        if (q.m > 0)
+            pieces.push_back({L.e_off + 4 * (eb[i] + i), q.e_off, 4 * ((size_t)q.m + 1)});
+        else
+            pieces.push_back({L.e_off + 4 * (eb[i] + i), &zero, 4});
     }
+    for (int i = 0; i < count; ++i) {
+        const hgm_request &q = wave[i].req;
+        pieces.push_back({L.e_pins + 4 * pb[i], q.e_pins, 4 * (size_t)q.kappa});
+    }
+    for (int i = 0; vside && i < count; ++i) {
+        const hgm_request &q = wave[i].req;
+        pieces.push_back({L.v_off + 4 * (vb[i] + i), q.v_off, 4 * ((size_t)q.n + 1)});
+    }
+    for (int i = 0; vside && i < count; ++i) {
+        const hgm_request &q = wave[i].req;
+        pieces.push_back({L.v_edges + 4 * pb[i], q.v_edges, 4 * (size_t)q.kappa});
+    }
+    for (int i = 0; i < count; ++i) {
+        const hgm_request &q = wave[i].req;
+        pieces.push_back({L.w + 4 * eb[i], q.w, 4 * (size_t)q.m});
+    }
+    SRV_TRY(upload(T, blk, pieces, stream));
     hgm_batch d;
     memset(&d, 0, sizeof(d));
     d.count = count;
@@ -299,19 +407,51 @@ int run_wave(hgm_server *S, hipStream_t stream, const std::vector<Pending> &wave
         (void)hipStreamSynchronize(stream);
         return rc;
     }
-    for (int i = 0; i < count; ++i) {
-        const hgm_request &q = wave[i].req;
-        const size_t nw = words_of(q.m);
-        if (nw && q.bits_out)
-            SRV_TRY(hipMemcpyAsync(q.bits_out, blk + L.bits + 4 * wb[i], 4 * nw,
-                                   hipMemcpyDeviceToHost, stream));
+    // The bitmaps, as many at a time as the pinned memory holds.
+    if (!T.base) {
+        for (int i = 0; i < count; ++i) {
+            const hgm_request &q = wave[i].req;
+            const size_t nw = words_of(q.m);
+            if (nw && q.bits_out)
+                SRV_TRY(hipMemcpyAsync(q.bits_out, blk + L.bits + 4 * wb[i], 4 * nw,
+                                       hipMemcpyDeviceToHost, stream));
+        }
+        SRV_TRY(hipStreamSynchronize(stream));
+        return HGM_OK;
     }
     SRV_TRY(hipStreamSynchronize(stream));
+    const size_t all = 4 * (size_t)words, cap = T.chunk * Staging::kChunks;
+    int i = 0;  // the first request with words at or beyond lo
+    for (size_t lo = 0; lo < all; lo += cap) {
+        const size_t hi = std::min(all, lo + cap);
+        SRV_TRY(hipMemcpyAsync(T.base, blk + L.bits + lo, hi - lo, hipMemcpyDeviceToHost, stream));
+        SRV_TRY(hipStreamSynchronize(stream));
+        for (; i < count; ++i) {
+            const size_t b0 = 4 * (size_t)wb[i], b1 = 4 * (size_t)wb[i + 1];
+            const size_t from = std::max(b0, lo), to = std::min(b1, hi);
+            if (to > from && wave[i].req.bits_out)
+                memcpy((char *)wave[i].req.bits_out + (from - b0), T.base + (from - lo), to - from);
+            if (b1 > hi) break;  // goes on in the next part
+        }
+    }
 #undef SRV_TRY
     return HGM_OK;
 }
 
-void worker_main(hgm_server *S, hipStream_t stream) {
+// Bytes of a request's arrays.
+size_t request_bytes(const hgm_request &q, bool vside) {
+    return 4 * ((vside ? 2 : 1) * (size_t)q.kappa + 2 * (size_t)q.m + (vside ? (size_t)q.n : 0));
+}
+
+// A wave leaves the rest of the queue to the other idle workers once it holds
+// its share of the queued bytes, and at least this many: below it a wave's
+// launches (about 0.4 ms) cost more than its upload (about 8 GB/s a worker).
+// The burst above measures the same with 512 KB; one worker that takes all
+// that is queued uploads 35 of its requests while seven wait.
+constexpr size_t kWaveMinBytes = (size_t)2 << 20;
+
+void worker_main(hgm_server *S, hipStream_t stream, int self) {
+    Staging &T = S->staging[self];
     (void)hipSetDevice(S->device);  // checked by hgm_server_create on this device
     const int max_batch = S->opts.max_batch;
     for (;;) {
@@ -323,7 +463,9 @@ void worker_main(hgm_server *S, hipStream_t stream) {
         {
             std::unique_lock<std::mutex> lk(S->mu);
             // Wait for our turn to form a wave and for a request to serve.
+            S->idle += 1;
             S->cv_work.wait(lk, [&] { return S->stopping || (!S->forming && !S->queue.empty()); });
+            S->idle -= 1;
             if (S->queue.empty() && S->stopping) break;
             S->forming = true;
             for (;;) {
@@ -331,28 +473,34 @@ void worker_main(hgm_server *S, hipStream_t stream) {
                 wave.clear();
                 n = m = kappa = words = 0;
                 bool fits_alone = true;
-                size_t best = 0;
-                for (size_t i = 0; i < S->queue.size() && (int)wave.size() < max_batch; ++i) {
+                const bool vside = !S->opts.edge_side_only;
+                size_t queued = 0, taken = 0;
+                for (const Pending &p : S->queue) queued += request_bytes(p.req, vside);
+                const size_t share =
+                    std::max(kWaveMinBytes, queued / (size_t)(S->idle + 1));
+                for (size_t i = 0; i < S->queue.size() && (int)wave.size() < max_batch &&
+                                   taken < share;
+                     ++i) {
                     const hgm_request &q = S->queue[i].req;
                     if (n + q.n > kWaveLimit || m + q.m > kWaveLimit ||
                         kappa + q.kappa > kWaveLimit ||
                         32 * (words + (int64_t)words_of(q.m)) > kWaveLimit)
                         break;  // submit checked that each request fits alone
-                    const WaveLayout T = wave_layout((int)wave.size() + 1, n + q.n, m + q.m,
+                    const WaveLayout W = wave_layout((int)wave.size() + 1, n + q.n, m + q.m,
                                                      kappa + q.kappa,
                                                      words + (int64_t)words_of(q.m), S->opts);
                     size_t probe;
-                    if (!S->arena.alloc(T.total, &probe)) {
-                        if (wave.empty() && T.total > S->arena.size()) fits_alone = false;
+                    if (!S->arena.alloc(W.total, &probe)) {
+                        if (wave.empty() && W.total > S->arena.size()) fits_alone = false;
                         break;
                     }
-                    S->arena.release(probe, T.total);
+                    S->arena.release(probe, W.total);
                     wave.push_back(S->queue[i]);
                     n += q.n;
                     m += q.m;
                     kappa += q.kappa;
                     words += (int64_t)words_of(q.m);
-                    best = T.total;
+                    taken += request_bytes(q, vside);
                 }
                 if (!fits_alone) {  // larger than the whole budget: fail it
                     Pending p = S->queue.front();
@@ -365,7 +513,6 @@ void worker_main(hgm_server *S, hipStream_t stream) {
                 }
                 if (!wave.empty()) {
                     L = wave_layout((int)wave.size(), n, m, kappa, words, S->opts);
-                    (void)best;
                     if (S->arena.alloc(L.total, &off)) break;
                 }
                 // Nothing fits now: wait for memory to come back.
@@ -408,7 +555,7 @@ void worker_main(hgm_server *S, hipStream_t stream) {
             }
             const WaveLayout G =
                 bad.empty() ? L : wave_layout((int)good.size(), n, m, kappa, words, S->opts);
-            rc = G.total <= L.total ? run_wave(S, stream, good, off, G, n, m, kappa, words)
+            rc = G.total <= L.total ? run_wave(S, stream, T, good, off, G, n, m, kappa, words)
                                     : HGM_E_SIZE;
         }
         {
@@ -456,7 +603,19 @@ int hgm_server_create(void *arena, size_t arena_bytes, const hgm_server_opts *op
     S->opts = o;
     S->device = dev;
     S->streams = streams;
-    for (int i = 0; i < o.workers; ++i) S->workers.emplace_back(worker_main, S, streams[i]);
+    S->staging.resize(o.workers);
+    const size_t chunk =
+        std::min(kStagingChunk, kStagingBytes / Staging::kChunks / (size_t)o.workers);
+    void *pinned = nullptr;
+    if (hipHostMalloc(&pinned, chunk * Staging::kChunks * o.workers, hipHostMallocPortable) ==
+        hipSuccess) {
+        S->pinned = (char *)pinned;
+        for (int i = 0; i < o.workers; ++i)
+            S->staging[i].create(S->pinned + i * chunk * Staging::kChunks, chunk);
+    } else {
+        (void)hipGetLastError();
+    }
+    for (int i = 0; i < o.workers; ++i) S->workers.emplace_back(worker_main, S, streams[i], i);
     *out = S;
     return HGM_OK;
 }
@@ -521,6 +680,8 @@ int hgm_server_destroy(hgm_server *S) {
     S->cv_work.notify_all();
     for (auto &t : S->workers) t.join();
     for (hipStream_t st : S->streams) (void)hipStreamDestroy(st);
+    for (Staging &T : S->staging) T.destroy();
+    if (S->pinned) (void)hipHostFree(S->pinned);
     delete S;
     return HGM_OK;
 }
