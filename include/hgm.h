@@ -352,7 +352,7 @@ int hgm_tuned_batch_opts(const char *cache, const hgm_batch *b, hgm_opts *opts);
  * its own HIP stream, take turns forming a wave from the queued requests
  * that fit the arena's free memory (arrival order, at most max_batch, a share
  * of the queue while other workers are idle), upload it through pinned memory
- * (64 MB at most, allocated with the server) into one arena block, match it
+ * (32 MB at most, allocated with the server) into one arena block, match it
  * with hgm_match_batch and copy each
  * request's bitmap back; requests arriving meanwhile go into the next wave,
  * which another worker runs concurrently.  A wave's memory returns to the

@@ -93,7 +93,7 @@ class Arena {
 // NULL and the arrays are copied one by one.
 class Staging {
   public:
-    static constexpr int kChunks = 4;
+    static constexpr int kChunks = 2;
     char *base = nullptr;
     size_t chunk = 0;
 
@@ -140,10 +140,12 @@ class Staging {
 };
 
 // Pinned host memory of a server at most, shared out over its workers' chunks.
-// A burst of 64 requests (57 MB, eight workers): 3.1 ms with chunks of 256 KB
-// (a copy, its event and the wait cost about 20 us), 2.2 ms with 1 MB, 2.1 ms
-// with 2 MB; 3.9 to 4.1 ms with one copy per array and whole queues as waves.
-constexpr size_t kStagingBytes = (size_t)64 << 20;
+// A burst of 64 requests (57 MB, eight workers) takes 2.05 ms with two chunks
+// of 2 MB each, 2.2 ms with two or four of 1 MB and 3.1 ms with 256 KB (a
+// copy, its event and the wait cost about 20 us); 3.9 to 4.1 ms with one copy
+// per array and whole queues as waves.  Four of 2 MB are no faster, and a new
+// server's first burst then waits 2 ms more for the first touch of its pages.
+constexpr size_t kStagingBytes = (size_t)32 << 20;
 constexpr size_t kStagingChunk = (size_t)2 << 20;
 
 // A range of a wave's arena block and the host memory it holds a copy of.
@@ -615,6 +617,13 @@ int hgm_server_create(void *arena, size_t arena_bytes, const hgm_server_opts *op
     } else {
         (void)hipGetLastError();
     }
+    // The first use of a stream here, once, instead of in the first waves.
+    for (int i = 0; i < o.workers; ++i) {
+        char *at;
+        Staging &T = S->staging[i];
+        if (T.base && T.acquire(&at) == hipSuccess) (void)T.send(S->arena_base, 1, streams[i]);
+    }
+    for (int i = 0; i < o.workers; ++i) (void)hipStreamSynchronize(streams[i]);
     for (int i = 0; i < o.workers; ++i) S->workers.emplace_back(worker_main, S, streams[i], i);
     *out = S;
     return HGM_OK;

@@ -60,7 +60,7 @@ def test_chunk_edges(hgm, workers, edge_side_only):
 
 
 def test_bitmap_beyond_the_chunks(hgm):
-    """64 workers have 1 MB of chunks each: 8.4 M bits."""
+    """64 workers have 512 KB of chunks each: 4.2 M bits, here twice as many."""
     m = 8_800_003
     off = np.arange(m + 1, dtype=np.int32)
     pins = (np.arange(m, dtype=np.int64) * 7 % 3_000_000).astype(np.int32)
