@@ -1043,17 +1043,6 @@ void *scratch_address() {
     return p;
 }
 
-// The lists of a solo job, in the call's workspace.
-void solo_lists(SoloJob *J, const State &s) {
-    for (int k = 0; k < 2; ++k) {
-        J->list[k] = s.list[k];
-        J->rec_a[k] = s.rec_a[k];
-        J->rec_b[k] = s.rec_b[k];
-        J->rec_c[k] = s.rec_c[k];
-        J->rec_key[k] = s.rec_key[k];
-    }
-}
-
 // One instance in one workgroup (solo.hip): small instances, where a round
 // costs barriers instead of two launches.  *ran = false: not for this call.
 // With statistics or priorities redrawn every round the rounds are exact.
@@ -1086,7 +1075,6 @@ int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     if (stats) slot.emplace(may_allocate);
     J.host = slot ? (unsigned long long *)slot->get() : nullptr;
     J.host_rows = kSlotRows;
-    solo_lists(&J, s);
     HGM_TRY(launch_solo_one(stream, J, g.pairs != 0, lds));
     if (!stats) {
         HGM_TRY(hipStreamSynchronize(stream));
@@ -1320,7 +1308,11 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         J.max_verts = sa.max_verts;
         J.ctl = s.solo;
         J.order = (int32_t *)(s.solo + kSoloJobHeader);
-        solo_lists(&J, s);
+        // The records take the place of the rounds' (48 bytes an edge of a
+        // batch, one array behind the other) and of both lists (8 bytes), which
+        // are written later.
+        J.edges = reinterpret_cast<uint4 *>(s.rec_a[0]);
+        J.picked = reinterpret_cast<uint2 *>(s.list[0]);
         J.choose = o.solo_max_kappa == 0 ? 1 : 0;
         HostSlot slot(true);
         int64_t listed[2] = {0, 0};  // in the solo part, left to the round kernels

@@ -246,8 +246,8 @@ struct SoloJob {
     unsigned long long *ctl, *rows;
     unsigned long long *host;  // exact: ctl and the first rows again, in pinned host memory
     int32_t host_rows;
-    int32_t *list[2], *rec_a[2], *rec_b[2], *rec_c[2];
-    uint64_t *rec_key[2];
+    uint4 *edges;        // batches: two for each edge of the batch
+    uint2 *picked;       // and one
     int32_t count;
     const int64_t *v_base, *e_base, *pin_base, *word_base;
     const uint32_t *seeds;

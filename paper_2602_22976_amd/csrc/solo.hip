@@ -37,6 +37,12 @@ constexpr int kSteps = 16;  // parts of the order: fifteen thresholds, then the 
 // about a hundredth of the edges.
 __device__ constexpr int kRank[kSteps - 1] = {2,  4,  6,  8,  11, 15,  20, 27,
                                               36, 48, 63, 83, 110, 145, 190};
+// The parts up to this one, a tenth of the edges, are admitted before the others
+// are looked at: by then seven of eight of those have a pin that is done.  (The
+// batch: 2.44 ms; 2.48 with one part less, 2.44 and 2.48 with one and two more.
+// Parts growing by a half 2.66, by a sixth 2.72: more edges share slots at a
+// time, or more rounds.)
+constexpr int kSplit = 6;
 constexpr int kAdvance = 3;  // parts admitted per round where every vertex has its slot
 
 constexpr int kU = 2;          // edges per lane and step: their loads overlap
@@ -188,6 +194,60 @@ __device__ __forceinline__ void lane_act(const int32_t *e_pins, const int (&base
     });
 }
 
+// A listed edge: its id, pin offset and count, its weight, its first pins.
+constexpr int kHead = 4;
+struct EdgeHead {
+    uint4 edge;
+    int4 pin;
+};
+
+__device__ __forceinline__ void load_head(const int32_t *e_pins, int len, EdgeHead &h) {
+    const int b = (int)h.edge.y;
+    h.pin.x = len > 0 ? e_pins[b] : 0;
+    h.pin.y = len > 1 ? e_pins[b + 1] : 0;
+    h.pin.z = len > 2 ? e_pins[b + 2] : 0;
+    h.pin.w = len > 3 ? e_pins[b + 3] : 0;
+}
+
+// The same passes for listed edges: their first pins are at hand.
+template <int kU, class Look, class Check>
+__device__ __forceinline__ uint32_t head_pins(const int32_t *e_pins, const EdgeHead (&h)[kU],
+                                              const uint64_t (&key)[kU], uint32_t on, bool every,
+                                              Look look, Check check) {
+    uint32_t hit = 0;
+    decltype(look(0)) x[kU][kHead];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        x[u][0] = look(h[u].pin.x);
+        x[u][1] = look(h[u].pin.y);
+        x[u][2] = look(h[u].pin.z);
+        x[u][3] = look(h[u].pin.w);
+    }
+    int base[kU], len[kU], most = 0;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        const int n = (on >> u & 1) ? (int)h[u].edge.z : 0;
+        if (n > 0 && check(h[u].pin.x, key[u], x[u][0])) hit |= 1u << u;
+        if (n > 1 && check(h[u].pin.y, key[u], x[u][1])) hit |= 1u << u;
+        if (n > 2 && check(h[u].pin.z, key[u], x[u][2])) hit |= 1u << u;
+        if (n > 3 && check(h[u].pin.w, key[u], x[u][3])) hit |= 1u << u;
+        base[u] = (int)h[u].edge.y + kHead;
+        len[u] = n > kHead && (every || !(hit >> u & 1)) ? n - kHead : 0;
+        most = len[u] > most ? len[u] : most;
+    }
+    if (__any(most > 0)) hit |= lane_pins<kU>(e_pins, base, len, key, every, look, check);
+    return hit;
+}
+
+template <int kU, class Act>
+__device__ __forceinline__ void head_act(const int32_t *e_pins, const EdgeHead (&h)[kU],
+                                         const uint64_t (&key)[kU], uint32_t on, Act act) {
+    head_pins<kU>(e_pins, h, key, on, true, NoRead(), [&](int v, uint64_t k, int) {
+        act(v, k);
+        return false;
+    });
+}
+
 // Exclusive sum over the workgroup.
 template <int T>
 __device__ __forceinline__ int solo_scan(int v, int *tmp, int *total) {
@@ -205,21 +265,30 @@ __device__ __forceinline__ int solo_scan(int v, int *tmp, int *total) {
 }
 
 // The list rounds of an instance of more edges than threads.  Each wave owns a
-// range of edge ids, `per` long, and keeps its live edges in its own range of
-// the lists (compaction by ballot).  First it sorts its ids by part of the
-// order (the number of thresholds above the key), so that a round reads the
-// ids it admits one after the other.  Ends after a round's test, when every
-// part is admitted and at most T edges are listed: returns their number, with
-// *kept those of this wave.
-template <int T, bool kPairs>
+// range of edge ids, `per` long, and writes records of its edges to its range
+// of J.edges: in a first phase of the edges of the first parts, found by their
+// weights; when those are admitted, of the others those that are not dead,
+// found in one pass over the pins in order.  A phase's records are listed by
+// part of the order (the number of thresholds above the key); a round admits a
+// part or more, and the live edges stay in the same list, compacted by ballot
+// over entries already read.  Ends after a round's test, when every part is
+// admitted and at most T edges are listed: returns their number, with *kept
+// those of this wave.
+//
+// Bound by memory.  A part's edges lie far apart: gathered by id as they are
+// admitted, each costs a line for its offsets, its weight and its pins.  The
+// batch of 4,096 instances with 4.6e8 pins: 3.75 ms so, 1.15e8 requests that
+// leave L2; 2.91 ms with a record of every edge sorted first; 2.53 ms in two
+// phases; 2.44 ms with places sorted instead of records, by halving.  Half of
+// it is now the pass over the pins (3.9 TB/s), the rest the rounds, 20 to 30 us
+// each for the largest instances, a chain of memory accesses.
+template <int T>
 __device__ __forceinline__ int solo_lists(const Inst &I, const SoloJob &J, SoloShared<T> &S,
-                                          SoloSide<kPairs> &m, int per, int *kept_out,
-                                          int *parity) {
+                                          SoloSide<false> &m, int per, int *kept_out) {
     constexpr int kLast = kSteps - 1, kW = T / kWave;
     static_assert(kW * kWave == T && T % kSamples == 0, "whole waves, whole sample groups");
     const int tid = threadIdx.x, wid = tid / kWave, lane = lane_id();
     int *const part_end = S.part[wid];
-    int32_t *ids = J.rec_c[0] + I.at;
     const int lo = wid * per < I.ne ? wid * per : I.ne, end = lo + per < I.ne ? lo + per : I.ne;
     // From the first step that admits at least one edge per thread: a round of
     // fewer costs the same.
@@ -249,162 +318,210 @@ __device__ __forceinline__ int solo_lists(const Inst &I, const SoloJob &J, SoloS
         S.th[tid] = 0;  // no edge is below a threshold
     }
     __syncthreads();
-    // Sort the wave's ids by part.
     auto part_of = [&](int e, uint32_t w) -> int {
-        int part = 0;
-        bool tie = false;  // the hash is needed only where a weight equals a threshold's
+        const uint64_t k = m.key_of(w, e);
+        int part = 0;  // thresholds above the key: they fall
+        static_assert(kSteps == 16, "four halvings");
 #pragma unroll
-        for (int q = 0; q < kLast; ++q) {
-            const uint32_t tw = (uint32_t)(S.th[q] >> 32);
-            part += w < tw ? 1 : 0;
-            tie |= w == tw;
-        }
-        if (tie) {
-            const uint64_t k = m.key_of(w, e);
-            part = 0;
-#pragma unroll
-            for (int q = 0; q < kLast; ++q) part += k < S.th[q] ? 1 : 0;
-        }
+        for (int q = 8; q > 0; q >>= 1) part += k < S.th[part + q - 1] ? q : 0;
         return part;
     };
-    if (lane < kSteps) part_end[lane] = 0;
-    wave_fence();
-    constexpr int kSortU = 4;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int c0 = lo; c0 < end; c0 += kSortU * kWave) {
-            uint32_t w[kSortU];
-#pragma unroll
-            for (int u = 0; u < kSortU; ++u) {
-                const int e = c0 + u * kWave + lane;
-                w[u] = e < end ? I.w[e] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < kSortU; ++u) {
-                const int e = c0 + u * kWave + lane;
-                if (e < end) {
-                    const int at = atomicAdd(&part_end[part_of(e, w[u])], 1);
-                    if (pass) ids[lo + at] = e;
-                }
-            }
-        }
-        wave_fence();
-        if (pass == 0) {  // counts to starts; the second pass moves them to the ends
-            const int c = lane < kSteps ? part_end[lane] : 0;
-            const int begin = wave_inclusive_sum(c) - c;
-            wave_fence();
-            if (lane < kSteps) part_end[lane] = begin;
-            wave_fence();
-        }
-    }
+    const int split = step > kSplit ? step : kSplit;  // kLast: one phase
+    const uint64_t bound = split < kLast ? S.th[split] : 0;  // of the first phase's keys
+    EdgeHead *const edges = reinterpret_cast<EdgeHead *>(J.edges) + I.at + lo;
+    uint2 *const picked = J.picked + I.at + lo;  // {id, weight} of the first phase's edges,
+    uint32_t *const list = reinterpret_cast<uint32_t *>(picked);  // then places in `edges`
     const int advance = m.slots < I.nv ? 1 : kAdvance;
-    int kept = 0, before = -1;  // parts up to `before` are admitted
-    int next = lo;              // the first id not admitted
-    for (int r = 0;; ++r) {
-        const int to = r & 1;
-        const int32_t *fl = J.list[to ^ 1] + I.at, *fb = J.rec_a[to ^ 1] + I.at,
-                      *fn = J.rec_b[to ^ 1] + I.at;
-        const uint64_t *fk = J.rec_key[to ^ 1] + I.at;
-        int32_t *tl = J.list[to] + I.at, *tb = J.rec_a[to] + I.at, *tn = J.rec_b[to] + I.at;
-        uint64_t *tk = J.rec_key[to] + I.at;
-        // ---- join: the survivors of the last list, then the round's parts
-        if (step > kLast && before < kLast) step = kLast;
-        const int listed = kept;
-        const int stop = step > kLast ? next : lo + part_end[step];
-        kept = 0;
-        for (int i0 = 0; i0 < listed || next < stop;) {
-            int e[kU], base[kU], len[kU];
-            uint64_t key[kU];
-            uint32_t on = 0;
-            if (i0 < listed) {
+    auto first = [&](uint32_t w, int e) {
+        const uint32_t bw = (uint32_t)(bound >> 32);
+        return w == bw ? m.key_of(w, e) >= bound : w > bw;
+    };
+    int records = 0, kept = 0, before = -1;  // parts up to `before` are admitted
+    for (int r = 0, phase = 0;; ++phase) {
+        const int old = records;
+        if (phase == 0) {
+            constexpr int kPickU = 4;
+            int count = 0;
+            for (int c0 = lo; c0 < end; c0 += kPickU * kWave) {
+                uint32_t w[kPickU];
 #pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const int i = i0 + u * kWave + lane, at = lo + i;
-                    const bool v = i < listed;
-                    e[u] = v ? fl[at] : 0;
-                    base[u] = v ? (kPairs ? 2 * e[u] : fb[at]) : 0;
-                    len[u] = v ? (kPairs ? 2 : fn[at]) : 0;
-                    key[u] = v ? fk[at] : 0;
-                    on |= len[u] > 0 ? 1u << u : 0;  // an empty edge was matched by its test
-                }
-                i0 += kGroup;
-            } else {
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const int i = next + u * kWave + lane;
-                    e[u] = i < stop ? ids[i] : 0;
-                    on |= i < stop ? 1u << u : 0;
+                for (int u = 0; u < kPickU; ++u) {
+                    const int e = c0 + u * kWave + lane;
+                    w[u] = e < end ? I.w[e] : 0;
                 }
 #pragma unroll
+                for (int u = 0; u < kPickU; ++u) {
+                    const int e = c0 + u * kWave + lane;
+                    const bool take = e < end && first(w[u], e);
+                    const uint64_t mask = __ballot(take);
+                    if (take) picked[count + bits_below(mask)] = make_uint2((uint32_t)e, w[u]);
+                    count += __popcll(mask);
+                }
+            }
+            wave_fence();
+            for (int c0 = 0; c0 < count; c0 += kU * kWave) {
+                EdgeHead h[kU];
+#pragma unroll
                 for (int u = 0; u < kU; ++u) {
-                    base[u] = len[u] = 0;
-                    key[u] = 0;
-                    if (on >> u & 1) {
-                        m.place(e[u], base[u], len[u]);
-                        key[u] = m.key(e[u]);
+                    const int i = c0 + u * kWave + lane;
+                    const uint2 x = picked[i < count ? i : c0];
+                    h[u].edge = make_uint4(x.x, (uint32_t)I.e_off[x.x], (uint32_t)I.e_off[x.x + 1],
+                                           x.y);
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    h[u].edge.z -= h[u].edge.y;
+                    load_head(I.e_pins, (int)h[u].edge.z, h[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int i = c0 + u * kWave + lane;
+                    if (i < count) edges[i] = h[u];
+                }
+            }
+            records = count;
+        } else {
+            for (int c0 = lo; c0 < end; c0 += kU * kWave) {
+                EdgeHead h[kU];
+                const uint64_t key[kU] = {0};  // not looked at
+                uint32_t on = 0;
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int e = c0 + u * kWave + lane, at = e < end ? e : lo;
+                    h[u].edge = make_uint4((uint32_t)e, (uint32_t)I.e_off[at],
+                                           (uint32_t)I.e_off[at + 1], I.w[at]);
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    h[u].edge.z -= h[u].edge.y;
+                    if ((int)h[u].edge.x < end && !first(h[u].edge.w, (int)h[u].edge.x))
+                        on |= 1u << u;
+                    load_head(I.e_pins, (on >> u & 1) ? (int)h[u].edge.z : 0, h[u]);
+                }
+                const uint32_t dead = head_pins<kU>(
+                    I.e_pins, h, key, on, false, [&](int v) { return m.done_word(v); },
+                    [](int v, uint64_t, uint32_t word) { return (bool)((word >> (v & 31)) & 1u); });
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const bool take = (on & ~dead) >> u & 1;
+                    const uint64_t mask = __ballot(take);
+                    if (take) edges[records + bits_below(mask)] = h[u];
+                    records += __popcll(mask);
+                }
+            }
+        }
+        // ---- list them by part, behind the edges still listed
+        int next = kept;  // the first entry not admitted
+        if (lane < kSteps) part_end[lane] = 0;
+        wave_fence();
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int c0 = old; c0 < records; c0 += kU * kWave) {
+                uint4 x[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int i = c0 + u * kWave + lane;
+                    x[u] = edges[i < records ? i : c0].edge;
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int i = c0 + u * kWave + lane;
+                    if (i < records) {
+                        const int at = atomicAdd(&part_end[part_of((int)x[u].x, x[u].w)], 1);
+                        if (pass) list[at] = (uint32_t)i;
                     }
                 }
-                next = next + kGroup < stop ? next + kGroup : stop;
             }
-            const uint32_t dead = lane_pins<kU>(
-                I.e_pins, base, len, key, false, [&](int v) { return m.done_word(v); },
-                [](int v, uint64_t, uint32_t word) { return (bool)((word >> (v & 31)) & 1u); });
-            const uint32_t live = on & ~dead;
+            wave_fence();
+            if (pass == 0) {  // counts to starts; the second pass moves them to the ends
+                const int c = lane < kSteps ? part_end[lane] : 0;
+                const int begin = next + wave_inclusive_sum(c) - c;
+                wave_fence();
+                if (lane < kSteps) part_end[lane] = begin;
+                wave_fence();
+            }
+        }
+        // ---- the rounds that admit them
+        const int last = phase == 0 ? split : kLast;
+        for (;; ++r) {
+            // ---- join: the survivors of the list, then the round's parts
+            if (step > last && before < last) step = last;
+            const int listed = kept;
+            const int stop = step > last ? next : part_end[step];
+            kept = 0;
+            for (int i0 = 0; i0 < listed || next < stop;) {
+                const bool again = i0 < listed;
+                const int from = again ? i0 : next, to = again ? listed : stop;
+                EdgeHead h[kU];
+                uint32_t at[kU];
+                uint64_t key[kU];
+                uint32_t on = 0;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const bool l = live >> u & 1;
-                const uint64_t mask = __ballot(l);
-                if (l) {
-                    const int at = lo + kept + bits_below(mask);
-                    tl[at] = e[u];
-                    if constexpr (!kPairs) {
-                        tb[at] = base[u];
-                        tn[at] = len[u];
-                    }
-                    tk[at] = key[u];
+                for (int u = 0; u < kU; ++u) {
+                    const int i = from + u * kWave + lane;
+                    at[u] = list[i < to ? i : from];
                 }
-                kept += __popcll(mask);
-            }
-            lane_act<kU>(I.e_pins, base, len, key, live,
-                         [&](int v, uint64_t k) { m.raise(v, k); });
-        }
-        before = step;
-        step += advance;
-        if (lane == 0 && kept) atomicAdd(&S.live[to], kept);
-        __syncthreads();
-        const int E = S.live[to];
-        // ---- test
-        for (int i0 = 0; i0 < kept; i0 += kGroup) {
-            int e[kU], base[kU], len[kU];
-            uint64_t key[kU];
-            uint32_t on = 0;
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int i = i0 + u * kWave + lane, at = lo + i;
-                const bool v = i < kept;
-                e[u] = v ? tl[at] : 0;
-                base[u] = v ? (kPairs ? 2 * e[u] : tb[at]) : 0;
-                len[u] = v ? (kPairs ? 2 : tn[at]) : 0;
-                key[u] = v ? tk[at] : 0;
-                on |= v ? 1u << u : 0;
-            }
-            const uint32_t lost = lane_pins<kU>(
-                I.e_pins, base, len, key, false, [&](int v) { return m.slot(v); },
-                [](int, uint64_t k, unsigned long long b) { return b != k; });
-            const uint32_t won = on & ~lost;
+                for (int u = 0; u < kU; ++u) {
+                    const int i = from + u * kWave + lane;
+                    h[u] = edges[at[u]];
+                    // A listed empty edge was matched by its test.
+                    if (i < to && !(again && h[u].edge.z == 0)) on |= 1u << u;
+                    key[u] = m.key_of(h[u].edge.w, (int)h[u].edge.x);
+                }
+                if (again)
+                    i0 += kGroup;
+                else
+                    next = next + kGroup < stop ? next + kGroup : stop;
+                const uint32_t dead = head_pins<kU>(
+                    I.e_pins, h, key, on, false, [&](int v) { return m.done_word(v); },
+                    [](int v, uint64_t, uint32_t word) { return (bool)((word >> (v & 31)) & 1u); });
+                const uint32_t live = on & ~dead;
 #pragma unroll
-            for (int u = 0; u < kU; ++u)
-                if (won >> u & 1) m.win(e[u]);
-            lane_act<kU>(I.e_pins, base, len, key, won, [&](int v, uint64_t) { m.mark(v); });
+                for (int u = 0; u < kU; ++u) {
+                    const bool l = live >> u & 1;
+                    const uint64_t mask = __ballot(l);
+                    if (l) list[kept + bits_below(mask)] = at[u];
+                    kept += __popcll(mask);
+                }
+                head_act<kU>(I.e_pins, h, key, live, [&](int v, uint64_t k) { m.raise(v, k); });
+            }
+            before = step;
+            step += advance;
+            if (lane == 0 && kept) atomicAdd(&S.live[r & 1], kept);
+            __syncthreads();
+            const int E = S.live[r & 1];
+            // ---- test
+            for (int i0 = 0; i0 < kept; i0 += kGroup) {
+                EdgeHead h[kU];
+                uint64_t key[kU];
+                uint32_t on = 0;
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int i = i0 + u * kWave + lane;
+                    h[u] = edges[list[i < kept ? i : i0]];
+                    on |= i < kept ? 1u << u : 0;
+                    key[u] = m.key_of(h[u].edge.w, (int)h[u].edge.x);
+                }
+                const uint32_t lost = head_pins<kU>(
+                    I.e_pins, h, key, on, false, [&](int v) { return m.slot(v); },
+                    [](int, uint64_t k, unsigned long long b) { return b != k; });
+                const uint32_t won = on & ~lost;
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+                    if (won >> u & 1) m.win((int)h[u].edge.x);
+                head_act<kU>(I.e_pins, h, key, won, [&](int v, uint64_t) { m.mark(v); });
+            }
+            __syncthreads();
+            if (tid == 0) S.live[r & 1 ^ 1] = 0;
+            for (int i = tid; i < m.slots; i += T) m.max[i] = 0;
+            if (before >= kLast && E <= T) {
+                *kept_out = kept;
+                return E;
+            }
+            __syncthreads();
+            if (before >= last && last < kLast) break;
         }
-        __syncthreads();
-        if (tid == 0) S.live[to ^ 1] = 0;
-        for (int i = tid; i < m.slots; i += T) m.max[i] = 0;
-        if (before >= kLast && E <= T) {
-            *kept_out = kept;
-            *parity = to;
-            return E;
-        }
-        __syncthreads();
+        ++r;
     }
 }
 
@@ -439,11 +556,12 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
             m.place(e, base, len);
             key = m.key(e);
         }
-    } else {
+    } else if constexpr (kMany) {
         constexpr int kW = T / kWave;
+        static_assert(!kPairs, "batches have no graph layout");
         const int per = ((I.ne + kW - 1) / kW + kWave - 1) / kWave * kWave;
-        int kept = 0, k = 0;
-        const int E = solo_lists<T, kPairs>(I, J, S, m, per, &kept, &k);
+        int kept = 0;
+        const int E = solo_lists<T>(I, J, S, m, per, &kept);
         if (lane == 0) S.cnt[wid] = kept;
         __syncthreads();
         mine = tid < E;
@@ -451,11 +569,13 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
         if (mine) {
             int from = 0, at = tid;
             for (; at >= S.cnt[from]; ++from) at -= S.cnt[from];
-            const int64_t i = I.at + (int64_t)from * per + at;
-            e = J.list[k][i];
-            base = kPairs ? 2 * e : J.rec_a[k][i];
-            len = kPairs ? 2 : J.rec_b[k][i];
-            key = J.rec_key[k][i];
+            const int64_t i = I.at + (int64_t)from * per;  // the wave's range
+            const uint4 x =
+                J.edges[2 * (i + reinterpret_cast<const uint32_t *>(J.picked + i)[at])];
+            e = (int)x.x;
+            base = (int)x.y;
+            len = (int)x.z;
+            key = m.key_of(x.w, e);
         }
     }
 
