@@ -1289,7 +1289,7 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
     // (solo.hip), unless the mean instance alone is too long for it.
     const size_t order_room = s.solo ? 40 * (size_t)lay.solo_rounds : 0;
     const bool too_long = o.solo_max_kappa == 0 && b->count > 0 &&
-                          b->kappa_total / b->count > kSoloShort + b->kappa_total / kSoloShare;
+                          b->kappa_total / b->count > solo_longest(b->kappa_total);
     if (s.explicit0 && staged_call(o, stats) && b->m_total > 0 && !too_long &&
         4 * (size_t)b->count <= order_room) {
         SoloJob J;

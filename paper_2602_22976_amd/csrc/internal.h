@@ -257,9 +257,13 @@ struct SoloJob {
     int64_t *report;     // {instances listed, instances left to the round kernels}
     int32_t choose;      // leave the solo part out where the round kernels are faster
 };
-// The solo part runs when its longest instance has at most kSoloShort pins and
-// a kSoloShare-th of the batch's.
-constexpr int64_t kSoloShort = 24 * 1024, kSoloShare = 128;
+// The solo part runs when its longest instance has at most this many of the
+// batch's pins (solo.hip says why).
+constexpr int64_t kSoloShort = 40 * 1024, kSoloShare = 64, kSoloLess = 48 * 1024;
+__host__ __device__ __forceinline__ int64_t solo_longest(int64_t kappa) {
+    const int64_t share = kappa / kSoloShare - kSoloLess;
+    return share > kSoloShort ? share : kSoloShort;
+}
 // LDS of the done bits of n vertices; the maxima follow when they fit.
 __host__ __device__ __forceinline__ int64_t solo_done_bytes(int64_t n) {
     return (4 * ((n + 31) / 32) + 15) & ~(int64_t)15;

@@ -768,10 +768,13 @@ __global__ void __launch_bounds__(T, 4) k_solo_batch(SoloJob J) {
 //
 // With J.choose the bound on an instance's pins is the default, and the whole
 // solo part is left out when its longest instance would outlast the round
-// kernels on the whole batch: a workgroup matches about 1e6 pins a millisecond,
-// the grid's rounds take about 0.15 ms and 1 ms per 6e7 pins, and running both
-// parts costs the fixed time of both.  (512 instances of up to 7e5 pins, 5e7 in
-// all: 0.99 ms in the rounds, 1.30 here; 1,500 of them, 1.6e8: 2.60 and 1.81.)
+// kernels on the whole batch: a workgroup matches about 1e6 pins a millisecond
+// after 0.1 ms, the grid's rounds take about 0.15 ms and 1 ms per 6e7 pins, and
+// running both parts costs the fixed time of both.  (Instances of up to 7e5
+// pins, rounds / here in ms: 400 of them, 4e7 pins, 0.78 / 0.93; 512 0.98 /
+// 0.87; 1,500, 1.6e8, 2.60 / 1.17.  Up to 7e4: 256, 4.2e6, 0.23 / 0.28.  Up to
+// 2.8e5: 400, 1.9e7, 0.41 / 0.49.  Up to 3.8e4: 2, 4e4, 0.14 / 0.12; 64, 6.8e5,
+// 0.14 / 0.12; 1,000, 1.05e7, 0.31 / 0.17.)
 constexpr int kOrderThreads = 1024;
 __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
     constexpr int kClasses = 128;
@@ -795,7 +798,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
         __syncthreads();
     }
     const bool none =
-        J.choose && (int64_t)longest > kSoloShort + J.pin_base[J.count] / kSoloShare;
+        J.choose && (int64_t)longest > solo_longest(J.pin_base[J.count]);
     auto size_class = [&](int i) -> int {  // -1: left to the round kernels, -2: nothing to match
         const int64_t n = J.v_base[i + 1] - J.v_base[i], k = J.pin_base[i + 1] - J.pin_base[i];
         if (J.e_base[i + 1] == J.e_base[i]) return -2;
