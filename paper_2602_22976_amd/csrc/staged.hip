@@ -45,6 +45,7 @@ constexpr int kFill = 16;     // chunks of edges looked at in one step (join_wav
 constexpr int kSamplesPerGroup = 16;
 constexpr int kThresholds = kStagedSteps - 1;
 constexpr int kFromMaxima = 3;
+constexpr int kSweep = 4;  // the step at which the edges left are looked at
 __device__ constexpr int kRank[kThresholds] = {1, 16, 98, 25, 51, 128};
 
 template <bool kB>
@@ -244,7 +245,8 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
     const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
     const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
         m, scratch[wid], queue[wid], g.e_pins, lists(s, from), lists(s, to), range.lo, end,
-        round > 0 ? s.rec_c[from][range.wave] : 0, round == 0, first + round, step_bytes(s),
+        round > 0 ? s.rec_c[from][range.wave] : 0, round == 0,
+        first + round == (first < kSweep ? kSweep : first + 1), first + round, step_bytes(s),
         reinterpret_cast<const uint64_t *>(s.hot));
     if (lane_id() == 0) {
         s.rec_c[to][range.wave] = kept;

@@ -236,7 +236,9 @@ struct WaveLists {
 // the join writes each edge's step, the number of thresholds above its key (so
 // that a lower key never has an earlier step, whatever the thresholds), and
 // admits the steps up to `step`; later rounds read that byte instead of the
-// weight.
+// weight.  The join with `sweep` looks at the first pins of every edge not
+// admitted yet and drops the dead ones, so that the steps from it on hold few
+// edges.
 //
 // Edges to look at wait in LDS (cand) until they fill a wave, and one loop
 // takes them and the last round's list: flat_edges is inlined once.  (With a
@@ -248,12 +250,13 @@ struct WaveLists {
 // w, k) / exact_sort(e, w) (weight or key that the thresholds are compared
 // with), entered(len).
 // kFill: chunks of 64 edges looked at in one step, at most (a multiple of 4).
+constexpr uint8_t kNever = 255;  // step of an edge that was dropped
 constexpr int cand_size(int fill) { return (fill + 1) * kWave; }
 template <bool kPairs, bool kB, int kKeep, int kSteps, int kFill, class M>
 __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const int32_t *e_pins,
                                          const WaveLists &from, const WaveLists &to, int64_t lo,
-                                         int64_t end, int listed, bool first_round, int step,
-                                         uint8_t *steps, const uint64_t *thresholds) {
+                                         int64_t end, int listed, bool first_round, bool sweep,
+                                         int step, uint8_t *steps, const uint64_t *thresholds) {
     const int lane = lane_id();
     int queued = 0;
     auto push = [&](int64_t e, bool on) {
@@ -319,16 +322,17 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
             }
         return 4 * kU * kWave;
     };
-    // Half of all edges: the first two pins, then the next four, show that
-    // nearly all of them are dead, so that few are queued.
+    // Every edge not admitted yet: the first two pins, then the next four, show
+    // that most of them are dead.  Their step becomes kNever.
     auto fill_rest = [&](int64_t c0) -> int {
         constexpr int kU = 4;
-        int base[kU], len[kU], vb[kU], p0[kU], p1[kU];
+        int base[kU], len[kU], vb[kU], p0[kU], p1[kU], part[kU];
         bool on[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int64_t at = c0 + u * kWave + lane;
-            on[u] = at < end && steps[at] == step;
+            part[u] = at < end ? steps[at] : 0;
+            on[u] = part[u] >= step;
             base[u] = len[u] = vb[u] = 0;
             if (at < end) m.place((int)at, base[u], len[u], vb[u]);
         }
@@ -375,7 +379,11 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
                 for (int q = 0; q < 4; ++q) on[u] = on[u] && !((d[u][q] >> (p[u][q] & 31)) & 1);
         }
 #pragma unroll
-        for (int u = 0; u < kU; ++u) push(c0 + u * kWave + lane, on[u]);
+        for (int u = 0; u < kU; ++u) {
+            const int64_t at = c0 + u * kWave + lane;
+            if (part[u] > step && !on[u]) steps[at] = kNever;
+            push(at, on[u] && part[u] == step);
+        }
         return kU * kWave;
     };
 
@@ -410,7 +418,7 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
                     push(c0 + lane, c0 + lane < end);
                     c0 += kWave;
                 } else {
-                    c0 += first_round ? fill_first(c0) : all ? fill_rest(c0) : fill_few(c0);
+                    c0 += first_round ? fill_first(c0) : sweep ? fill_rest(c0) : fill_few(c0);
                 }
             }
             if (queued == 0) break;
