@@ -609,6 +609,10 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     // CREW: setup finds the weight range.  AUTO: the round-0 edge kernel does,
     // only when it leaves the round to the vertex form.
     if (o.variant == HGM_VARIANT_CREW && !batch) init_flags |= kInitWeightRange;
+    const bool max0 = o.variant == HGM_VARIANT_AUTO && o.have_vertex_side;
+    const bool sampled = !max0 && !crew_round(o, 0) && !g.pairs && !batch &&
+                         g.kappa >= kHubSampleKappa && (int64_t)s.grid * s.region >= kSampleRoom;
+    if (sampled) init_flags |= kInitSample;
     KernelTimer T;
     T.on = stats && stats->timing;
     T.stream = L.stream;
@@ -655,7 +659,7 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     bool finished = g.m == 0;
     if (!finished) {
         HGM_TRY(T.resume());
-        if (o.variant == HGM_VARIANT_AUTO && o.have_vertex_side) {
+        if (max0) {
             HGM_TRY(launch_max0(L, g, s, kseed(0)));
             max0_event = (int)T.cls.size();
             HGM_TRY(T.after(HGM_K_VERTEX_MAX, 0));
@@ -663,7 +667,7 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
             HGM_TRY(launch_vertex_max(L, g, s, 0, kseed(0), 0));
             HGM_TRY(T.after(HGM_K_VERTEX_MAX, 0));
         } else {
-            HGM_TRY(launch_scatter(L, g, s, kseed(0)));
+            HGM_TRY(launch_scatter(L, g, s, kseed(0), sampled));
             HGM_TRY(T.after(HGM_K_SCATTER, 0));
         }
     }

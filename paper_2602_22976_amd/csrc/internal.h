@@ -288,6 +288,8 @@ constexpr int kInitWeightRange = 4;  // smallest and largest weight (CREW round-
                                      // one instance: equal weights need no gather)
 constexpr int kInitLiveMark = 8;     // with kInitLiveKey: live_key = w << 32 | 1 (priorities
                                      // redrawn every round)
+constexpr int kInitSample = 16;      // sample the pins for hubs (kernels.hip, hub_sample)
+constexpr int kSampleRoom = 1024;    // entries that the sampled hubs take of a list
 // `kseed` arguments: the priority seed of the round the kernel works on
 // (the call's seed, or round_seed(seed, r) when the order is redrawn);
 // `rekey`: nonzero when the order is redrawn every round.
@@ -300,7 +302,9 @@ hipError_t launch_solo(const Launch &L, const Graph &g, const State &s, const So
 hipError_t launch_zero(const Launch &L, uint32_t *p, int64_t words);
 hipError_t launch_live0(const Launch &L, const Graph &g, const State &s, const SoloArgs &a);
 hipError_t launch_validate(const Launch &L, const Graph &g, const State &s, int check_dual);
-hipError_t launch_scatter(const Launch &L, const Graph &g, const State &s, uint32_t kseed);
+// sampled: with the hubs that kInitSample found (one instance, offset layout).
+hipError_t launch_scatter(const Launch &L, const Graph &g, const State &s, uint32_t kseed,
+                          bool sampled);
 // binned (CRCW form, one instance, offset layout, s.bin_nb > 0): the next
 // round's maximum by bins (k_retire_bin, then k_bin_max) instead of atomics.
 hipError_t launch_retire(const Launch &L, const Graph &g, const State &s, int round, int scatter,

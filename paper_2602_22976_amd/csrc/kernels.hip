@@ -290,6 +290,63 @@ __device__ void hub_table_build(HubTable &H, const State &s) {
     __syncthreads();
 }
 
+// The hubs of an instance without the vertex side (or whose rounds do not count
+// degrees): vertices met at least kSampleHits times among kHubSamples sampled
+// pins, left in rec_a[0] (free until round 2's lists): their number, their ids.
+// One workgroup; samples whose table slot another vertex took are dropped.
+constexpr int kHubSamples = 4096, kSampleHits = 4;
+struct HubSample {
+    int id[kHubSamples], hits[kHubSamples], count;
+};
+__device__ __forceinline__ void hub_sample(const Graph &g, const State &s, HubSample &S) {
+    constexpr int kOwn = kHubSamples / kBlock;
+    int v[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const int64_t i = q * kBlock + threadIdx.x;
+        v[q] = g.e_pins[g.kappa * i / kHubSamples];
+    }
+    for (int i = threadIdx.x; i < kHubSamples; i += kBlock) {
+        S.id[i] = -1;
+        S.hits[i] = 0;
+    }
+    if (threadIdx.x == 0) S.count = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const int h = (int)(((uint32_t)v[q] * 0x9E3779B1u) >> 20);
+        static_assert(kHubSamples == 1 << 12, "the hash's bits");
+        const int was = atomicCAS(&S.id[h], -1, v[q]);
+        if (was == -1 || was == v[q]) atomicAdd(&S.hits[h], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kHubSamples; i += kBlock)
+        if (S.hits[i] >= kSampleHits) {
+            const int at = atomicAdd(&S.count, 1);
+            if (at < kHubTableMax) s.rec_a[0][1 + at] = S.id[i];
+        }
+    __syncthreads();
+    if (threadIdx.x == 0) s.rec_a[0][0] = S.count < kHubTableMax ? S.count : kHubTableMax;
+}
+
+// Fills the table from the sampled hubs; whether there are any.
+__device__ bool hub_table_sampled(HubTable &H, const State &s) {
+    const int n = s.rec_a[0][0];
+    if (n == 0) return false;
+    for (int i = threadIdx.x; i < kHubSlots; i += kBlock) {
+        H.id[i] = -1;
+        H.mx[i] = 0;
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < n; q += kBlock) {
+        const int v = s.rec_a[0][1 + q];
+        int h = hub_home(v);
+        while (atomicCAS(&H.id[h], -1, v) != -1) h = (h + 1) & (kHubSlots - 1);
+    }
+    __syncthreads();
+    return true;
+}
+
 // scatter_chunk with hub pins reduced in the table.
 template <bool kB>
 __device__ __forceinline__ void scatter_chunk_hubs(const ChunkLds &L, const int32_t *e_pins,
@@ -386,9 +443,9 @@ __device__ void reduce_weight_range(const Graph &g, const State &s) {
 
 // Setup: cleared per-vertex state and bitmap; optionally the CREW live keys,
 // the pieces of high-degree vertices and the weight range.
-__global__ void __launch_bounds__(kBlock) k_init(Graph g, uint32_t seed, State s, uint32_t *bits,
-                                                 int flags) {
-    __shared__ unsigned long long sum_tmp[kWaves];
+__device__ __forceinline__ void init_body(const Graph &g, uint32_t seed, const State &s,
+                                          uint32_t *bits, int flags,
+                                          unsigned long long *sum_tmp) {
     unsigned long long hot = 0;
     const int64_t words = g.words;
     const int64_t edges = (flags & kInitLiveKey) ? g.m : 0;  // edge-indexed work: live keys only
@@ -424,6 +481,21 @@ __global__ void __launch_bounds__(kBlock) k_init(Graph g, uint32_t seed, State s
         if (threadIdx.x == 0 && hot) atomicAdd(&s.hot[blockIdx.x % kSub], hot);
     }
     if (flags & kInitWeightRange) reduce_weight_range(g, s);
+}
+
+__global__ void __launch_bounds__(kBlock) k_init(Graph g, uint32_t seed, State s, uint32_t *bits,
+                                                 int flags) {
+    __shared__ unsigned long long sum_tmp[kWaves];
+    init_body(g, seed, s, bits, flags, sum_tmp);
+}
+
+// With kInitSample: workgroup 0 samples the hubs while the others clear.
+__global__ void __launch_bounds__(kBlock) k_init_sample(Graph g, uint32_t seed, State s,
+                                                        uint32_t *bits, int flags) {
+    __shared__ unsigned long long sum_tmp[kWaves];
+    __shared__ HubSample S;
+    if (blockIdx.x == 0) hub_sample(g, s, S);
+    init_body(g, seed, s, bits, flags, sum_tmp);
 }
 
 // ---------------------------------------------------------------------------
@@ -600,6 +672,17 @@ template <bool kPairs, bool kB>
 __global__ void __launch_bounds__(kBlock) k_scatter0(Graph g, State s, uint32_t kseed) {
     __shared__ ChunkLds L;
     scatter0_region<kPairs, kB>(g, s, L, xcd_item(blockIdx.x, gridDim.x), kseed);
+}
+
+// The same with sampled hubs.  Bound by requests beyond L2, and without the
+// table by atomics on one address, which serialise: 4.1 M pins with Zipf
+// popularity took 143 to 194 us, 92 us so (hits from 2 to 8: the same).
+__global__ void __launch_bounds__(kBlock) k_scatter0_hubs(Graph g, State s, uint32_t kseed) {
+    __shared__ ChunkLds L;
+    __shared__ HubTable H;
+    const bool hubs = hub_table_sampled(H, s);
+    scatter0_region<false, false>(g, s, L, xcd_item(blockIdx.x, gridDim.x), kseed,
+                                  hubs ? &H : nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -2148,8 +2231,12 @@ __global__ void __launch_bounds__(kBlock) k_zero_words(uint32_t *p, int64_t n) {
 hipError_t launch_init(const Launch &L, const Graph &g, uint32_t seed, const State &s,
                        uint32_t *bits, int init_flags) {
     hipLaunchKernelGGL(k_prologue, dim3(1), dim3(kBlock), 0, L.stream, g, s);
-    hipLaunchKernelGGL(k_init, dim3(L.grid), dim3(kBlock), 0, L.stream, g, seed, s, bits,
-                       init_flags);
+    if (init_flags & kInitSample)
+        hipLaunchKernelGGL(k_init_sample, dim3(L.grid), dim3(kBlock), 0, L.stream, g, seed, s, bits,
+                           init_flags);
+    else
+        hipLaunchKernelGGL(k_init, dim3(L.grid), dim3(kBlock), 0, L.stream, g, seed, s, bits,
+                           init_flags);
     return hipGetLastError();
 }
 
@@ -2203,12 +2290,15 @@ hipError_t launch_validate(const Launch &L, const Graph &g, const State &s, int 
 // Launch helpers: the instantiation follows the layout (graph pairs or
 // offsets) and whether the graph is a batch (g.vbase set); batches of graphs
 // in the pair layout are rejected by the interface.
-hipError_t launch_scatter(const Launch &L, const Graph &g, const State &s, uint32_t kseed) {
+hipError_t launch_scatter(const Launch &L, const Graph &g, const State &s, uint32_t kseed,
+                          bool sampled) {
     const dim3 grid(s.grid), block(kBlock);
     if (g.pairs)
         hipLaunchKernelGGL((k_scatter0<true, false>), grid, block, 0, L.stream, g, s, kseed);
     else if (g.vbase)
         hipLaunchKernelGGL((k_scatter0<false, true>), grid, block, 0, L.stream, g, s, kseed);
+    else if (sampled)
+        hipLaunchKernelGGL(k_scatter0_hubs, grid, block, 0, L.stream, g, s, kseed);
     else
         hipLaunchKernelGGL((k_scatter0<false, false>), grid, block, 0, L.stream, g, s, kseed);
     return hipGetLastError();

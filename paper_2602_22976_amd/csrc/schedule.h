@@ -43,6 +43,11 @@ inline int64_t solo_auto_bound(int64_t kappa_total) {
 // edges and kSoloOneKappa pins in one workgroup (tiny: 50 -> 28 us).
 constexpr int64_t kSoloBatchKappa = (int64_t)1 << 20;
 constexpr int64_t kSoloOneKappa = (int64_t)1 << 17;
+// An edge-centric round 0 of one instance samples the pins for hubs from this
+// many pins, in the setup kernel (Zipf popularity: a call of 4.1 M pins 470 ->
+// 380 us; a hub in a quarter of the edges, 4.8 M: 600 -> 480; none, 1.1 M: 3 us
+// of 245 for nothing).
+constexpr int64_t kHubSampleKappa = (int64_t)1 << 20;
 // Rounds over all edges: the last ones run in one workgroup (ending.hip, up to
 // 2,048 edges and 8,192 pins) after as many rounds as leave about this many
 // live pins (or edges, where those run out first) at the usual shrink per

@@ -95,3 +95,31 @@ def test_round_limit(hgm, variant):
         with pytest.raises(hgm.HgmError) as ei:
             hgm.match(dg, 4, hgm.make_opts(variant, max_rounds=limit, solo_max_kappa=-1))
         assert ei.value.code == hgm.HGM_E_ROUND_LIMIT
+
+
+@pytest.mark.parametrize("reseed", [False, True])
+@pytest.mark.parametrize("n,hubs,share", [(100, 0, 0), (400, 0, 0), (2000, 0, 0), (300_000, 0, 0),
+                                          (300_000, 1, 0.3), (300_000, 40, 0.5)])
+def test_sampled_hubs(hgm, n, hubs, share, reseed):
+    """An edge-centric round 0 whose hubs come from a sample of the pins, from
+    2^20 pins on: every vertex a hub, more than its table holds, none, one and
+    some; the vertex side given and not."""
+    import torch
+    rng = np.random.default_rng(n + hubs)
+    m, size = (1 << 20) // 4 + 3, 4
+    pins = rng.integers(hubs, n - size, (m, 1)) + np.arange(size)
+    if hubs:
+        pick = rng.random(m) < share
+        pins[pick, 0] = rng.integers(0, hubs, int(pick.sum()))
+    g = synth.from_edge_lists(n, pins, rng.integers(1, 1000, m).astype(np.uint32))
+    exp, ref = oracle.local_max(g.n, g.m, g.e_off, g.e_pins, g.v_off, g.v_edges, g.w, 3,
+                                reseed=reseed)
+    dg = hgm.DeviceHypergraph.from_host(g, "cuda:0")
+    none = torch.empty(0, dtype=torch.int32, device="cuda:0")
+    bare = hgm.DeviceHypergraph(g.n, g.m, dg.e_off, dg.e_pins, none, none, dg.w)
+    for d, variant in ((dg, "crcw"), (bare, "auto")):
+        print(f"n={n} hubs={hubs} reseed={reseed} {variant}", flush=True)
+        bits, st = hgm.match(d, 3, hgm.make_opts(variant, reseed=reseed))
+        assert np.array_equal(bits.cpu().numpy().view(np.uint32), exp)
+        for k in ("live_edges", "live_pins", "matched_per_round"):
+            assert np.array_equal(st[k], ref[k]), k
