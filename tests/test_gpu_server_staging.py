@@ -43,9 +43,20 @@ def _serve(hgm, reqs, **kw):
 CHUNK = 1 << 19  # pins (or weights) in a chunk of 2 MB
 
 
+def _pinned(g):
+    """The same instance in pinned memory, which large arrays are copied from
+    without a chunk."""
+    import torch
+    for k in ("e_off", "e_pins", "v_off", "v_edges", "w"):
+        x = getattr(g, k)
+        setattr(g, k, torch.from_numpy(x.view(np.int32)).pin_memory().numpy().view(x.dtype))
+    return g
+
+
+@pytest.mark.parametrize("pinned", [False, True])
 @pytest.mark.parametrize("edge_side_only", [True, False])
 @pytest.mark.parametrize("workers", [1, 5])
-def test_chunk_edges(hgm, workers, edge_side_only):
+def test_chunk_edges(hgm, workers, edge_side_only, pinned):
     reqs = [synth.from_edge_lists(0, [], []), synth.from_edge_lists(3, [[0, 2]], [7])]
     for kappa in (1, 63, 64, 65, CHUNK - 300, CHUNK, CHUNK + 1, 3 * CHUNK + 17):
         m = max(1, kappa // 4)
@@ -56,6 +67,8 @@ def test_chunk_edges(hgm, workers, edge_side_only):
         edges = [((int(rng.integers(n)) + np.arange(k)) % n).tolist() for k in sizes]
         reqs.append(synth.from_edge_lists(n, edges, rng.integers(1, 99, m)))
         reqs.append(synth.from_edge_lists(5, [], []))
+    if pinned:  # every other one: direct copies between chunks
+        reqs = [_pinned(g) if i % 4 < 2 else g for i, g in enumerate(reqs)]
     _serve(hgm, reqs, workers=workers, edge_side_only=edge_side_only)
 
 
