@@ -30,7 +30,9 @@
  *
  * Conventions for every entry point:
  *  - All array pointers inside hgm_csr, the output bitmap and the workspace
- *    are DEVICE pointers owned by the caller; the library allocates nothing.
+ *    are DEVICE pointers owned by the caller; the library allocates nothing on
+ *    the device.  (On first use a process takes 128 KB of pinned host memory,
+ *    through which counters are read; hgm_match_noalloc does not take it.)
  *  - `stream` is a hipStream_t (NULL = default stream).  Work is enqueued on
  *    it in batches of rounds (opts->rounds_per_sync rounds, or a number the
  *    library predicts from the instance when that is 0); the stream is

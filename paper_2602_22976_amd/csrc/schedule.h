@@ -61,13 +61,14 @@ constexpr int kStagedGrid = 1024;
 // Rounds by admission: round 0 starts with the first step expected to admit
 // at least this many edges (fewer leave the grid idle for a whole round).
 constexpr int64_t kStagedFirstEdges = 1024;
-// The tail follows in the round of the last admission for instances of at most
-// this many edges (up to 2^19 edges: one round later, and so on).
+// The last rounds' workgroup follows in the round of the last admission for
+// instances of at most this many edges (up to 2^19 edges: one round later, and
+// so on).
 constexpr int64_t kStagedTailEdges = (int64_t)1 << 15;
-// One instance: the tail workgroup takes over a round with at most this many
-// live pins (and at most 65536 live edges).  Off unless asked for: on the
-// synthetic workloads a round in one workgroup costs as much as a round of
-// the grid-wide kernels (both are a chain of dependent memory accesses).
+// One instance: the tail workgroup (k_tail, state in global memory) takes over
+// a round with at most this many live pins (and at most 65536 live edges).  Off
+// unless asked for: a round there costs as much as a round of the grid-wide
+// kernels (both are a chain of dependent memory accesses).
 constexpr int kDefaultTailPins = -1;
 // Binned maximum: automatic by default (0): on for large instances whose
 // round 0 takes the vertex form, where it won (hub-stress 1.26 -> 1.18 ms);

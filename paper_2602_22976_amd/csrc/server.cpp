@@ -13,6 +13,7 @@
 // copied out, which admits waiting requests.  A request's result does not
 // depend on the wave it ran in (instances of a batch are independent).
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 #include <string.h>
 
 #include <algorithm>
@@ -499,10 +500,11 @@ void worker_main(hgm_server *S, hipStream_t stream, int self) {
                 n = m = kappa = words = 0;
                 bool fits_alone = true;
                 const bool vside = !S->opts.edge_side_only;
-                size_t queued = 0, taken = 0;
-                for (const Pending &p : S->queue) queued += request_bytes(p.req, vside);
-                const size_t share =
-                    std::max(kWaveMinBytes, queued / (size_t)(S->idle + 1));
+                size_t queued = 0, taken = 0, share = SIZE_MAX;
+                if (S->idle > 0) {
+                    for (const Pending &p : S->queue) queued += request_bytes(p.req, vside);
+                    share = std::max(kWaveMinBytes, queued / (size_t)(S->idle + 1));
+                }
                 for (size_t i = 0; i < S->queue.size() && (int)wave.size() < max_batch &&
                                    taken < share;
                      ++i) {

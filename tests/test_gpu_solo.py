@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import synth
-from tests.fixtures import path_graph
+from tests.fixtures import disjoint, path_graph, star
 
 pytestmark = pytest.mark.gpu
 
@@ -110,3 +110,22 @@ def test_batch(hgm, solo):
             exp = oracle.greedy(g.n, g.m, g.e_off, g.e_pins, g.w, 5 + i)[0]
             seg = _bits(bits)[int(b.word_base[i]):int(b.word_base[i + 1])]
             assert np.array_equal(seg, exp), f"instance {i}, vertex side {side}"
+
+
+@pytest.mark.parametrize("solo", [0, 1 << 20])
+def test_two_phases(hgm, solo):
+    """The first parts of the order, then the edges they leave: instances at the
+    least edges that are split, none or nearly all dead at the split, ties at
+    its key, weights in the order of the ids, edges beyond a record's pins."""
+    import torch
+    gs = [synth.random_instance(200 + m, n, m, 1, 9, 1, w, empty_frac=0.02)
+          for n in (60, 2500, 30_000) for m in (512, 513, 2048, 2049, 9001) for w in (1, 2, 10**6)]
+    gs += [path_graph(5000), disjoint(20_000), disjoint(3000, size=40), star(6000), star(6000, wmax=1),
+           synth.random_instance(9, 40_000, 5000, 3, 90, 1, 100)]
+    b = synth.batch_from_instances(gs, np.arange(5, 5 + len(gs), dtype=np.uint32))
+    db = hgm.DeviceBatch.from_host(b, "cuda:0")
+    bits, _ = hgm.match_batch(db, hgm.make_opts(solo_max_kappa=solo), want_stats=False)
+    got = bits.cpu().numpy().view(np.uint32)
+    for i, g in enumerate(gs):
+        exp = oracle.greedy(g.n, g.m, g.e_off, g.e_pins, g.w, 5 + i)[0]
+        assert np.array_equal(got[int(b.word_base[i]):int(b.word_base[i + 1])], exp), (i, g.n, g.m)
