@@ -964,7 +964,9 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
                uint32_t *bits, const BatchIn *batch, bool may_allocate) {
     // Its own edge grid: a wave's lists stay below index m whatever the grid.
     const int64_t chunks = ((int64_t)g.m + kBlock - 1) / kBlock;
-    const int64_t most = o.edge_grid ? o.edge_grid : kStagedGrid;
+    const int64_t most = o.edge_grid               ? o.edge_grid
+                         : g.m > kStagedLargeEdges ? kStagedGridLarge
+                                                   : kStagedGrid;
     s.region = (int)((chunks + most - 1) / most) * kBlock;
     s.grid = (int)((chunks * kBlock + s.region - 1) / s.region);
     if (batch) HGM_TRY(launch_batch_setup(L, g, *batch, s));

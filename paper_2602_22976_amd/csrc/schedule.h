@@ -55,9 +55,14 @@ constexpr int64_t kHubSampleKappa = (int64_t)1 << 20;
 // and one a round late two near-empty launches (about 13 us).
 constexpr double kEndingPins = 5000.0;
 constexpr double kEndingEdges = 1400.0;
-// Rounds by admission: workgroups of the join and the test (at 1536: power-law
-// 444 against 377 us, hub-stress 562 against 497, RGG 453 against 429).
-constexpr int kStagedGrid = 1024;
+// Rounds by admission: workgroups of the join and the test.  A wave's work
+// between two waits grows with its range, and the chip is full with 8 waves a
+// compute unit (1024 against 512: 600,000 edges 222 / 208 us, RGG, 6.9M, 404 /
+// 385, hub-stress, 4M, 470 / 455, power-law, 5M, the same); from about 8M edges
+// on 16 waves hide more (10M 1,215 / 1,240, 20M 1,750 / 1,805).  At 256 or 1536
+// all take longer.
+constexpr int kStagedGrid = 512, kStagedGridLarge = 1024;
+constexpr int64_t kStagedLargeEdges = (int64_t)1 << 23;
 // Rounds by admission: round 0 starts with the first step expected to admit
 // at least this many edges (fewer leave the grid idle for a whole round).
 constexpr int64_t kStagedFirstEdges = 1024;
