@@ -581,7 +581,6 @@ EndArgs end_args(const State &s, unsigned long long *report) {
     EndArgs a;
     memset(&a, 0, sizeof(a));
     a.report = report;
-    a.run = 1;
     for (int k = 0; k < 2; ++k) a.counts[k] = s.cnt[k];
     a.lists = s.grid;
     a.stride = s.region;

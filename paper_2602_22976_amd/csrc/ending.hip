@@ -79,16 +79,14 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
             if (lane == 0) {
                 for (int q = 0; q < 5; ++q) a.report[kEndHeader + 5 * (r - a.first) + q] = v[q];
                 if (st.bin_overflow) a.report[kEndOverflow] = 1;
-                if (r == 0) a.report[kEndForm] = st.form;
             }
         }
     }
     const unsigned long long live = wave_total(s.stats[a.round % s.ring].live[lane]);
     const bool limit = a.max_rounds > 0 && a.round >= a.max_rounds;
-    if (live == 0 || live > (unsigned long long)kEdges || limit || !a.run) {
+    if (live == 0 || live > (unsigned long long)kEdges || limit) {
         if (tid == 0) {
             a.report[kEndFinished] = live == 0;
-            a.report[kEndLive] = live;
             a.report[kEndRounds] = (unsigned long long)a.round;
         }
         return;
@@ -128,7 +126,6 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
     if (total > kPins) {  // left to the grid's rounds
         if (tid == 0) {
             a.report[kEndFinished] = 0;
-            a.report[kEndLive] = live;
             a.report[kEndRounds] = (unsigned long long)a.round;
         }
         return;
@@ -291,7 +288,6 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
     }
     if (tid == 0) {
         a.report[kEndFinished] = stopped ? 0 : 1;
-        a.report[kEndLive] = (unsigned long long)live_now;
         a.report[kEndRounds] = (unsigned long long)r;
     }
 }

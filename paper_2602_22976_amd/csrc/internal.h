@@ -330,10 +330,8 @@ hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, i
 // few edges are left, every remaining round.  The lists are `lists` many, list w
 // at slot w * stride with counts[parity][w] edges.
 constexpr int kEndFinished = 0;  // words of the report: 1 when no live edge is left
-constexpr int kEndLive = 1;      // live edges left
-constexpr int kEndRounds = 2;    // rounds run (with edges left: whose test is to come)
-constexpr int kEndOverflow = 3;  // set when a bin overflowed in one of the rounds
-constexpr int kEndForm = 4;      // RoundStats::form, when round 0 is among them
+constexpr int kEndRounds = 1;    // rounds run (with edges left: whose test is to come)
+constexpr int kEndOverflow = 2;  // set when a bin overflowed in one of the rounds
 constexpr int kEndHeader = 8;    // then 5 words a round: live edges and pins, matched
                                  // edges, their weight and pins
 struct EndArgs {
@@ -343,7 +341,6 @@ struct EndArgs {
     int32_t first, round;
     uint32_t seed;
     int32_t reseed, max_rounds;
-    int32_t run;
     int32_t counting;  // report the rounds' counts (rounds beyond the `rows` that fit:
     int32_t rows;      // rec_key[round & 1], one word each: live edges, live pins, matched
                        // edges and their pins in 16 bits each; rec_key[other]: the weight)
