@@ -128,12 +128,13 @@ __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s
     const int64_t stride = (int64_t)(gridDim.x - 1) * kSetupThreads;
     const int64_t at = (int64_t)(blockIdx.x - 1) * kSetupThreads + tid;
     // The arrays start at 256-byte boundaries and are padded to them.
-    for (int64_t i = at; i < (g.n + 1) / 2; i += stride) {
+    const int64_t n = g.n;  // up to 2^31 - 1: rounded up in 64 bits
+    for (int64_t i = at; i < (n + 1) / 2; i += stride) {
         reinterpret_cast<ulonglong2 *>(s.best[0])[i] = make_ulonglong2(0, 0);
         reinterpret_cast<ulonglong2 *>(s.best[1])[i] = make_ulonglong2(0, 0);
     }
     uint32_t *done = done_bits(s);
-    for (int64_t i = at; i < (g.n + 31) / 32; i += stride) done[i] = 0;
+    for (int64_t i = at; i < (n + 31) / 32; i += stride) done[i] = 0;
     if (!keep_bits)
         for (int64_t i = at; i < g.words; i += stride) bits[i] = 0;
 }
@@ -244,7 +245,8 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
         m.lowering = false;
         ulonglong2 *all = reinterpret_cast<ulonglong2 *>(s.best[from]);
         const int64_t stride = (int64_t)gridDim.x * kBlock;
-        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < (g.n + 1) / 2; i += stride)
+        const int64_t pairs = ((int64_t)g.n + 1) / 2;
+        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < pairs; i += stride)
             all[i] = make_ulonglong2(0, 0);
     }
     const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
