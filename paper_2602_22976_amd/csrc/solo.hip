@@ -78,7 +78,8 @@ struct Inst {
     const uint32_t *w;
     uint32_t seed;
     uint32_t *bits;
-    int64_t at;  // the instance's first slot in the workspace lists
+    int64_t words;  // of bits, those of a batch that no edge needs among them
+    int64_t at;     // the instance's first slot in the workspace lists
 };
 
 __device__ __forceinline__ void add_wave(unsigned long long v, unsigned long long *sum) {
@@ -542,7 +543,7 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
                        rekey};
     for (int i = tid; i < dwords; i += T) m.done[i] = 0;
     for (int i = tid; i < m.slots; i += T) m.max[i] = 0;
-    for (int i = tid; i < (I.ne + 31) >> 5; i += T) I.bits[i] = 0;
+    for (int64_t i = tid; i < I.words; i += T) I.bits[i] = 0;
     if (tid < 2) S.live[tid] = 0;
     if (tid < 4) S.sum[tid] = 0;
     __syncthreads();
@@ -726,7 +727,7 @@ template <bool kPairs>
 __global__ void __launch_bounds__(kSoloOneThreads) k_solo_one(SoloJob J) {
     extern __shared__ __align__(16) unsigned char solo_lds[];
     __shared__ SoloShared<kSoloOneThreads> S;
-    const Inst I{J.n, J.m, J.e_off, J.e_pins, J.w, J.seed, J.bits, 0};
+    const Inst I{J.n, J.m, J.e_off, J.e_pins, J.w, J.seed, J.bits, ((int64_t)J.m + 31) / 32, 0};
     solo_match<kSoloOneThreads, kPairs, false>(I, J, S, solo_lds);
 }
 
@@ -755,6 +756,7 @@ __global__ void __launch_bounds__(T, 4) k_solo_batch(SoloJob J) {
                      J.w + e0,
                      J.seeds[i],
                      J.bits + J.word_base[i],
+                     J.word_base[i + 1] - J.word_base[i],
                      e0};
         solo_match<T, false, true>(I, J, S, solo_lds);
         __syncthreads();
@@ -828,6 +830,8 @@ __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
     for (int i = tid; i < J.count; i += kOrderThreads) {
         const int c = size_class(i);
         if (c >= 0) J.order[atomicAdd(&start[c], 1)] = i;
+        if (c == -2)  // not listed: any words it has are cleared here
+            for (int64_t q = J.word_base[i]; q < J.word_base[i + 1]; ++q) J.bits[q] = 0;
     }
 }
 
