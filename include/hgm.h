@@ -132,7 +132,9 @@ typedef struct hgm_opts {
                                 where the longest instance would outlast the
                                 round kernels on the whole batch; others: the
                                 batch's kappa_total / 1024, clamped to
-                                [2^12, 2^20]), -1 = none.
+                                [2^12, 2^20]), -1 = none.  Calls that want
+                                only the matching apply the bound, at most
+                                2^30, to an instance's edges as well.
                                 hgm_match: an instance of at most 1024 edges
                                 and this many pins is matched by one
                                 workgroup (0 = 2^17, -1 = never). */

@@ -1309,7 +1309,7 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         J.pin_base = b->pin_base;
         J.word_base = b->word_base;
         J.seeds = b->seeds;
-        J.max_kappa = o.solo_max_kappa ? o.solo_max_kappa : kSoloBatchKappa;
+        J.max_size = o.solo_max_kappa ? std::min(o.solo_max_kappa, kSoloMaxSize) : kSoloBatchKappa;
         J.max_verts = sa.max_verts;
         J.ctl = s.solo;
         J.order = (int32_t *)(s.solo + kSoloJobHeader);
@@ -1322,8 +1322,9 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         HostSlot slot(true);
         int64_t listed[2] = {0, 0};  // in the solo part, left to the round kernels
         J.report = slot.get() ? (int64_t *)slot.get() : (int64_t *)(s.hot + kSub / 2);
-        const bool all = b->kappa_total <= (J.choose ? kSoloShort : J.max_kappa) &&
-                         b->n_total <= J.max_verts;
+        const bool all =
+            std::max(b->kappa_total, b->m_total) <= (J.choose ? kSoloShort : J.max_size) &&
+            b->n_total <= J.max_verts;
         if (!all) HGM_TRY(launch_zero(L, matched_bits, b->words_total));
         HGM_TRY(launch_solo_batch(L.stream, J, b->n_total, device_cus(), device_lds()));
         if (!slot.get())
@@ -1333,7 +1334,7 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         if (slot.get()) memcpy(listed, J.report, sizeof(listed));
         if (listed[1] == 0) return HGM_OK;
         in.mark_done = listed[0] > 0;
-        in.solo_max_kappa = J.max_kappa;
+        in.solo_max_size = J.max_size;
         in.solo_max_verts = J.max_verts;
         return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     }

@@ -91,7 +91,7 @@ struct BatchIn {
     int32_t *gvoff;           // out [n_total + 1] (NULL: no vertex side)
     int32_t *ebase;           // out [n_total]
     int32_t mark_done;        // the solo part has matched the instances within these
-    int64_t solo_max_kappa;   // bounds: their bits stand, their vertices are done
+    int64_t solo_max_size;    // bounds: their bits stand, their vertices are done
     int32_t solo_max_verts;   // (rounds by admission)
 };
 
@@ -252,7 +252,7 @@ struct SoloJob {
     const int64_t *v_base, *e_base, *pin_base, *word_base;
     const uint32_t *seeds;
     int32_t *order;      // [count] solo instances, longest first
-    int64_t max_kappa;
+    int64_t max_size;
     int32_t max_verts, small_verts;
     int64_t *report;     // {instances listed, instances left to the round kernels}
     int32_t choose;      // leave the solo part out where the round kernels are faster
@@ -263,6 +263,15 @@ constexpr int64_t kSoloShort = 40 * 1024, kSoloShare = 64, kSoloLess = 48 * 1024
 __host__ __device__ __forceinline__ int64_t solo_longest(int64_t kappa) {
     const int64_t share = kappa / kSoloShare - kSoloLess;
     return share > kSoloShort ? share : kSoloShort;
+}
+// An instance's size against the solo part's bound: its pins, or its edges
+// where most are empty.  The bound is at most kSoloMaxSize, so that an
+// instance's edge ids and the steps beyond its last one fit 32 bits.
+constexpr int64_t kSoloMaxSize = (int64_t)1 << 30;
+__device__ __forceinline__ int64_t solo_size(const int64_t *e_base, const int64_t *pin_base,
+                                             int i) {
+    const int64_t k = pin_base[i + 1] - pin_base[i], m = e_base[i + 1] - e_base[i];
+    return k > m ? k : m;
 }
 // LDS of the done bits of n vertices; the maxima follow when they fit.
 __host__ __device__ __forceinline__ int64_t solo_done_bytes(int64_t n) {

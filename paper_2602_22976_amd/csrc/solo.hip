@@ -764,8 +764,8 @@ __global__ void __launch_bounds__(T, 4) k_solo_batch(SoloJob J) {
 }
 
 // Lists the batch's solo instances: those too wide for a small workgroup's LDS,
-// then the others, each by falling size class (bit length of the pins), so that the
-// longest start first; and counts the instances left to the round kernels.
+// then the others, each by falling size class (bit length of solo_size), so that
+// the longest start first; and counts the instances left to the round kernels.
 // One workgroup.
 //
 // With J.choose the bound on an instance's pins is the default, and the whole
@@ -792,8 +792,9 @@ __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
     if (J.choose) {
         unsigned long long most = 0;
         for (int i = tid; i < J.count; i += kOrderThreads) {
-            const int64_t n = J.v_base[i + 1] - J.v_base[i], k = J.pin_base[i + 1] - J.pin_base[i];
-            if (k <= J.max_kappa && n <= J.max_verts && (unsigned long long)k > most)
+            const int64_t n = J.v_base[i + 1] - J.v_base[i];
+            const int64_t k = solo_size(J.e_base, J.pin_base, i);
+            if (k <= J.max_size && n <= J.max_verts && (unsigned long long)k > most)
                 most = (unsigned long long)k;
         }
         atomicMax(&longest, most);
@@ -802,9 +803,10 @@ __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
     const bool none =
         J.choose && (int64_t)longest > solo_longest(J.pin_base[J.count]);
     auto size_class = [&](int i) -> int {  // -1: left to the round kernels, -2: nothing to match
-        const int64_t n = J.v_base[i + 1] - J.v_base[i], k = J.pin_base[i + 1] - J.pin_base[i];
+        const int64_t n = J.v_base[i + 1] - J.v_base[i];
+        const int64_t k = solo_size(J.e_base, J.pin_base, i);
         if (J.e_base[i + 1] == J.e_base[i]) return -2;
-        if (none || k > J.max_kappa || n > J.max_verts) return -1;
+        if (none || k > J.max_size || n > J.max_verts) return -1;
         return (n > J.small_verts ? 0 : 64) + (k > 0 ? __clzll(k) : 63);
     };
     for (int i = tid; i < J.count; i += kOrderThreads) {

@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kBlock) k_staged_mark_solo(State s, BatchIn b)
     uint32_t *done = done_bits(s);
     for (int i = blockIdx.x; i < b.count; i += gridDim.x) {
         const int64_t v0 = b.v_base[i], v1 = b.v_base[i + 1];
-        if (v1 - v0 > b.solo_max_verts || b.pin_base[i + 1] - b.pin_base[i] > b.solo_max_kappa)
+        if (v1 - v0 > b.solo_max_verts || solo_size(b.e_base, b.pin_base, i) > b.solo_max_size)
             continue;
         for (int64_t w = (v0 >> 5) + threadIdx.x; w * 32 < v1; w += kBlock) {
             uint32_t m = 0xFFFFFFFFu;
