@@ -17,8 +17,6 @@
 // after: 100,000 pins 194 -> 145 us; a graph of 400,000 edges 236 -> 203 us;
 // vertex passes, 3.5 M pins 434 -> 383 us; per-round priorities, 4.1 M pins 525
 // -> 434 us; 30 M pins 969 -> 923 us.
-#include <atomic>
-
 #include "internal.h"
 #include "wave.h"
 
@@ -295,14 +293,9 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
 template <bool kPairs, bool kB>
 hipError_t launch_as(const Launch &L, const Graph &g, const State &s, const EndArgs &a,
                      uint32_t *bits) {
-    static std::atomic<bool> allowed{false};
-    if (!allowed.load(std::memory_order_relaxed)) {
-        const hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_end<kPairs, kB>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                  sizeof(EndShared));
-        if (rc != hipSuccess) return rc;
-        allowed.store(true, std::memory_order_relaxed);
-    }
+    static LdsGrant lds;
+    const hipError_t rc = lds.ensure(&k_end<kPairs, kB>, (int)sizeof(EndShared));
+    if (rc != hipSuccess) return rc;
     hipLaunchKernelGGL((k_end<kPairs, kB>), dim3(1), dim3(kThreads), sizeof(EndShared), L.stream, g,
                        s, a, bits);
     return hipGetLastError();

@@ -6,6 +6,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <mutex>
+
 namespace hgm {
 
 constexpr int kBlock = 256;  // threads per workgroup = edges (or vertices) per chunk
@@ -284,6 +287,32 @@ hipError_t launch_solo_batch(hipStream_t stream, SoloJob J, int64_t n_total, int
 
 constexpr int kStagedSteps = 7;  // admission steps of staged.hip
 constexpr int kStagedWave = 64;  // threads that share a live list there
+
+// Raises the dynamic LDS that a kernel may be launched with, once per device
+// and size: the limit belongs to the kernel on one device, and a thread that
+// needs less must not lower what another has raised.
+class LdsGrant {
+  public:
+    template <class K>
+    hipError_t ensure(K *kernel, int bytes) {
+        int dev = -1;
+        hipError_t rc = hipGetDevice(&dev);
+        if (rc != hipSuccess) return rc;
+        const bool kept = dev >= 0 && dev < kDevices;
+        if (kept && granted_[dev].load(std::memory_order_relaxed) >= bytes) return hipSuccess;
+        std::lock_guard<std::mutex> lk(mu_);
+        if (kept && granted_[dev].load(std::memory_order_relaxed) >= bytes) return hipSuccess;
+        rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (rc == hipSuccess && kept) granted_[dev].store(bytes, std::memory_order_relaxed);
+        return rc;
+    }
+
+  private:
+    static constexpr int kDevices = 64;
+    std::mutex mu_;
+    std::atomic<int> granted_[kDevices] = {};
+};
 
 struct Launch {
     int grid;            // persistent workgroup count for vertex / setup kernels

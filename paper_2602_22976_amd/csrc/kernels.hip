@@ -25,8 +25,6 @@
 // go to stats[r % ring], spread over kSub addresses.  best[] is
 // double-buffered by round parity so that the test of round r can clear the
 // buffer round r+1 will fill.
-#include <atomic>
-
 #include "internal.h"
 
 namespace hgm {
@@ -2249,13 +2247,9 @@ hipError_t launch_batch_setup(const Launch &L, const Graph &g, const BatchIn &b,
 hipError_t launch_solo(const Launch &L, const Graph &g, const State &s, const SoloArgs &a,
                        uint32_t *bits, int rekey, int workgroups) {
     const size_t lds = (size_t)a.lds_bytes;
-    static std::atomic<size_t> granted{0};
-    if (granted.load(std::memory_order_relaxed) < lds) {
-        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_solo),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (rc != hipSuccess) return rc;
-        granted.store(lds, std::memory_order_relaxed);
-    }
+    static LdsGrant grant;
+    const hipError_t rc = grant.ensure(&k_solo, (int)lds);
+    if (rc != hipSuccess) return rc;
     hipLaunchKernelGGL(k_solo, dim3(workgroups), dim3(kSoloThreads), lds, L.stream, g, s, a, bits,
                        rekey);
     return hipGetLastError();
@@ -2312,14 +2306,9 @@ hipError_t launch_retire(const Launch &L, const Graph &g, const State &s, int ro
             s.bin_rb < kBinMinShift || s.bin_rb > kBinMaxShift || !g.v_off)
             return hipErrorInvalidValue;
         const size_t tile = (size_t)8 << s.bin_rb;
-        static std::atomic<size_t> granted{0};
-        if (granted.load(std::memory_order_relaxed) < tile) {
-            hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_bin_max),
-                                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                (int)tile);
-            if (rc != hipSuccess) return rc;
-            granted.store(tile, std::memory_order_relaxed);
-        }
+        static LdsGrant lds;
+        const hipError_t rc = lds.ensure(&k_bin_max, (int)tile);
+        if (rc != hipSuccess) return rc;
         hipLaunchKernelGGL(k_retire_bin, grid, block, 8 * (size_t)s.bin_nb, L.stream, g, s, round,
                            kseed, rekey);
         hipLaunchKernelGGL(k_bin_max, dim3(s.bin_nb), dim3(kBinThreads), tile, L.stream, g, s,

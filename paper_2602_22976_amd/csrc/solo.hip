@@ -23,7 +23,6 @@
 // (per-round counts, priorities redrawn every round) have at most one edge per
 // thread here and a slot for every vertex.
 #include <algorithm>
-#include <atomic>
 
 #include "internal.h"
 #include "wave.h"
@@ -837,16 +836,6 @@ __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
     }
 }
 
-// Largest dynamic LDS a kernel may be launched with, raised once per size.
-template <class K>
-hipError_t allow_lds(K *kernel, std::atomic<int> &granted, int bytes) {
-    if (granted.load(std::memory_order_relaxed) >= bytes) return hipSuccess;
-    hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (rc == hipSuccess) granted.store(bytes, std::memory_order_relaxed);
-    return rc;
-}
-
 template <int T>
 constexpr int static_lds() {
     return (int)sizeof(SoloShared<T>) + 256;
@@ -868,8 +857,8 @@ int own_slots(int bytes) {
 
 template <bool kPairs>
 hipError_t launch_one(hipStream_t stream, const SoloJob &J) {
-    static std::atomic<int> granted{0};
-    hipError_t rc = allow_lds(&k_solo_one<kPairs>, granted, J.lds_bytes);
+    static LdsGrant lds;
+    const hipError_t rc = lds.ensure(&k_solo_one<kPairs>, J.lds_bytes);
     if (rc != hipSuccess) return rc;
     hipLaunchKernelGGL(k_solo_one<kPairs>, dim3(1), dim3(kSoloOneThreads), J.lds_bytes, stream, J);
     return hipGetLastError();
@@ -877,9 +866,9 @@ hipError_t launch_one(hipStream_t stream, const SoloJob &J) {
 
 template <int T, bool kSmall>
 hipError_t launch_batch(hipStream_t stream, SoloJob J, int workgroups, int lds) {
-    static std::atomic<int> granted{0};
+    static LdsGrant grant;
     J.lds_bytes = lds;
-    hipError_t rc = allow_lds(&k_solo_batch<T, kSmall>, granted, lds);
+    const hipError_t rc = grant.ensure(&k_solo_batch<T, kSmall>, lds);
     if (rc != hipSuccess) return rc;
     hipLaunchKernelGGL((k_solo_batch<T, kSmall>), dim3(workgroups), dim3(T), lds, stream, J);
     return hipGetLastError();
