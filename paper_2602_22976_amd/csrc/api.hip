@@ -1326,7 +1326,11 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
             std::max(b->kappa_total, b->m_total) <= (J.choose ? kSoloShort : J.max_size) &&
             b->n_total <= J.max_verts;
         if (!all) HGM_TRY(launch_zero(L, matched_bits, b->words_total));
-        HGM_TRY(launch_solo_batch(L.stream, J, b->n_total, device_cus(), device_lds()));
+        if (launch_solo_batch(L.stream, J, b->n_total, device_cus(), device_lds()) != hipSuccess) {
+            // The kernel that writes the slot may be enqueued: not given back before it ends.
+            (void)hipStreamSynchronize(L.stream);
+            return HGM_E_HIP;
+        }
         if (!slot.get())
             HGM_TRY(hipMemcpyAsync(listed, J.report, sizeof(listed), hipMemcpyDeviceToHost,
                                    L.stream));
