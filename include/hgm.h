@@ -24,9 +24,11 @@
  * reseed, max_rounds or validate, not HGM_VARIANT_CREW, tail_pins and
  * bin_shift not set to a positive value) admits the edges in steps of the
  * order, the highest keys first: the same matching with far fewer incidences
- * visited.  Its rounds are edge-centric and read only the edge side (the bins
- * of bin_shift, and the check that comes with them, do not run).  Every other
- * call runs its rounds over all live edges, as the paper counts them.
+ * visited.  Its rounds are edge-centric and read only the edge side; where the
+ * other rounds would use automatic bins (bin_shift), the pins of each bin are
+ * counted, and unless they are v_off's degree sums the call goes on with those
+ * rounds and returns what they return.  Every other call runs its rounds over
+ * all live edges, as the paper counts them.
  *
  * Conventions for every entry point:
  *  - All array pointers inside hgm_csr, the output bitmap and the workspace

@@ -959,8 +959,13 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
 
 
 // Rounds by admission (staged.hip): calls that want only the matching.
+// *recheck (one instance): v_off is not the transpose, in a way that the rounds
+// over all live edges may find or not: the call runs them.
 int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t seed,
-               uint32_t *bits, const BatchIn *batch, bool may_allocate) {
+               uint32_t *bits, const BatchIn *batch, bool may_allocate, bool *recheck = nullptr) {
+    // Those rounds use automatic bins, and find one overflowing, only where
+    // they expect n / 2 live pins.
+    const bool check_bins = s.bin_nb > 0 && s.bin_auto && 2 * g.kappa >= (int64_t)g.n;
     // Its own edge grid: a wave's lists stay below index m whatever the grid.
     const int64_t chunks = ((int64_t)g.m + kBlock - 1) / kBlock;
     const int64_t most = o.edge_grid               ? o.edge_grid
@@ -969,7 +974,7 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
     s.region = (int)((chunks + most - 1) / most) * kBlock;
     s.grid = (int)((chunks * kBlock + s.region - 1) / s.region);
     if (batch) HGM_TRY(launch_batch_setup(L, g, *batch, s));
-    HGM_TRY(launch_staged_setup(L, g, s, seed, bits, batch));
+    HGM_TRY(launch_staged_setup(L, g, s, seed, bits, batch, check_bins));
     // Round 0 admits up to the first threshold with at least kStagedFirstEdges
     // edges above it.
     const double part[kStagedSteps - 1] = {1.0 / 2700, 1.0 / 250, 1.0 / 33, 0.1, 0.2, 0.5};
@@ -980,9 +985,13 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
     HostSlot slot(may_allocate);
     unsigned long long copy[kEndHeader] = {0};
     unsigned long long *report = (unsigned long long *)slot.get();
-    if (!report) report = s.hot + kSub / 2;
+    if (report)
+        memset(report, 0, sizeof(copy));
+    else
+        report = s.hot + kSub / 2;
     EndArgs end = end_args(s, report);
     for (int k = 0; k < 2; ++k) end.counts[k] = s.rec_c[k];
+    end.check_bins = check_bins ? 1 : 0;
     end.lists = s.grid * (kBlock / kStagedWave);
     end.stride = s.region / (kBlock / kStagedWave);
     HGM_TRY(launch_staged_join(L, g, s, 0, first, seed));
@@ -1011,6 +1020,11 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
             HGM_TRY(hipMemcpyAsync(copy, report, sizeof(copy), hipMemcpyDeviceToHost, L.stream));
         HGM_TRY(hipStreamSynchronize(L.stream));
         if (slot.get()) memcpy(copy, report, sizeof(copy));
+        if (copy[kEndOverflow] == 2) return HGM_E_CSR;
+        if (copy[kEndOverflow]) {
+            *recheck = true;
+            return HGM_OK;
+        }
         if (copy[kEndFinished]) return HGM_OK;
         plan = more;
     }
@@ -1155,8 +1169,11 @@ int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *w
     bool ran = false;
     rc = match_solo(g, o, lay, s, L.stream, seed, matched_bits, stats, may_allocate, &ran);
     if (rc != HGM_OK || ran) return rc;
-    if (g.m > 0 && staged_call(o, stats))
-        return run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate);
+    if (g.m > 0 && staged_call(o, stats)) {
+        bool recheck = false;
+        rc = run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate, &recheck);
+        if (rc != HGM_OK || !recheck) return rc;
+    }
     return run_rounds(g, o, lay, s, L, seed, matched_bits, stats, nullptr, nullptr, may_allocate);
 }
 

@@ -80,6 +80,15 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
             }
         }
     }
+    if (a.check_bins) {
+        const int found = *s.piece_count;
+        for (int j = tid; found == kBinsCompare && j < s.bin_nb; j += kThreads) {
+            const int64_t v0 = (int64_t)j << s.bin_rb, v1 = v0 + ((int64_t)1 << s.bin_rb);
+            const int64_t sum = (int64_t)g.v_off[v1 < g.n ? v1 : g.n] - g.v_off[v0];
+            if (sum != (int64_t)s.bin_cursor[j]) a.report[kEndOverflow] = 1;
+        }
+        if (found == kBinsBadOffsets && tid == 0) a.report[kEndOverflow] = 2;
+    }
     const unsigned long long live = wave_total(s.stats[a.round % s.ring].live[lane]);
     const bool limit = a.max_rounds > 0 && a.round >= a.max_rounds;
     if (live == 0 || live > (unsigned long long)kEdges || limit) {

@@ -357,8 +357,11 @@ constexpr int kClearNone = 0, kClearAll = 1, kClearPins = 2;
 hipError_t launch_test(const Launch &L, const Graph &g, const State &s, int round, int clear,
                        uint32_t *bits, uint32_t kseed);
 // Rounds by admission (staged.hip).  `first`: the admission step of round 0.
+// check_bins: the pins of every bin are counted for k_end (one instance with
+// automatic bins); what that finds of v_off is left in piece_count.
+constexpr int kBinsUnused = 0, kBinsCompare = 1, kBinsBadOffsets = 2;
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
-                               uint32_t *bits, const BatchIn *batch);
+                               uint32_t *bits, const BatchIn *batch, bool check_bins);
 hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, int round,
                               int first, uint32_t seed);
 hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, int round,
@@ -369,7 +372,8 @@ hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, i
 // at slot w * stride with counts[parity][w] edges.
 constexpr int kEndFinished = 0;  // words of the report: 1 when no live edge is left
 constexpr int kEndRounds = 1;    // rounds run (with edges left: whose test is to come)
-constexpr int kEndOverflow = 2;  // set when a bin overflowed in one of the rounds
+constexpr int kEndOverflow = 2;  // 1 when a bin overflowed in one of the rounds, or when its
+                                 // pins are not its degree sum (check_bins); 2: bad offsets
 constexpr int kEndHeader = 8;    // then 5 words a round: live edges and pins, matched
                                  // edges, their weight and pins
 struct EndArgs {
@@ -382,6 +386,7 @@ struct EndArgs {
     int32_t counting;  // report the rounds' counts (rounds beyond the `rows` that fit:
     int32_t rows;      // rec_key[round & 1], one word each: live edges, live pins, matched
                        // edges and their pins in 16 bits each; rec_key[other]: the weight)
+    int32_t check_bins;  // compare the counts of launch_staged_setup with v_off
     unsigned long long *report;  // device or pinned host memory, header cleared by the caller
 };
 hipError_t launch_end(const Launch &L, const Graph &g, const State &s, const EndArgs &a,

@@ -87,12 +87,24 @@ __device__ __forceinline__ int rank_of(const uint64_t *keys, int i, int part) {
     return rank;
 }
 
+// What a workgroup of the setup has seen of v_off (check_bins): the degrees of
+// its hot vertices and whether an offset decreases or lies outside [0, kappa].
+struct VOffPart {
+    unsigned long long hot, bad;
+};
+__device__ __forceinline__ VOffPart *v_off_parts(const State &s) {
+    return reinterpret_cast<VOffPart *>(s.bin_key);
+}
+
 // Clears the state; workgroup 0 clears the counters and draws the thresholds.
 template <bool kB>
 __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s, uint32_t seed,
-                                                                uint32_t *bits, int keep_bits) {
+                                                                uint32_t *bits, int keep_bits,
+                                                                int check_bins) {
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
+        for (int j = tid; check_bins && j < s.bin_nb; j += kSetupThreads) s.bin_cursor[j] = 0;
+        if (tid < kEndHeader) s.hot[kSub / 2 + tid] = 0;  // the report, without a host slot
         __shared__ uint64_t top[kSampleGroups], one[kSampleGroups];
         constexpr int kOwn = kSamplesPerGroup / kSetupParts;
         const int i = tid / kSetupParts, part = tid % kSetupParts;
@@ -137,6 +149,95 @@ __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s
     for (int64_t i = at; i < (n + 31) / 32; i += stride) done[i] = 0;
     if (!keep_bits)
         for (int64_t i = at; i < g.words; i += stride) bits[i] = 0;
+    if (check_bins) {
+        __shared__ unsigned long long hot_sum;
+        if (tid == 0) hot_sum = 0;
+        __syncthreads();
+        unsigned long long hot = 0;
+        bool bad = false;
+        for (int64_t i = at; i < n; i += stride) {
+            const int lo = g.v_off[i], hi = g.v_off[i + 1], deg = hi - lo;
+            bad |= lo < 0 || hi < lo || hi > g.kappa;
+            if (deg >= s.hot_degree) hot += (unsigned long long)deg;
+        }
+        if (hot) atomicAdd(&hot_sum, hot);
+        const bool any = __syncthreads_or(bad);
+        if (tid == 0) v_off_parts(s)[blockIdx.x - 1] = {hot_sum, any ? 1ull : 0ull};
+    }
+}
+
+// The check that comes with automatic bins, for calls whose rounds do not use
+// them: the rounds over all live edges find a v_off that is not the transpose
+// when a bin holds more pins than its vertices' degrees add up to.  No bin can
+// where every bin's degree sum equals the pins it really has, which this
+// counts and k_end compares; where they differ the host runs those rounds and
+// returns what they return.  Bins run only where the degrees send round 0 to
+// the vertex form, so the pins are left alone elsewhere.
+//
+// Bound by streaming the pins (4.4 TB/s): hub-stress, 36M pins, 465 -> 506 us;
+// power-law, 30M, the edge form, 341 -> 347 for the pass over v_off.
+constexpr int kCheckThreads = 256, kCheckGrid = 1024;
+__global__ void __launch_bounds__(kCheckThreads) k_staged_check(Graph g, State s, int parts) {
+    __shared__ uint32_t count[kCheckThreads / kWave][kBinMaxBins];
+    __shared__ unsigned long long hot_sum;
+    const int tid = threadIdx.x;
+    if (tid == 0) hot_sum = 0;
+    __syncthreads();
+    unsigned long long hot = 0;
+    bool bad = false;
+    for (int i = tid; i < parts; i += kCheckThreads) {
+        const VOffPart p = v_off_parts(s)[i];
+        hot += p.hot;
+        bad |= p.bad != 0;
+    }
+    if (hot) atomicAdd(&hot_sum, hot);
+    const bool any = __syncthreads_or(bad);
+    const int verdict = 2 * hot_sum >= (unsigned long long)g.kappa ? kBinsUnused
+                        : any                                      ? kBinsBadOffsets
+                                                                   : kBinsCompare;
+    if (blockIdx.x == 0 && tid == 0) *s.piece_count = verdict;
+    if (verdict != kBinsCompare) return;
+    uint32_t *mine = count[tid / kWave];
+    for (int j = lane_id(); j < s.bin_nb; j += kWave) mine[j] = 0;
+    wave_fence();
+    const uint32_t last = (uint32_t)s.bin_nb - 1;
+    auto add = [&](int v) { atomicAdd(&mine[min((uint32_t)v >> s.bin_rb, last)], 1u); };
+    // 16-byte loads from the first aligned pin on.
+    const int64_t head = min((int64_t)((16 - ((uintptr_t)g.e_pins & 15)) / 4 % 4), g.kappa);
+    const int4 *quads = reinterpret_cast<const int4 *>(g.e_pins + head);
+    const int64_t nq = (g.kappa - head) / 4, tail = head + 4 * nq;
+    constexpr int kU = 4;
+    const int64_t stride = (int64_t)gridDim.x * kCheckThreads;
+    int64_t i = (int64_t)blockIdx.x * kCheckThreads + tid;
+    for (; i + (kU - 1) * stride < nq; i += kU * stride) {
+        int4 q[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) q[u] = quads[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            add(q[u].x);
+            add(q[u].y);
+            add(q[u].z);
+            add(q[u].w);
+        }
+    }
+    for (; i < nq; i += stride) {
+        const int4 q = quads[i];
+        add(q.x);
+        add(q.y);
+        add(q.z);
+        add(q.w);
+    }
+    if (blockIdx.x == 0) {
+        if (tid < head) add(g.e_pins[tid]);
+        if (tail + tid < g.kappa) add(g.e_pins[tail + tid]);
+    }
+    __syncthreads();
+    for (int j = tid; j < s.bin_nb; j += kCheckThreads) {
+        uint32_t c = 0;
+        for (int w = 0; w < kCheckThreads / kWave; ++w) c += count[w][j];
+        if (c) atomicAdd(&s.bin_cursor[j], c);
+    }
 }
 
 // Marks every vertex of the instances the solo part has matched.
@@ -309,13 +410,18 @@ __global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int ro
 }  // namespace
 
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
-                               uint32_t *bits, const BatchIn *batch) {
+                               uint32_t *bits, const BatchIn *batch, bool check_bins) {
     const dim3 grid(L.grid / 4 + 2), block(kSetupThreads);
-    const int keep = batch && batch->mark_done;
+    const int keep = batch && batch->mark_done, check = check_bins ? 1 : 0;
     if (g.vbase)
-        hipLaunchKernelGGL(k_staged_setup<true>, grid, block, 0, L.stream, g, s, seed, bits, keep);
+        hipLaunchKernelGGL(k_staged_setup<true>, grid, block, 0, L.stream, g, s, seed, bits, keep,
+                           0);
     else
-        hipLaunchKernelGGL(k_staged_setup<false>, grid, block, 0, L.stream, g, s, seed, bits, keep);
+        hipLaunchKernelGGL(k_staged_setup<false>, grid, block, 0, L.stream, g, s, seed, bits, keep,
+                           check);
+    if (check)
+        hipLaunchKernelGGL(k_staged_check, dim3(kCheckGrid), dim3(kCheckThreads), 0, L.stream, g, s,
+                           (int)grid.x - 1);
     if (keep)
         hipLaunchKernelGGL(k_staged_mark_solo, dim3(L.grid), dim3(kBlock), 0, L.stream, s, *batch);
     return hipGetLastError();
