@@ -967,12 +967,18 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
     // they expect n / 2 live pins.
     const bool check_bins = s.bin_nb > 0 && s.bin_auto && 2 * g.kappa >= (int64_t)g.n;
     // Its own edge grid: a wave's lists stay below index m whatever the grid.
-    const int64_t chunks = ((int64_t)g.m + kBlock - 1) / kBlock;
+    // Long edges that leave the grid idle: a wave's range is shorter than its
+    // 64 lanes, down to kStagedWavePins pins (a multiple of 4 edges, whose
+    // step bytes it reads at once).
     const int64_t most = o.edge_grid               ? o.edge_grid
                          : g.m > kStagedLargeEdges ? kStagedGridLarge
                                                    : kStagedGrid;
-    s.region = (int)((chunks + most - 1) / most) * kBlock;
-    s.grid = (int)((chunks * kBlock + s.region - 1) / s.region);
+    int64_t unit = kBlock;
+    if ((int64_t)g.m < most * kBlock && g.kappa > kStagedWavePins / kStagedWave * g.m)
+        unit = kBlock / kStagedWave * std::max<int64_t>(4, kStagedWavePins * g.m / g.kappa / 4 * 4);
+    const int64_t chunks = ((int64_t)g.m + unit - 1) / unit;
+    s.region = (int)((chunks + most - 1) / most * unit);
+    s.grid = (int)((chunks * unit + s.region - 1) / s.region);
     if (batch) HGM_TRY(launch_batch_setup(L, g, *batch, s));
     HGM_TRY(launch_staged_setup(L, g, s, seed, bits, batch, check_bins));
     // Round 0 admits up to the first threshold with at least kStagedFirstEdges

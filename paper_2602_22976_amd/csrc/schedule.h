@@ -63,6 +63,11 @@ constexpr double kEndingEdges = 1400.0;
 // all take longer.
 constexpr int kStagedGrid = 512, kStagedGridLarge = 1024;
 constexpr int64_t kStagedLargeEdges = (int64_t)1 << 23;
+// Rounds by admission, where the mean edge is longer than 8 pins: a wave's range
+// shrinks to the pins that it keeps in registers (edges of 258 pins, 2,000 of
+// them: 1,023 us with 64 edges a wave, 354 with 4,096 pins, 255 with 512; the
+// rounds over all edges 1,115).
+constexpr int64_t kStagedWavePins = 512;
 // Rounds by admission: round 0 starts with the first step expected to admit
 // at least this many edges (fewer leave the grid idle for a whole round).
 constexpr int64_t kStagedFirstEdges = 1024;

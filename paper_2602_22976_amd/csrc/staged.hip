@@ -270,7 +270,8 @@ __device__ __forceinline__ WaveRange wave_range(const State &s) {
     return r;
 }
 
-// Live edges of round r (its join is finished; every lane gets the sum).
+// Live edges of round r, long ones by their weight (its join is finished; every
+// lane gets the sum).
 __device__ __forceinline__ int64_t live_edges(const State &s, int r) {
     unsigned long long v = s.stats[r % s.ring].live[lane_id()];
     static_assert(kSub == kWave, "one counter per lane");
@@ -283,8 +284,81 @@ __device__ __forceinline__ int64_t live_edges(const State &s, int r) {
 // many live edges by one pass over the array, one with few by a store at each
 // of its pins; either in the join of round r + 1.  Scattered stores run at
 // about 30 G/s.
+// A long edge adds kLongWeight times its pins to the round's count of live
+// edges: a workgroup lowers 2,048 pins in the time that the pass takes for
+// about 500 times as many vertices.  (The last rounds' workgroup, which also
+// reads the count, leaves such rounds to the grid.)
+constexpr unsigned long long kLongWeight = 8;
 __device__ __forceinline__ bool clears_by_pass(const Graph &g, int64_t live) {
     return live * 64 >= g.n;
+}
+
+// Edges of more pins than a window are left by the waves that meet them to the
+// whole workgroup, which takes them one after the other when its waves are
+// done (those that find no room stay with their wave).  Bound by latency: two
+// dependent reads a step, 2,048 pins in about 2.3 us; one wave needs 10 to 18,
+// and such an edge is alone in its chunk.  64 edges of 100,000 pins: 145 ms by
+// one wave each 64, 13.3 by short ranges, 6.6 so (the rounds over all edges 55);
+// 200,000 small edges and 20 of 300,000 pins: 4.6 -> 1.4 ms (13.1); sixteen
+// instances of 20,000 and one of 100,000: 2.7 -> 0.66 ms (0.60).
+constexpr int kLong = kWindow, kLongMax = 16;  // kept of each wave
+struct LongEdge {
+    uint64_t key;
+    int e, base, len, vb;
+    bool listed;  // in the last round's list
+};
+struct LongEdges {
+    int count[kWaves];
+    int kept[kWaves];  // entries of each wave's list (join)
+    LongEdge edge[kWaves][kLongMax];
+    // By each wave, its own: no barrier.
+    __device__ __forceinline__ void reset(int wave) {
+        if (lane_id() == 0) count[wave] = 0;
+        wave_fence();
+    }
+    __device__ __forceinline__ bool take(int wave, const LongEdge &x) {
+        if (x.len <= kLong) return false;
+        const int i = atomicAdd(&count[wave], 1);
+        if (i >= kLongMax) return false;
+        edge[wave][i] = x;
+        return true;
+    }
+    // After a barrier.
+    __device__ __forceinline__ bool any() const {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) n |= count[w];
+        return n != 0;
+    }
+    __device__ __forceinline__ int taken(int wave) const {
+        return count[wave] < kLongMax ? count[wave] : kLongMax;
+    }
+};
+
+// The workgroup at the pins of one long edge: look(pin) of kLongU pins a thread
+// at a time, then use(pin, looked); whether use held somewhere.  `every`: at
+// all pins, else until it holds.  All threads call it and get the answer.
+constexpr int kLongU = 8;
+template <class Look, class Use>
+__device__ __forceinline__ bool long_pins(const int32_t *e_pins, const LongEdge &x, bool every,
+                                          Look look, Use use) {
+    bool any = false;
+    for (int64_t t0 = 0; t0 < x.len; t0 += kLongU * kBlock) {
+        int v[kLongU];
+        decltype(look(0)) l[kLongU];
+#pragma unroll
+        for (int u = 0; u < kLongU; ++u) {
+            const int64_t t = t0 + u * kBlock + threadIdx.x;
+            v[u] = e_pins[x.base + (t < x.len ? t : 0)] + x.vb;
+        }
+#pragma unroll
+        for (int u = 0; u < kLongU; ++u) l[u] = look(v[u]);
+#pragma unroll
+        for (int u = 0; u < kLongU; ++u)
+            if (t0 + u * kBlock + threadIdx.x < x.len) any |= use(v[u], l[u]);
+        if (!every && __syncthreads_or(any)) return true;
+    }
+    return every ? __syncthreads_or(any) : false;
 }
 
 // The grid's side of join_wave.
@@ -296,6 +370,7 @@ struct GridJoin {
     uint64_t *best, *old;
     uint32_t seed;
     bool lowering;
+    LongEdges *longs;
     __device__ __forceinline__ uint32_t done_word(int v) const { return done[v >> 5]; }
     __device__ __forceinline__ void lower(int v) const {
         if (lowering) old[v] = 0;
@@ -325,6 +400,10 @@ struct GridJoin {
     __device__ __forceinline__ uint64_t exact_sort(int e, uint32_t w) const {
         return (uint64_t)w << 32 | priority_hash(seed, (uint32_t)e);
     }
+    __device__ __forceinline__ bool defer(int e, int base, int len, int vb, uint64_t key,
+                                          bool listed) const {
+        return longs->take(threadIdx.x / kWave, {key, e, base, len, vb, listed});
+    }
     __device__ __forceinline__ void entered(int) const {}
 };
 
@@ -338,10 +417,13 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
                                                         uint32_t seed) {
     __shared__ WaveScratch scratch[kWaves];
     __shared__ int queue[kWaves][cand_size(kFill)];
+    __shared__ LongEdges longs;
     const int wid = threadIdx.x / kWave;
+    if (!kPairs) longs.reset(wid);
     const WaveRange range = wave_range(s);
     const int to = round & 1, from = to ^ 1;
-    GridJoin<kPairs, kB> m{g, s, done_bits(s), s.best[to], s.best[from], seed, round > 0};
+    GridJoin<kPairs, kB> m{g, s, done_bits(s), s.best[to], s.best[from], seed, round > 0,
+                          &longs};
     if (round > 0 && clears_by_pass(g, live_edges(s, round - 1))) {
         m.lowering = false;
         ulonglong2 *all = reinterpret_cast<ulonglong2 *>(s.best[from]);
@@ -351,11 +433,48 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
             all[i] = make_ulonglong2(0, 0);
     }
     const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
-    const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
+    int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
         m, scratch[wid], queue[wid], g.e_pins, lists(s, from), lists(s, to), range.lo, end,
         round > 0 ? s.rec_c[from][range.wave] : 0, round == 0,
         first + round == (first < kSweep ? kSweep : first + 1), first + round, step_bytes(s),
         reinterpret_cast<const uint64_t *>(s.hot));
+    if constexpr (!kPairs) {
+        if (lane_id() == 0) longs.kept[wid] = kept;
+        __syncthreads();
+        if (longs.any()) {
+            const WaveLists out = lists(s, to);
+            for (int w = 0; w < kWaves; ++w)
+                for (int i = 0; i < longs.taken(w); ++i) {
+                    const LongEdge x = longs.edge[w][i];
+                    const bool every = x.listed && m.lowering;
+                    const bool dead = long_pins(
+                        g.e_pins, x, every, [&](int v) { return m.done_word(v); },
+                        [&](int v, uint32_t word) {
+                            if (every) m.lower(v);
+                            return (bool)((word >> (v & 31)) & 1u);
+                        });
+                    if (dead) continue;
+                    if (threadIdx.x == 0) {
+                        const int64_t at =
+                            range.lo + (int64_t)w * range.per + longs.kept[w]++;  // wave 0's range
+                        out.list[at] = x.e;
+                        out.base[at] = x.base;
+                        out.len[at] = x.len;
+                        if constexpr (kB) out.vb[at] = x.vb;
+                        out.key[at] = x.key;
+                        atomicAdd(&s.stats[round % s.ring].live[w], kLongWeight * x.len);
+                    }
+                    long_pins(
+                        g.e_pins, x, true, [&](int v) { return m.peek(v); },
+                        [&](int v, uint64_t now) {
+                            m.raise(v, x.key, now);
+                            return false;
+                        });
+                }
+            __syncthreads();
+            kept = longs.kept[wid];
+        }
+    }
     if (lane_id() == 0) {
         s.rec_c[to][range.wave] = kept;
         if (kept > 0)
@@ -367,8 +486,10 @@ template <bool kPairs, bool kB>
 __global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int round,
                                                         uint32_t *bits) {
     __shared__ WaveScratch scratch[kWaves];
-    const int lane = lane_id();
-    WaveScratch &W = scratch[threadIdx.x / kWave];
+    __shared__ LongEdges longs;
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    if (!kPairs) longs.reset(wid);
+    WaveScratch &W = scratch[wid];
     const WaveRange range = wave_range(s);
     const int k = round & 1;
     if (blockIdx.x == 0 && threadIdx.x < kSub)
@@ -376,11 +497,17 @@ __global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int ro
     const int n = s.rec_c[k][range.wave];
     const uint64_t *best = s.best[k];
     uint32_t *done = done_bits(s);
+    auto win = [&](int e) {
+        const int bit = kB ? e + g.bitoff[e] : e;
+        atomicOr(&bits[bit >> 5], 1u << (bit & 31));
+    };
+    auto mark = [&](int v) { atomicOr(&done[v >> 5], 1u << (v & 31)); };
     for (int i0 = 0; i0 < n; i0 += kWave) {
         const int i = i0 + lane;
+        bool on = i < n;
         int e = 0, base = 0, len = 0, vb = 0;
         uint64_t key = 0;
-        if (i < n) {
+        if (on) {
             const int64_t at = range.lo + i;
             e = s.list[k][at];
             if constexpr (kPairs) {
@@ -394,16 +521,36 @@ __global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int ro
             key = s.rec_key[k][at];
         }
         flat_edges<kPairs, kB, kKeepPins>(
-            W, g.e_pins, base, len, key, [&](int v) { return best[v]; },
+            W, g.e_pins, base, len, key, false,
+            [&] {
+                if (!longs.take(wid, {key, e, base, len, vb, true})) return false;
+                on = false;
+                return true;
+            },
+            [&](int v) { return best[v]; },
             [](int, uint64_t key, uint64_t b) { return b != key; },
             [&](bool lost) {
-                if (i < n && !lost) {
-                    const int bit = kB ? e + g.bitoff[e] : e;
-                    atomicOr(&bits[bit >> 5], 1u << (bit & 31));
-                }
+                if (on && !lost) win(e);
                 return key;
             },
-            NoRead(), [&](int v, uint64_t, int) { atomicOr(&done[v >> 5], 1u << (v & 31)); }, vb);
+            NoRead(), [&](int v, uint64_t, int) { mark(v); }, vb);
+    }
+    if constexpr (!kPairs) {
+        __syncthreads();
+        if (!longs.any()) return;
+        for (int w = 0; w < kWaves; ++w)
+            for (int i = 0; i < longs.taken(w); ++i) {
+                const LongEdge x = longs.edge[w][i];
+                if (long_pins(
+                        g.e_pins, x, false, [&](int v) { return best[v]; },
+                        [&](int, uint64_t b) { return b != x.key; }))
+                    continue;
+                if (threadIdx.x == 0) win(x.e);
+                long_pins(g.e_pins, x, true, NoRead(), [&](int v, int) {
+                    mark(v);
+                    return false;
+                });
+            }
     }
 }
 

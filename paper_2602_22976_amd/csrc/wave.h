@@ -87,16 +87,20 @@ __device__ __forceinline__ int flat_edge(const WaveScratch &W, int blk, int &bef
 // For the wave's 64 edges (lane: n pins from base): an edge is hit when
 // check(pin, key, look(pin)) holds at one of its pins; key = middle(hit) is
 // called once per lane; then act(pin, key, peek(pin)) at every pin of the
-// edges not hit.  look and peek hold the memory reads: those of all the
-// chunk's pins are issued before any is used.  kBase: vb is added to the
-// edge's pins.  kKeep blocks of 64 pins stay in registers from the check to
+// edges not hit.  `every` (uniform): check is called at every pin; else an
+// edge longer than a window may be left once it is hit.  defer(): whether the
+// caller takes the lane's edge (asked where a chunk does not fit the
+// registers).  look and peek hold the memory reads: those of all the chunk's
+// pins are issued before any is used.  kBase: vb is added to the edge's pins.
+// kKeep blocks of 64 pins stay in registers from the check to
 // the act (0: none; their ids are read again).  All lanes of the wave call it
 // (n = 0: no edge).
-template <bool kPairs, bool kBase, int kKeep, class Look, class Check, class Middle, class Peek,
-          class Act>
+template <bool kPairs, bool kBase, int kKeep, class Defer, class Look, class Check, class Middle,
+          class Peek, class Act>
 __device__ __forceinline__ void flat_edges(WaveScratch &W, const int32_t *e_pins, int base, int n,
-                                           uint64_t key, Look look, Check check, Middle middle,
-                                           Peek peek, Act act, int vb = 0) {
+                                           uint64_t key, bool every, Defer defer, Look look,
+                                           Check check, Middle middle, Peek peek, Act act,
+                                           int vb = 0) {
     const int lane = lane_id();
     if constexpr (kPairs) {
         int2 p = make_int2(0, 0);
@@ -165,15 +169,17 @@ __device__ __forceinline__ void flat_edges(WaveScratch &W, const int32_t *e_pins
             if (on >> b & 1) act(v[b], W.key[j[b]], x[b]);
         return;
     }
+    if (defer()) n = 0;
     // Window after window, each taking as many pins of every unfinished edge
-    // as fit.  use(pin, key, get(pin)): whether the pin hits its edge.
-    auto windows = [&](int len, auto get, auto use) {
+    // as fit.  use(pin, key, get(pin)): whether the pin hits its edge, which is
+    // then finished unless every pin is asked for.
+    auto windows = [&](int len, bool every, auto get, auto use) {
         bool hit = false;
         for (int at = 0;;) {
-            const unsigned long long open = __ballot(at < len);
+            const unsigned long long open = __ballot(at < len && (every || !hit));
             if (!open) return hit;
             const int take = kWindow / __popcll(open);
-            const int now = len - at < take ? len - at : take;
+            const int left = every || !hit ? len - at : 0, now = left < take ? left : take;
             int total;
             const int ord = flatten(W, base + at, now, &total);
             if (now > 0) {
@@ -208,9 +214,9 @@ __device__ __forceinline__ void flat_edges(WaveScratch &W, const int32_t *e_pins
             wave_fence();
         }
     };
-    const bool hit = windows(n, look, check);
+    const bool hit = windows(n, every, look, check);
     key = middle(hit);
-    windows(hit ? 0 : n, peek, [&](int v, uint64_t k, decltype(peek(0)) x) {
+    windows(hit ? 0 : n, true, peek, [&](int v, uint64_t k, decltype(peek(0)) x) {
         act(v, k, x);
         return false;
     });
@@ -248,7 +254,8 @@ struct WaveLists {
 // M: done_word(v), lower(v), peek(v), raise(v, key, peeked), key(e), again(e,
 // key) (the key of a listed edge this round), place(e, base, len, vb), sort(e,
 // w, k) / exact_sort(e, w) (weight or key that the thresholds are compared
-// with), entered(len).
+// with), defer(e, base, len, vb, key, listed) (true: the edge is left to the
+// caller), entered(len).
 // kFill: chunks of 64 edges looked at in one step, at most (a multiple of 4).
 constexpr uint8_t kNever = 255;  // step of an edge that was dropped
 constexpr int cand_size(int fill) { return (fill + 1) * kWave; }
@@ -434,7 +441,13 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
             wave_fence();
         }
         flat_edges<kPairs, kB, kKeep>(
-            W, e_pins, base, len, key, [&](int v) { return m.done_word(v); },
+            W, e_pins, base, len, key, listing && m.lowering,
+            [&] {
+                if (!m.defer(e, base, len, vb, key, listing)) return false;
+                on = false;
+                return true;
+            },
+            [&](int v) { return m.done_word(v); },
             [&](int v, uint64_t, uint32_t word) {
                 if (listing) m.lower(v);
                 return (bool)((word >> (v & 31)) & 1u);
