@@ -139,7 +139,10 @@ typedef struct hgm_opts {
                                 2^30, to an instance's edges as well.
                                 hgm_match: an instance of at most 1024 edges
                                 and this many pins is matched by one
-                                workgroup (0 = 2^17, -1 = never). */
+                                workgroup (-1 = never; 0 = 2^17 with counts
+                                or per-round priorities, else 2^14 where
+                                every vertex has a slot in LDS and 8192 or
+                                4096 where they share them). */
     /* Schedule (any value gives the same result; hgm_tune picks them per
      * shape).  0 = library default for each. */
     int32_t edge_grid;       /* workgroups of the edge-centric kernels, each

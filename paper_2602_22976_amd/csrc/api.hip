@@ -1075,13 +1075,19 @@ int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
                hipStream_t stream, uint32_t seed, uint32_t *bits, hgm_stats *stats,
                bool may_allocate, bool *ran) {
     *ran = false;
-    const int64_t bound = o.solo_max_kappa ? o.solo_max_kappa : kSoloOneKappa;
+    const bool exact = stats || o.reseed;
+    const int lds = device_lds();
+    const int own = solo_one_max_verts(lds, true);  // vertices with a slot each
+    const int64_t bound = o.solo_max_kappa            ? o.solo_max_kappa
+                          : exact                     ? kSoloOneExact
+                          : g.n <= own                ? kSoloOneKappa
+                          : g.n <= kSoloOneManyVerts ? kSoloOneShared
+                                                      : kSoloOneSharedMany;
     if (g.m == 0 || g.m > kSoloOneThreads || g.kappa > bound || o.variant == HGM_VARIANT_CREW ||
         o.validate || o.max_rounds > 0 || o.tail_pins > 0 || o.bin_shift > 0 ||
         (stats && stats->timing))
         return HGM_OK;
-    const int lds = device_lds();
-    if (g.n > solo_one_max_verts(lds, stats || o.reseed)) return HGM_OK;
+    if (g.n > (exact ? own : solo_one_max_verts(lds, false))) return HGM_OK;
     SoloJob J;
     memset(&J, 0, sizeof(J));
     J.n = g.n;
@@ -1091,7 +1097,7 @@ int match_solo(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     J.w = g.w;
     J.seed = seed;
     J.bits = bits;
-    J.exact = stats || o.reseed ? 1 : 0;
+    J.exact = exact ? 1 : 0;
     J.reseed = o.reseed ? 1 : 0;
     J.ctl = (unsigned long long *)s.stats;
     J.rows = J.ctl + kSoloJobHeader;

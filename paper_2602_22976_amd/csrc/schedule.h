@@ -39,10 +39,20 @@ inline int64_t solo_auto_bound(int64_t kappa_total) {
     return b < kSoloAutoMin ? kSoloAutoMin : b > kSoloAutoMax ? kSoloAutoMax : b;
 }
 // Calls that want only the matching: the solo part takes instances of a batch
-// up to kSoloBatchKappa pins, and hgm_match runs an instance of at most 1,024
-// edges and kSoloOneKappa pins in one workgroup (tiny: 50 -> 28 us).
+// up to kSoloBatchKappa pins.
 constexpr int64_t kSoloBatchKappa = (int64_t)1 << 20;
-constexpr int64_t kSoloOneKappa = (int64_t)1 << 17;
+// hgm_match runs an instance of at most 1,024 edges in one workgroup up to these
+// many pins.  One workgroup / the grid, us: exact rounds (a slot for every
+// vertex) 199 / 409 at 1,000 edges of 131 pins, 525 / 737 at 100 of 1,310.
+// Matching only: 28 / 50 for 311 edges; 8,000 pins 40 / 74; 16,000 pins of
+// 1,000 edges 82 / 131 and of 100 edges 141 / 119; 32,000 159 / 144; 131,000
+// 187 / 140.  Beyond the vertices that have a slot each, 8,192 pins, all that
+// the registers hold: 50 / 77 with 50,000 vertices, but 141 / 127 at 16,000
+// pins and 3,900 / 123 at 65,000 with 500,000 vertices, whose done bits leave
+// fewer slots: there 45 / 68 at 4,000 pins, 161 / 73 at 8,100.
+constexpr int64_t kSoloOneExact = (int64_t)1 << 17, kSoloOneKappa = (int64_t)1 << 14;
+constexpr int64_t kSoloOneShared = 8192, kSoloOneSharedMany = 4096;
+constexpr int kSoloOneManyVerts = 1 << 18;
 // An edge-centric round 0 of one instance samples the pins for hubs from this
 // many pins, in the setup kernel (Zipf popularity: a call of 4.1 M pins 470 ->
 // 380 us; a hub in a quarter of the edges, 4.8 M: 600 -> 480; none, 1.1 M: 3 us
