@@ -283,11 +283,10 @@ __device__ __forceinline__ int64_t live_edges(const State &s, int r) {
 // How best[r & 1] goes back to zero before round r + 2 raises it: a round with
 // many live edges by one pass over the array, one with few by a store at each
 // of its pins; either in the join of round r + 1.  Scattered stores run at
-// about 30 G/s.
-// A long edge adds kLongWeight times its pins to the round's count of live
-// edges: a workgroup lowers 2,048 pins in the time that the pass takes for
-// about 500 times as many vertices.  (The last rounds' workgroup, which also
-// reads the count, leaves such rounds to the grid.)
+// about 30 G/s.  A long edge adds kLongWeight times its pins to the round's
+// count of live edges, instead of 1: a workgroup lowers 2,048 pins in the time
+// that the pass takes for about 500 times as many vertices.  (The last rounds'
+// workgroup, which also reads the count, leaves such rounds to the grid.)
 constexpr unsigned long long kLongWeight = 8;
 __device__ __forceinline__ bool clears_by_pass(const Graph &g, int64_t live) {
     return live * 64 >= g.n;
@@ -433,11 +432,17 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
             all[i] = make_ulonglong2(0, 0);
     }
     const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
-    int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
+    const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
         m, scratch[wid], queue[wid], g.e_pins, lists(s, from), lists(s, to), range.lo, end,
         round > 0 ? s.rec_c[from][range.wave] : 0, round == 0,
         first + round == (first < kSweep ? kSweep : first + 1), first + round, step_bytes(s),
         reinterpret_cast<const uint64_t *>(s.hot));
+    // Before the barrier, which waits for what the wave has in flight.
+    if (lane_id() == 0) {
+        s.rec_c[to][range.wave] = kept;
+        if (kept > 0)
+            atomicAdd(&s.stats[round % s.ring].live[range.wave % kSub], (unsigned long long)kept);
+    }
     if constexpr (!kPairs) {
         if (lane_id() == 0) longs.kept[wid] = kept;
         __syncthreads();
@@ -472,13 +477,8 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
                         });
                 }
             __syncthreads();
-            kept = longs.kept[wid];
+            if (lane_id() == 0) s.rec_c[to][range.wave] = longs.kept[wid];
         }
-    }
-    if (lane_id() == 0) {
-        s.rec_c[to][range.wave] = kept;
-        if (kept > 0)
-            atomicAdd(&s.stats[round % s.ring].live[range.wave % kSub], (unsigned long long)kept);
     }
 }
 
