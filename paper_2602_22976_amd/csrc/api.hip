@@ -1042,6 +1042,18 @@ bool staged_call(const Opts &o, const hgm_stats *stats) {
            o.variant != HGM_VARIANT_CREW && o.tail_pins <= 0 && o.bin_shift <= 0;
 }
 
+// Whether the rounds over all live edges are the faster ones for one instance
+// (schedule.h, kFewSize): an edge has few others at its pins, so that most
+// are matched in the first rounds whichever way they are looked at.
+bool few_conflicts(const Graph &g, const Opts &o) {
+    const int64_t size = std::max<int64_t>(g.kappa, g.m);
+    if (size < kFewSize) return false;
+    const double pins = (double)g.kappa, others = pins * pins / std::max(1.0, (double)g.n * g.m);
+    const double most = size <= kFewMiddle ? 12.0 : size <= kFewLarge ? 6.0 : 2.0;
+    const bool vertex_form = o.variant == HGM_VARIANT_AUTO && o.have_vertex_side;
+    return others <= (vertex_form ? most : most / 2);
+}
+
 // Workspace of hgm_match_noalloc: one array per GPU in the library's device
 // memory, held until the process ends.  In host code `scratch` names a host
 // stand-in, not the device array, so the array is only ever used through the
@@ -1181,7 +1193,7 @@ int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *w
     bool ran = false;
     rc = match_solo(g, o, lay, s, L.stream, seed, matched_bits, stats, may_allocate, &ran);
     if (rc != HGM_OK || ran) return rc;
-    if (g.m > 0 && staged_call(o, stats)) {
+    if (g.m > 0 && staged_call(o, stats) && !few_conflicts(g, o)) {
         bool recheck = false;
         rc = run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate, &recheck);
         if (rc != HGM_OK || !recheck) return rc;

@@ -78,6 +78,22 @@ constexpr int64_t kStagedLargeEdges = (int64_t)1 << 23;
 // them: 1,023 us with 64 edges a wave, 354 with 4,096 pins, 255 with 512; the
 // rounds over all edges 1,115).
 constexpr int64_t kStagedWavePins = 512;
+// Matching only, one instance with few edges at each pin (pins a vertex times
+// pins an edge, the others that an edge meets): rounds over all edges up to 12
+// of them below kFewMiddle pins (or edges), 6 below kFewLarge, 2 beyond; half
+// as many where round 0 has no vertex form.  Admission has twice the launches
+// and passes to pay for, and little to leave out.  Admission / all edges, us, by
+// others met:
+//   graphs, 40,000 pins    1: 144 / 95   4: 143 / 94    8: 103 / 102
+//           1M             1: 252 / 190  8: 225 / 195  12: 214 / 210  16: 172 / 214
+//           4M             1: 514 / 404  4: 372 / 331   8: 305 / 324
+//           16M            1: 1995 / 1523  2: 1473 / 1233  4: 1010 / 1093
+//   edges of 4, 2M         2: 370 / 258  8: 311 / 270  16: 283 / 263  24: 272 / 288
+//           8M             2: 874 / 800  4: 661 / 712
+//   no vertex form, 1M     1: 248 / 203  4: 249 / 202   8: 219 / 224
+//           4M             2: 449 / 426  4: 370 / 418
+// Below kFewSize both are a chain of launches (20,000 pins: 82 / 98).
+constexpr int64_t kFewSize = 1 << 15, kFewMiddle = 1 << 21, kFewLarge = 6 << 20;
 // Rounds by admission: round 0 starts with the first step expected to admit
 // at least this many edges (fewer leave the grid idle for a whole round).
 constexpr int64_t kStagedFirstEdges = 1024;
