@@ -175,10 +175,12 @@ __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s
 // the vertex form, so the pins are left alone elsewhere.
 //
 // Bound by streaming the pins (4.4 TB/s): hub-stress, 36M pins, 465 -> 506 us;
-// power-law, 30M, the edge form, 341 -> 347 for the pass over v_off.
-constexpr int kCheckThreads = 256, kCheckGrid = 1024;
+// 13M uniform pins 354 -> 369, 3.2M 201 -> 213 (230 with 1,024 workgroups, whose
+// sums meet at the same few counters); power-law, 30M, the edge form, 341 -> 347
+// for the pass over v_off.
+constexpr int kCheckThreads = 1024, kCheckGrid = 256, kCheckCopies = 4;
 __global__ void __launch_bounds__(kCheckThreads) k_staged_check(Graph g, State s, int parts) {
-    __shared__ uint32_t count[kCheckThreads / kWave][kBinMaxBins];
+    __shared__ uint32_t count[kCheckCopies][kBinMaxBins];  // each by some of the waves
     __shared__ unsigned long long hot_sum;
     const int tid = threadIdx.x;
     if (tid == 0) hot_sum = 0;
@@ -197,9 +199,10 @@ __global__ void __launch_bounds__(kCheckThreads) k_staged_check(Graph g, State s
                                                                    : kBinsCompare;
     if (blockIdx.x == 0 && tid == 0) *s.piece_count = verdict;
     if (verdict != kBinsCompare) return;
-    uint32_t *mine = count[tid / kWave];
-    for (int j = lane_id(); j < s.bin_nb; j += kWave) mine[j] = 0;
-    wave_fence();
+    uint32_t *mine = count[tid / kWave % kCheckCopies];
+    for (int j = tid; j < s.bin_nb; j += kCheckThreads)
+        for (int w = 0; w < kCheckCopies; ++w) count[w][j] = 0;
+    __syncthreads();
     const uint32_t last = (uint32_t)s.bin_nb - 1;
     auto add = [&](int v) { atomicAdd(&mine[min((uint32_t)v >> s.bin_rb, last)], 1u); };
     // 16-byte loads from the first aligned pin on.
@@ -235,7 +238,7 @@ __global__ void __launch_bounds__(kCheckThreads) k_staged_check(Graph g, State s
     __syncthreads();
     for (int j = tid; j < s.bin_nb; j += kCheckThreads) {
         uint32_t c = 0;
-        for (int w = 0; w < kCheckThreads / kWave; ++w) c += count[w][j];
+        for (int w = 0; w < kCheckCopies; ++w) c += count[w][j];
         if (c) atomicAdd(&s.bin_cursor[j], c);
     }
 }
