@@ -1042,15 +1042,19 @@ bool staged_call(const Opts &o, const hgm_stats *stats) {
            o.variant != HGM_VARIANT_CREW && o.tail_pins <= 0 && o.bin_shift <= 0;
 }
 
-// Whether the rounds over all live edges are the faster ones for one instance
-// (schedule.h, kFewSize): an edge has few others at its pins, so that most
+// Whether the rounds over all live edges are the faster ones (schedule.h,
+// kFewSize): edges are short and have few others at their pins, so that most
 // are matched in the first rounds whichever way they are looked at.
 bool few_conflicts(const Graph &g, const Opts &o) {
     const int64_t size = std::max<int64_t>(g.kappa, g.m);
-    if (size < kFewSize) return false;
-    const double pins = (double)g.kappa, others = pins * pins / std::max(1.0, (double)g.n * g.m);
-    const double most = size <= kFewMiddle ? 12.0 : size <= kFewLarge ? 6.0 : 2.0;
     const bool vertex_form = o.variant == HGM_VARIANT_AUTO && o.have_vertex_side;
+    if (size < (g.vbase ? kFewBatch : kFewSize) || g.kappa > kFewMean * g.m) return false;
+    // The vertex form reads every vertex, batches set all of them up.
+    if (g.vbase ? g.n > 8 * g.kappa : vertex_form && g.n >= kFewVerts && g.n > 4 * g.kappa)
+        return false;
+    const double pins = (double)g.kappa, others = pins * pins / std::max(1.0, (double)g.n * g.m);
+    if (g.vbase) return others <= kFewBatchOthers;
+    const double most = size <= kFewMiddle ? 12.0 : size <= kFewLarge ? 6.0 : 2.0;
     return others <= (vertex_form ? most : most / 2);
 }
 
@@ -1334,9 +1338,14 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
     // Calls that want only the matching run the solo part by admission
     // (solo.hip), unless the mean instance alone is too long for it.
     const size_t order_room = s.solo ? 40 * (size_t)lay.solo_rounds : 0;
-    const bool too_long = o.solo_max_kappa == 0 && b->count > 0 &&
-                          b->kappa_total / b->count > solo_longest(b->kappa_total);
-    if (s.explicit0 && staged_call(o, stats) && b->m_total > 0 && !too_long &&
+    const int64_t longest = solo_longest(b->kappa_total);
+    const bool too_long =
+        o.solo_max_kappa == 0 && b->count > 0 &&
+        (b->kappa_total / b->count > longest ||
+         solo_sparse_pins(b->n_total / b->count, b->m_total / b->count, b->kappa_total / b->count,
+                          solo_wide_own_verts(device_lds())) > longest + b->n_total / kGridVerts);
+    const bool admit = staged_call(o, stats) && b->m_total > 0;
+    if (s.explicit0 && admit && !too_long &&
         4 * (size_t)b->count <= order_room) {
         SoloJob J;
         memset(&J, 0, sizeof(J));
@@ -1378,12 +1387,14 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         HGM_TRY(hipStreamSynchronize(L.stream));
         if (slot.get()) memcpy(listed, J.report, sizeof(listed));
         if (listed[1] == 0) return HGM_OK;
+        if (listed[0] == 0 && few_conflicts(g, o))
+            return run_rounds(g, o, lay, s, L, 0, matched_bits, stats, &in, &sa);
         in.mark_done = listed[0] > 0;
         in.solo_max_size = J.max_size;
         in.solo_max_verts = J.max_verts;
         return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     }
-    if (b->m_total > 0 && staged_call(o, stats) && (!s.explicit0 || too_long))
+    if (admit && (!s.explicit0 || too_long) && !few_conflicts(g, o))
         return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     return run_rounds(g, o, lay, s, L, 0, matched_bits, stats, &in, &sa);
 }

@@ -256,7 +256,7 @@ struct SoloJob {
     const uint32_t *seeds;
     int32_t *order;      // [count] solo instances, longest first
     int64_t max_size;
-    int32_t max_verts, small_verts;
+    int32_t max_verts, small_verts, own_verts;  // own: a slot each in a wide workgroup
     int64_t *report;     // {instances listed, instances left to the round kernels}
     int32_t choose;      // leave the solo part out where the round kernels are faster
 };
@@ -276,12 +276,22 @@ __device__ __forceinline__ int64_t solo_size(const int64_t *e_base, const int64_
     const int64_t k = pin_base[i + 1] - pin_base[i], m = e_base[i + 1] - e_base[i];
     return k > m ? k : m;
 }
+// An instance of a batch whose vertices share slots (more than `own`) and with
+// few pins a vertex counts with this many pins against that and the batch's
+// vertices (solo.hip says why); 0: it does not.
+constexpr int64_t kSparse = 4, kGridVerts = 32;
+__host__ __device__ __forceinline__ int64_t solo_sparse_pins(int64_t n, int64_t m, int64_t kappa,
+                                                             int own) {
+    if (n <= own || kappa >= kSparse * n) return 0;
+    return kappa >= 8 * m ? 16 * kappa : (kappa + 2 * m) * 8 / 5;
+}
 // LDS of the done bits of n vertices; the maxima follow when they fit.
 __host__ __device__ __forceinline__ int64_t solo_done_bytes(int64_t n) {
     return (4 * ((n + 31) / 32) + 15) & ~(int64_t)15;
 }
 // lds: LDS of a compute unit.  Most vertices of one instance (exact: a slot each):
 int solo_one_max_verts(int lds, bool exact);
+int solo_wide_own_verts(int lds);  // of a batch's instance, a slot each
 hipError_t launch_solo_one(hipStream_t stream, SoloJob J, bool pairs, int lds);
 hipError_t launch_solo_batch(hipStream_t stream, SoloJob J, int64_t n_total, int cus, int lds);
 

@@ -78,7 +78,7 @@ constexpr int64_t kStagedLargeEdges = (int64_t)1 << 23;
 // them: 1,023 us with 64 edges a wave, 354 with 4,096 pins, 255 with 512; the
 // rounds over all edges 1,115).
 constexpr int64_t kStagedWavePins = 512;
-// Matching only, one instance with few edges at each pin (pins a vertex times
+// Matching only, short edges (kFewMean pins) and few of them at each pin (pins a vertex times
 // pins an edge, the others that an edge meets): rounds over all edges up to 12
 // of them below kFewMiddle pins (or edges), 6 below kFewLarge, 2 beyond; half
 // as many where round 0 has no vertex form.  Admission has twice the launches
@@ -92,8 +92,16 @@ constexpr int64_t kStagedWavePins = 512;
 //           8M             2: 874 / 800  4: 661 / 712
 //   no vertex form, 1M     1: 248 / 203  4: 249 / 202   8: 219 / 224
 //           4M             2: 449 / 426  4: 370 / 418
-// Below kFewSize both are a chain of launches (20,000 pins: 82 / 98).
-constexpr int64_t kFewSize = 1 << 15, kFewMiddle = 1 << 21, kFewLarge = 6 << 20;
+// Below kFewSize both are a chain of launches (20,000 pins: 82 / 98).  Longer
+// edges: 50,000 of 16 pins meeting 8, 208 / 183, but 2,000 of 64 136 / 326.  With
+// more than 4 vertices a pin, from kFewVerts on, the vertex form's pass over
+// them costs more (2M pins, 16M vertices 464 / 442, 33M 582 / 692).
+// Batches (rounds without the ending): 640,000 pins, 0.8 others 247 / 199;
+// 480,000, 2 192 / 184; 320,000, 2.7 173 / 174; 1.28M, 4 268 / 248; with 62
+// vertices a pin 213 / 225 and 419 / 649.
+constexpr int64_t kFewSize = 1 << 15, kFewMiddle = 1 << 21, kFewLarge = 6 << 20, kFewMean = 8;
+constexpr int64_t kFewVerts = 1 << 22, kFewBatch = 1 << 14;
+constexpr double kFewBatchOthers = 2.5;
 // Rounds by admission: round 0 starts with the first step expected to admit
 // at least this many edges (fewer leave the grid idle for a whole round).
 constexpr int64_t kStagedFirstEdges = 1024;

@@ -776,31 +776,47 @@ __global__ void __launch_bounds__(T, 4) k_solo_batch(SoloJob J) {
 // 0.87; 1,500, 1.6e8, 2.60 / 1.17.  Up to 7e4: 256, 4.2e6, 0.23 / 0.28.  Up to
 // 2.8e5: 400, 1.9e7, 0.41 / 0.49.  Up to 3.8e4: 2, 4e4, 0.14 / 0.12; 64, 6.8e5,
 // 0.14 / 0.12; 1,000, 1.05e7, 0.31 / 0.17.)
+//
+// An instance with few pins a vertex keeps most of its edges alive, and where
+// its vertices share slots it needs many rounds, the more the longer its edges
+// are: it takes about as long as one of solo_sparse_pins.  The grid's time on
+// such batches goes with the vertices, too, about 30 of them a pin.  (1, 16, 64
+// and 256 instances of 100,000 vertices, us, rounds over all edges / here / the
+// grid by admission.  1,000 edges of 32 pins: 239 / 620 / 148, 286 / 695 / 208,
+// 375 / 706 / 314, 1,067 / 753 / 755.  20,000 edges of 2: 141 / 216 / 185, 199 /
+// 229 / 247, 428 / 249 / 478, 1,096 / 383 / 1,603.  30,000 vertices, 15,000 edges
+// of 2: 134 / 160 / 165, 184 / 168 / 192, 286 / 180 / 331, 631 / 240 / 894.)
 constexpr int kOrderThreads = 1024;
 __global__ void __launch_bounds__(kOrderThreads) k_solo_order(SoloJob J) {
     constexpr int kClasses = 128;
     __shared__ int count[kClasses], start[kClasses], rest;
-    __shared__ unsigned long long longest;
+    __shared__ unsigned long long longest, sparse;
     const int tid = threadIdx.x;
     if (tid < kClasses) count[tid] = 0;
     if (tid == 0) {
         rest = 0;
         longest = 0;
+        sparse = 0;
     }
     __syncthreads();
     if (J.choose) {
-        unsigned long long most = 0;
+        unsigned long long most = 0, most_sparse = 0;
         for (int i = tid; i < J.count; i += kOrderThreads) {
             const int64_t n = J.v_base[i + 1] - J.v_base[i];
             const int64_t k = solo_size(J.e_base, J.pin_base, i);
-            if (k <= J.max_size && n <= J.max_verts && (unsigned long long)k > most)
-                most = (unsigned long long)k;
+            if (k > J.max_size || n > J.max_verts) continue;
+            const int64_t p = solo_sparse_pins(n, J.e_base[i + 1] - J.e_base[i],
+                                               J.pin_base[i + 1] - J.pin_base[i], J.own_verts);
+            most = max(most, (unsigned long long)k);
+            most_sparse = max(most_sparse, (unsigned long long)p);
         }
         atomicMax(&longest, most);
+        atomicMax(&sparse, most_sparse);
         __syncthreads();
     }
-    const bool none =
-        J.choose && (int64_t)longest > solo_longest(J.pin_base[J.count]);
+    const int64_t bound = solo_longest(J.pin_base[J.count]);
+    const bool none = J.choose && ((int64_t)longest > bound ||
+                                   (int64_t)sparse > bound + J.v_base[J.count] / kGridVerts);
     auto size_class = [&](int i) -> int {  // -1: left to the round kernels, -2: nothing to match
         const int64_t n = J.v_base[i + 1] - J.v_base[i];
         const int64_t k = solo_size(J.e_base, J.pin_base, i);
@@ -876,6 +892,8 @@ hipError_t launch_batch(hipStream_t stream, SoloJob J, int workgroups, int lds) 
 
 }  // namespace
 
+int solo_wide_own_verts(int lds) { return own_slots(room<kSoloWideThreads>(lds, kSoloWidePerCu)); }
+
 int solo_one_max_verts(int lds, bool exact) {
     const int bytes = room<kSoloOneThreads>(lds, 1);
     return exact ? own_slots(bytes) : 4 * bytes;  // done bits in half of it
@@ -894,6 +912,7 @@ hipError_t launch_solo_batch(hipStream_t stream, SoloJob J, int64_t n_total, int
     const int64_t most = n_total < J.max_verts ? n_total : J.max_verts;
     const int64_t full = solo_done_bytes(most) + 8 * most;
     J.small_verts = own_slots(small_lds);
+    J.own_verts = solo_wide_own_verts(lds);
     if (J.small_verts <= 0 || solo_done_bytes(most) > wide_lds / 2) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_solo_order, dim3(1), dim3(kOrderThreads), 0, stream, J);
     hipError_t rc = hipGetLastError();
