@@ -161,8 +161,10 @@ typedef struct hgm_opts {
                                 half the pins lie on vertices of at least
                                 this degree (default 64) */
     int32_t first_batch_pct; /* rounds enqueued before the first termination
-                                check: pct / 100 * log2(kappa) (default 40,
-                                35 for graphs; at most 400) */
+                                check: pct / 100 * log2(kappa) (at most 400).
+                                Default: 40, 35 for graphs; hgm_match with
+                                tail_pins 0: until that workgroup is expected
+                                to take over */
     int32_t tail_pins;       /* hgm_match: once a round has at most this many
                                 live pins (and at most 65536 live edges), one
                                 workgroup runs every remaining round.

@@ -691,15 +691,15 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
     bool tail_missed = false;
     std::vector<unsigned long long> tail_head(kTailHeader + 5 * (size_t)kTailRowsFirst, 0);
     // One instance: the last rounds run in one workgroup, which leaves the
-    // counts in pinned host memory.  The first batch of rounds goes on until
-    // that workgroup is expected to take over.
+    // counts in pinned host memory.  By default the first batch of rounds goes
+    // on until that workgroup is expected to take over.
     const bool graph = g.kappa == 2 * (int64_t)g.m;
     std::optional<HostSlot> slot;
     if (o.ending && !g.vbase && !T.on && !finished) slot.emplace(may_allocate);
     unsigned long long *report = slot ? (unsigned long long *)slot->get() : nullptr;
     while (!finished) {
         int batch = next_batch(o, launched, live_p, graph);
-        if (report && o.adaptive && launched == 0) {
+        if (report && o.adaptive && launched == 0 && o.first_batch_pct == 0) {
             const double pins = (double)g.kappa;
             const double most =
                 std::max(1.0, pins / std::min(kEndingPins, kEndingEdges * pins / (double)g.m));
