@@ -145,11 +145,13 @@ typedef struct hgm_opts {
                                 every vertex has a slot in LDS and 8192 or
                                 4096 where they share them). */
     /* Schedule (any value gives the same result; hgm_tune picks them per
-     * shape).  0 = library default for each. */
+     * shape).  0 = library default for each.  Calls that admit the edges in
+     * steps heed edge_grid, blocks_per_cu, rounds_per_sync and tail_pins. */
     int32_t edge_grid;       /* workgroups of the edge-centric kernels, each
-                                owning a fixed range of edge ids (default
-                                1536 for one instance, 4096 for a batch; at
-                                most 65536) */
+                                owning a fixed range of edge ids (at most
+                                65536).  Default: 1536 for one instance, 4096
+                                for a batch; calls that admit the edges in
+                                steps 512, beyond 2^23 edges 1024 */
     int32_t blocks_per_cu;   /* workgroups per compute unit of the vertex-
                                 centric and setup kernels (default 8, at
                                 most 32) */

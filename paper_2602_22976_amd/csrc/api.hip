@@ -584,6 +584,7 @@ EndArgs end_args(const State &s, unsigned long long *report) {
     for (int k = 0; k < 2; ++k) a.counts[k] = s.cnt[k];
     a.lists = s.grid;
     a.stride = s.region;
+    a.run = 1;
     return a;
 }
 
@@ -998,6 +999,7 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
     EndArgs end = end_args(s, report);
     for (int k = 0; k < 2; ++k) end.counts[k] = s.rec_c[k];
     end.check_bins = check_bins ? 1 : 0;
+    end.run = o.ending || batch ? 1 : 0;  // tail_pins is hgm_match's
     end.lists = s.grid * (kBlock / kStagedWave);
     end.stride = s.region / (kBlock / kStagedWave);
     HGM_TRY(launch_staged_join(L, g, s, 0, first, seed));

@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
         if (found == kBinsBadOffsets && tid == 0) a.report[kEndOverflow] = 2;
     }
     const unsigned long long live = wave_total(s.stats[a.round % s.ring].live[lane]);
-    const bool limit = a.max_rounds > 0 && a.round >= a.max_rounds;
+    const bool limit = !a.run || (a.max_rounds > 0 && a.round >= a.max_rounds);
     if (live == 0 || live > (unsigned long long)kEdges || limit) {
         if (tid == 0) {
             a.report[kEndFinished] = live == 0;

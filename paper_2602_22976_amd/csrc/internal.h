@@ -396,6 +396,7 @@ struct EndArgs {
     int32_t counting;  // report the rounds' counts (rounds beyond the `rows` that fit:
     int32_t rows;      // rec_key[round & 1], one word each: live edges, live pins, matched
                        // edges and their pins in 16 bits each; rec_key[other]: the weight)
+    int32_t run;         // 0: only report
     int32_t check_bins;  // compare the counts of launch_staged_setup with v_off
     unsigned long long *report;  // device or pinned host memory, header cleared by the caller
 };

@@ -54,3 +54,20 @@ def test_first_batch(hgm, variant):
     many = _best(hgm, g, True, variant=variant, first_batch_pct=400)
     usual = _best(hgm, g, True, variant=variant)
     assert many > 1.3 * usual and many > 1.3 * few
+
+
+def test_never_a_last_workgroup(hgm):
+    """A path of increasing weights: 750 rounds, nearly all of them in the last
+    workgroup, or with tail_pins -1 none, whatever the call wants."""
+    g = path_graph(1500)
+    for want_stats in (False, True):
+        usual = _best(hgm, g, want_stats, reps=4, solo_max_kappa=-1)
+        never = _best(hgm, g, want_stats, reps=4, solo_max_kappa=-1, tail_pins=-1)
+        assert never > 1.5 * usual
+
+
+@pytest.mark.parametrize("n,m", [(500, 1025), (4000, 12_000), (30_000, 90_000)])
+def test_never_a_last_workgroup_parity(hgm, n, m):
+    g = synth.random_instance(m, n, m, 1, 7, 1, 9, empty_frac=0.02)
+    for kw in (dict(), dict(variant="crcw"), dict(rounds_per_sync=1), dict(rounds_per_sync=7)):
+        _best(hgm, g, False, reps=2, solo_max_kappa=-1, tail_pins=-1, **kw)
