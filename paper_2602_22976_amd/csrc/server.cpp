@@ -631,8 +631,11 @@ int hgm_server_create(void *arena, size_t arena_bytes, const hgm_server_opts *op
     S->device = dev;
     S->streams = streams;
     S->staging.resize(o.workers);
+    // Whole pages, so that chunks and the offsets they are cut at stay aligned
+    // for every number of workers.
     const size_t chunk =
-        std::min(kStagingChunk, kStagingBytes / Staging::kChunks / (size_t)o.workers);
+        std::min(kStagingChunk, kStagingBytes / Staging::kChunks / (size_t)o.workers) &
+        ~(size_t)4095;
     void *pinned = nullptr;
     if (hipHostMalloc(&pinned, chunk * Staging::kChunks * o.workers, hipHostMallocPortable) ==
         hipSuccess) {
