@@ -325,10 +325,12 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
  * blocks_per_cu, hub_threshold, hot_degree, clear_ratio, first_batch_pct,
  * and solo_max_kappa for batches) change how the work is laid out, never the
  * result.  hgm_tune times whole matchings of the given instance (median of
- * `reps` calls after one untimed call) under candidate schedules, by
- * coordinate descent from `base` (NULL or 0 fields: the defaults), checks
- * that every candidate produces the starting schedule's bitmap, and returns
- * the fastest schedule in *best (base's other fields kept).  With a cache
+ * `reps` calls after one untimed call), without and with statistics, under
+ * candidate schedules, by coordinate descent from `base` (NULL or 0 fields: the
+ * defaults, which stay 0 where no candidate wins), checks that every candidate
+ * produces the starting schedule's bitmap, and returns in *best (base's other
+ * fields kept) a schedule that is faster for one kind of call and as fast for
+ * the other.  With a cache
  * path (or, when `cache` is NULL, the HGM_TUNE_CACHE environment variable)
  * the result is also stored in that text file under a key of the device
  * (architecture and compute units) and the shape bucket (kind, variant,
@@ -338,8 +340,8 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
  * bytes (the largest candidate edge grid); matched_bits receives the
  * matching.  Not part of the paper: a schedule search of this library. */
 typedef struct hgm_tune_report {
-    double ms_default;       /* median time of the starting schedule */
-    double ms_best;          /* median time of the schedule returned */
+    double ms_default;       /* median time of the starting schedule, and of the */
+    double ms_best;          /* schedule returned; calls without statistics */
     int32_t evaluations;     /* schedules timed */
     int32_t identical;       /* 1: every candidate gave the starting bitmap */
 } hgm_tune_report;

@@ -114,10 +114,5 @@ constexpr int64_t kStagedTailEdges = (int64_t)1 << 15;
 // unless asked for: a round there costs as much as a round of the grid-wide
 // kernels (both are a chain of dependent memory accesses).
 constexpr int kDefaultTailPins = -1;
-// Binned maximum: automatic by default (0): on for large instances whose
-// round 0 takes the vertex form, where it won (hub-stress 1.26 -> 1.18 ms);
-// skewed degrees keep the atomic scatter, which won there (power-law 1.05
-// against 1.11 ms with bins).
-constexpr int kDefaultBinShift = 0;
 
 }  // namespace hgm

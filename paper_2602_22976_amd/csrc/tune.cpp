@@ -10,11 +10,14 @@
 // reports a mismatch instead of choosing that candidate.
 //
 // Search: coordinate descent in a fixed order of fields, each over a short
-// list of candidate values around the default, keeping a value only when it
-// is faster than the best so far by more than the run-to-run spread (2%).
-// Time of a candidate = median over `reps` calls of the host wall time of
-// hgm_match / hgm_match_batch (which returns once the matching is complete
-// in device memory), after one untimed call.
+// list of candidate values, from the library's defaults (0, what a caller who
+// tunes nothing gets).  The cache serves calls that want only the matching and
+// calls with statistics, which run different kernels, so both are timed: a
+// value is kept when it is faster than the best so far by more than the
+// run-to-run spread (2%) for one of them and not slower by more than that for
+// the other.  Time of a candidate = median over `reps` calls of the host wall
+// time of hgm_match / hgm_match_batch (which returns once the matching is
+// complete in device memory), after one untimed call.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdio.h>
@@ -51,15 +54,15 @@ struct Knob {
 
 std::vector<Knob> knobs(bool batch) {
     std::vector<Knob> k = {
-        {"solo", &hgm_opts::solo_max_kappa, {-1, 1 << 16, 1 << 18, 1 << 20, 1 << 22}, 1},
-        {"grid", &hgm_opts::edge_grid, {512, 1024, 1536, 2048, 3072, 4096, 8192, 16384}, 0},
-        {"bpc", &hgm_opts::blocks_per_cu, {2, 4, 8, 16}, 0},
-        {"hub", &hgm_opts::hub_threshold, {1024, 4096, 8192, 32768, 1 << 30}, 0},
-        {"hot", &hgm_opts::hot_degree, {16, 64, 256}, 0},
-        {"clear", &hgm_opts::clear_ratio, {2, 8, 32}, 0},
-        {"first", &hgm_opts::first_batch_pct, {25, 40, 55}, 0},
-        {"tail", &hgm_opts::tail_pins, {-1, 1024, 4096, 32768}, 2},
-        {"bins", &hgm_opts::bin_shift, {-1, 0, 12, 13, 14}, 2},
+        {"solo", &hgm_opts::solo_max_kappa, {0, -1, 1 << 16, 1 << 18, 1 << 20, 1 << 22}, 1},
+        {"grid", &hgm_opts::edge_grid, {0, 512, 1024, 1536, 2048, 3072, 4096, 8192, 16384}, 0},
+        {"bpc", &hgm_opts::blocks_per_cu, {0, 2, 4, 16}, 0},
+        {"hub", &hgm_opts::hub_threshold, {0, 1024, 4096, 32768, 1 << 30}, 0},
+        {"hot", &hgm_opts::hot_degree, {0, 16, 256}, 0},
+        {"clear", &hgm_opts::clear_ratio, {0, 2, 32}, 0},
+        {"first", &hgm_opts::first_batch_pct, {0, 25, 40, 55}, 0},
+        {"tail", &hgm_opts::tail_pins, {0, -1, 1024, 4096, 32768}, 2},
+        {"bins", &hgm_opts::bin_shift, {0, -1, 12, 13, 14}, 2},
     };
     std::vector<Knob> out;
     for (auto &x : k)
@@ -84,9 +87,10 @@ hgm_opts largest_workspace(const hgm_opts *base) {
     return o;
 }
 
-// The library default of each field, as the value the tuner reports.
-int32_t default_of(const char *name, bool batch, bool graph) {
-    if (!strcmp(name, "solo")) return 0;  // by the batch's size (solo_auto_bound)
+// The value that a cache line without a version has for a field that was not
+// tuned: the defaults were written out, of a library in which they were the
+// same for every kind of call.
+int32_t untuned(const char *name, bool batch, bool graph) {
     if (!strcmp(name, "grid")) return batch ? kEdgeGridBatch : kEdgeGrid;
     if (!strcmp(name, "bpc")) return kBlocksPerCu;
     if (!strcmp(name, "hub")) return kDefaultHubThreshold;
@@ -94,13 +98,7 @@ int32_t default_of(const char *name, bool batch, bool graph) {
     if (!strcmp(name, "clear")) return kFullClearRatio;
     if (!strcmp(name, "first")) return graph ? kFirstBatchPctGraph : kFirstBatchPct;
     if (!strcmp(name, "tail")) return kDefaultTailPins;
-    if (!strcmp(name, "bins")) return kDefaultBinShift;
     return 0;
-}
-
-void fill_defaults(hgm_opts *o, bool batch, bool graph) {
-    for (auto &k : knobs(batch))
-        if (o->*(k.field) == 0) o->*(k.field) = default_of(k.name, batch, graph);
 }
 
 // Shape bucket of a matching: device, kind, variant and layout, log2 of the
@@ -136,9 +134,11 @@ const char *cache_path(const char *path) {
 
 std::mutex g_cache_mu;
 
-// The schedule fields of `o` as "name=value" words.
+// The schedule fields of `o` as "name=value" words, after the line's version
+// (2: a field that was not tuned is 0).
 std::string encode(const hgm_opts &o, bool batch) {
     std::ostringstream s;
+    s << " version=2";
     for (auto &k : knobs(batch)) s << " " << k.name << "=" << o.*(k.field);
     return s.str();
 }
@@ -175,12 +175,16 @@ int cache_get(const char *path, const std::string &key, hgm_opts *o, bool batch)
         std::istringstream words(line.substr(key.size() + 3));
         std::string w;
         hgm_opts t = *o;
+        const bool versioned = line.find(" version=") != std::string::npos;
         while (words >> w) {
             const size_t eq = w.find('=');
             if (eq == std::string::npos) continue;
             const std::string name = w.substr(0, eq);
             for (auto &k : knobs(batch))
-                if (name == k.name) t.*(k.field) = (int32_t)strtol(w.c_str() + eq + 1, nullptr, 10);
+                if (name == k.name) {
+                    const int32_t v = (int32_t)strtol(w.c_str() + eq + 1, nullptr, 10);
+                    t.*(k.field) = !versioned && v == untuned(k.name, batch, o->pairs != 0) ? 0 : v;
+                }
         }
         *o = t;
         return HGM_OK;
@@ -188,56 +192,67 @@ int cache_get(const char *path, const std::string &key, hgm_opts *o, bool batch)
     return HGM_E_ARG;
 }
 
-// Coordinate descent over the knobs.  run(o) performs one matching with
-// options o and returns an HGM code; snapshot(true) copies the output as the
-// reference after the starting schedule's first run, snapshot(false)
-// compares a candidate's output with it (1 when they differ).
-int search(bool batch, bool graph, const hgm_opts *base, int reps,
-           const std::function<int(const hgm_opts &)> &run,
+// Coordinate descent over the knobs.  run(o, counted) performs one matching
+// with options o, with statistics when `counted`, and returns an HGM code;
+// snapshot(true) copies the output as the reference after the starting
+// schedule's first run, snapshot(false) compares a later output with it (1 when
+// they differ).  The report's times are those of the calls without statistics.
+int search(bool batch, const hgm_opts *base, int reps,
+           const std::function<int(const hgm_opts &, bool)> &run,
            const std::function<int(bool)> &snapshot,  // true: keep as reference; false: compare
            hgm_opts *best, hgm_tune_report *rep) {
     if (reps < 1) reps = 1;
     hgm_opts cur;
     memset(&cur, 0, sizeof(cur));
     if (base) cur = *base;
-    fill_defaults(&cur, batch, graph);
     int evaluations = 0, identical = 1;
-    auto time_of = [&](const hgm_opts &o, double *ms, bool reference) -> int {
-        int rc = run(o);  // untimed first call, also the bitmap check
-        if (rc != HGM_OK) return rc;
-        rc = snapshot(reference);
-        if (rc != HGM_OK) return rc;
-        std::vector<double> t;
-        for (int i = 0; i < reps; ++i) {
-            const double t0 = now_s();
-            rc = run(o);
+    struct Times {
+        double ms[2];  // without and with statistics
+    };
+    auto time_of = [&](const hgm_opts &o, Times *out, bool reference) -> int {
+        for (int counted = 0; counted < 2; ++counted) {
+            int rc = run(o, counted != 0);  // untimed first call, also the bitmap check
             if (rc != HGM_OK) return rc;
-            t.push_back((now_s() - t0) * 1e3);
+            rc = snapshot(reference && !counted);
+            if (rc != HGM_OK) return rc;
+            std::vector<double> t;
+            for (int i = 0; i < reps; ++i) {
+                const double t0 = now_s();
+                rc = run(o, counted != 0);
+                if (rc != HGM_OK) return rc;
+                t.push_back((now_s() - t0) * 1e3);
+            }
+            std::sort(t.begin(), t.end());
+            out->ms[counted] = t[t.size() / 2];
         }
-        std::sort(t.begin(), t.end());
-        *ms = t[t.size() / 2];
         evaluations += 1;
         return HGM_OK;
     };
-    double best_ms = 0.0;
-    int rc = time_of(cur, &best_ms, true);
+    constexpr double kFaster = 0.98, kSame = 1.02;
+    Times least;
+    int rc = time_of(cur, &least, true);
+    if (rc == 1) {  // the starting schedule's two calls differ
+        identical = 0;
+        rc = HGM_OK;
+    }
     if (rc != HGM_OK) return rc;
-    const double ms_default = best_ms;
+    const double ms_default = least.ms[0];
     for (auto &k : knobs(batch)) {
         int32_t keep = cur.*(k.field);
         for (int32_t v : k.values) {
             if (v == keep) continue;
             hgm_opts cand = cur;
             cand.*(k.field) = v;
-            double ms = 0.0;
-            rc = time_of(cand, &ms, false);
+            Times t;
+            rc = time_of(cand, &t, false);
             if (rc == 1) {  // bitmap differs from the reference: never chosen
                 identical = 0;
                 continue;
             }
             if (rc != HGM_OK) return rc;
-            if (ms < best_ms * 0.98) {
-                best_ms = ms;
+            const bool faster = t.ms[0] < least.ms[0] * kFaster || t.ms[1] < least.ms[1] * kFaster;
+            if (faster && t.ms[0] < least.ms[0] * kSame && t.ms[1] < least.ms[1] * kSame) {
+                for (int i = 0; i < 2; ++i) least.ms[i] = std::min(least.ms[i], t.ms[i]);
                 keep = v;
             }
         }
@@ -246,7 +261,7 @@ int search(bool batch, bool graph, const hgm_opts *base, int reps,
     *best = cur;
     if (rep) {
         rep->ms_default = ms_default;
-        rep->ms_best = best_ms;
+        rep->ms_best = least.ms[0];
         rep->evaluations = evaluations;
         rep->identical = identical;
     }
@@ -309,12 +324,14 @@ int hgm_tune(const hgm_csr *g, uint32_t seed, uint32_t *matched_bits, void *work
              const char *cache, hgm_opts *best, hgm_tune_report *report) {
     if (!g || !best || reps < 0) return HGM_E_ARG;
     if (ws_bytes < hgm_tune_workspace_size(g, base)) return HGM_E_SIZE;
-    const bool graph = base && base->pairs;
     BitsCheck check{matched_bits, (size_t)((int64_t)g->m + 31) / 32, (hipStream_t)stream, {}, {}};
-    auto run = [&](const hgm_opts &o) {
-        return hgm_match(g, seed, matched_bits, workspace, ws_bytes, &o, stream, nullptr);
+    hgm_stats counts;
+    memset(&counts, 0, sizeof(counts));
+    auto run = [&](const hgm_opts &o, bool counted) {
+        return hgm_match(g, seed, matched_bits, workspace, ws_bytes, &o, stream,
+                         counted ? &counts : nullptr);
     };
-    int rc = search(false, graph, base, reps, run, std::ref(check), best, report);
+    int rc = search(false, base, reps, run, std::ref(check), best, report);
     if (rc != HGM_OK) return rc;
     const char *path = cache_path(cache);
     if (path)
@@ -329,10 +346,13 @@ int hgm_tune_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace, 
     if (!b || !best || reps < 0) return HGM_E_ARG;
     if (ws_bytes < hgm_tune_batch_workspace_size(b, base)) return HGM_E_SIZE;
     BitsCheck check{matched_bits, (size_t)b->words_total, (hipStream_t)stream, {}, {}};
-    auto run = [&](const hgm_opts &o) {
-        return hgm_match_batch(b, matched_bits, workspace, ws_bytes, &o, stream, nullptr);
+    hgm_stats counts;
+    memset(&counts, 0, sizeof(counts));
+    auto run = [&](const hgm_opts &o, bool counted) {
+        return hgm_match_batch(b, matched_bits, workspace, ws_bytes, &o, stream,
+                               counted ? &counts : nullptr);
     };
-    int rc = search(true, false, base, reps, run, std::ref(check), best, report);
+    int rc = search(true, base, reps, run, std::ref(check), best, report);
     if (rc != HGM_OK) return rc;
     const char *path = cache_path(cache);
     if (path)
