@@ -40,20 +40,6 @@ struct EndShared {
     unsigned long long sum[4];  // live pins; matched edges, their weight and pins
 };
 
-__device__ __forceinline__ int end_scan(int v, int *tmp, int *total) {
-    const int wid = threadIdx.x / kWave, incl = wave_inclusive_sum(v);
-    if (lane_id() == kWave - 1) tmp[wid] = incl;
-    __syncthreads();
-    int off = 0, all = 0;
-    for (int i = 0; i < kThreads / kWave; ++i) {
-        off += i < wid ? tmp[i] : 0;
-        all += tmp[i];
-    }
-    __syncthreads();
-    *total = all;
-    return off + incl - v;
-}
-
 __device__ __forceinline__ unsigned long long wave_total(unsigned long long v) {
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -103,7 +89,7 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
     const int w0 = tid * per, w1 = min(w0 + per, a.lists);
     int mine = 0, E;
     for (int w = w0; w < w1; ++w) mine += a.counts[k][w];
-    int at = end_scan(mine, S.scan, &E);
+    int at = workgroup_scan<kThreads>(mine, S.scan, &E);
     for (int w = w0; w < w1 && mine > 0; ++w) {
         const int n = a.counts[k][w];
         for (int i = 0; i < n; ++i, ++at) {
@@ -129,7 +115,7 @@ __global__ void __launch_bounds__(kThreads) k_end(Graph g, State s, EndArgs a, u
         pins = pins < kPins ? pins : kPins + 1;
     }
     int total;
-    int begin = end_scan(pins, S.scan, &total);
+    int begin = workgroup_scan<kThreads>(pins, S.scan, &total);
     if (total > kPins) {  // left to the grid's rounds
         if (tid == 0) {
             a.report[kEndFinished] = 0;

@@ -26,11 +26,11 @@
 // double-buffered by round parity so that the test of round r can clear the
 // buffer round r+1 will fill.
 #include "internal.h"
+#include "wave.h"
 
 namespace hgm {
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kWaves = kBlock / kWave;
 
 // Key of edge e in a round whose priority seed is kseed.  A batch stores its
@@ -60,26 +60,6 @@ __device__ __forceinline__ uint64_t round_key(const Graph &g, const State &s, ui
         return ((uint64_t)g.w[e] << 32) | priority_hash(rs, (uint32_t)sl);
     }
     return edge_key<false>(g, s, kseed, e);
-}
-
-// v plus the value DPP control kCtrl reads for this lane (0 where it reads
-// none or the row is masked off).
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ int dpp_add(int v) {
-    return v + __builtin_amdgcn_update_dpp(0, v, kCtrl, kRowMask, 0xF, false);
-}
-
-// Inclusive prefix sum over a wave with DPP lane moves (VALU, no LDS
-// traffic): row shifts by 1, 2, 4, 8 sum each row of 16 lanes; lane 15 of
-// each row then adds into rows 1 and 3, and lane 31 into rows 2 and 3.
-__device__ __forceinline__ int wave_inclusive_sum(int v) {
-    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
-    v = dpp_add<0x112, 0xF>(v);  // row_shr:2
-    v = dpp_add<0x114, 0xF>(v);  // row_shr:4
-    v = dpp_add<0x118, 0xF>(v);  // row_shr:8
-    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15
-    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31
-    return v;
 }
 
 // Segmented inclusive max-scan over a wave with DPP lane moves (VALU), not
@@ -150,19 +130,6 @@ __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v
     for (int i = 0; i < kWaves; ++i) t += tmp[i];
     __syncthreads();
     return t;
-}
-
-// The work item (edge region or run of vertex chunks) of workgroup b among
-// `grid`.  The dispatcher deals workgroups to the chip's 8 XCDs round-robin
-// (b on XCD b % 8), and each XCD has its own L2: mapping each XCD's
-// workgroups to one contiguous share of the items keeps neighbouring items,
-// e.g. the edges and vertices of one instance of a batch, on one L2 instead
-// of all eight.  A bijection of [0, grid).
-constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_item(int b, int grid) {
-    const int x = b % kXcds, q = b / kXcds;
-    const int per = grid / kXcds, rem = grid % kXcds;
-    return x * per + (x < rem ? x : rem) + q;
 }
 
 // Largest j in [0, kBlock) with start[j] <= t (start non-decreasing, start[0] = 0).

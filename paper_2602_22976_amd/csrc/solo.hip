@@ -95,7 +95,6 @@ struct SoloSide {
     unsigned long long *max;
     int slots;       // fewer than vertices: shared
     uint32_t seed;   // the round's
-    bool rekey;
     __device__ __forceinline__ uint32_t done_word(int v) const { return done[v >> 5]; }
     __device__ __forceinline__ unsigned long long &slot(int v) const {
         const uint32_t at = __umulhi((uint32_t)v * 0x9E3779B1u, (uint32_t)slots);
@@ -246,22 +245,6 @@ __device__ __forceinline__ void head_act(const int32_t *e_pins, const EdgeHead (
         act(v, k);
         return false;
     });
-}
-
-// Exclusive sum over the workgroup.
-template <int T>
-__device__ __forceinline__ int solo_scan(int v, int *tmp, int *total) {
-    const int wid = threadIdx.x / kWave, incl = wave_inclusive_sum(v);
-    if (lane_id() == kWave - 1) tmp[wid] = incl;
-    __syncthreads();
-    int off = 0, all = 0;
-    for (int i = 0; i < T / kWave; ++i) {
-        off += i < wid ? tmp[i] : 0;
-        all += tmp[i];
-    }
-    __syncthreads();
-    *total = all;
-    return off + incl - v;
 }
 
 // The list rounds of an instance of more edges than threads.  Each wave owns a
@@ -538,8 +521,7 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
                        reinterpret_cast<uint32_t *>(lds),
                        reinterpret_cast<unsigned long long *>(lds + solo_done_bytes(I.nv)),
                        I.nv < room ? I.nv : room,
-                       rekey ? round_seed(I.seed, 0) : I.seed,
-                       rekey};
+                       rekey ? round_seed(I.seed, 0) : I.seed};
     for (int i = tid; i < dwords; i += T) m.done[i] = 0;
     for (int i = tid; i < m.slots; i += T) m.max[i] = 0;
     for (int64_t i = tid; i < I.words; i += T) I.bits[i] = 0;
@@ -611,7 +593,7 @@ __device__ __forceinline__ void solo_match(const Inst &I, const SoloJob &J, Solo
     };
     int total;
     const int n = len < kEndPins * T ? len : kEndPins * T + 1;
-    const int first = solo_scan<T>(mine ? n : 0, S.scan, &total);
+    const int first = workgroup_scan<T>(mine ? n : 0, S.scan, &total);
     bool alive = mine && (len > 0 || !tested);
     if (total > kEndPins * T) {
         // More pins than the workgroup's registers take: lane per edge.

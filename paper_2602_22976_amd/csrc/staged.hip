@@ -268,7 +268,7 @@ struct WaveRange {
 __device__ __forceinline__ WaveRange wave_range(const State &s) {
     WaveRange r;
     r.per = s.region / kWaves;
-    r.wave = xcd_share(blockIdx.x, gridDim.x) * kWaves + threadIdx.x / kWave;
+    r.wave = xcd_item(blockIdx.x, gridDim.x) * kWaves + threadIdx.x / kWave;
     r.lo = (int64_t)r.wave * r.per;
     return r;
 }
@@ -387,7 +387,6 @@ struct GridJoin {
             __hip_atomic_fetch_max(&best[v], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __device__ __forceinline__ uint64_t key(int e) const { return staged_key<kB>(g, s, seed, e); }
-    __device__ __forceinline__ uint64_t again(int, uint64_t k) const { return k; }
     __device__ __forceinline__ void place(int e, int &base, int &len, int &vb) const {
         base = kPairs ? 2 * e : g.e_off[e];
         len = kPairs ? 2 : g.e_off[e + 1] - base;
@@ -406,7 +405,6 @@ struct GridJoin {
                                           bool listed) const {
         return longs->take(threadIdx.x / kWave, {key, e, base, len, vb, listed});
     }
-    __device__ __forceinline__ void entered(int) const {}
 };
 
 __device__ __forceinline__ WaveLists lists(const State &s, int k) {

@@ -1,4 +1,6 @@
-// Wave-level building blocks of the admission kernels (solo.hip, staged.hip).
+// Wave- and workgroup-level building blocks: the sums and ids that every file
+// of kernels uses, then the passes over flattened pins and the join of a wave,
+// which are staged.hip's.
 #pragma once
 
 #include "internal.h"
@@ -8,17 +10,8 @@ namespace {
 
 constexpr int kWave = 64;
 
-// A wave's scratch for its chunk of 64 edges, the edges with pins numbered
-// 0, 1, ... in lane order.
-constexpr int kWindow = 2048;  // pins of a chunk flattened at a time
-struct WaveScratch {
-    uint64_t key[kWave];
-    int vb[kWave];                    // vertex base of the edge (batch)
-    int rel[kWave];                   // offset of the edge's pins less its start in the chunk
-    uint32_t flag[kWave];
-    uint32_t bits[kWindow / 32 + 2];  // a bit where an edge's pins start (or a pin is done)
-};
-
+// v plus the value that DPP control kCtrl reads for this lane (0 where it reads
+// none or the row is masked off).
 template <int kCtrl, int kRowMask>
 __device__ __forceinline__ int dpp_add(int v) {
     return v + __builtin_amdgcn_update_dpp(0, v, kCtrl, kRowMask, 0xF, false);
@@ -38,6 +31,36 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
+// Exclusive sum over a workgroup of T threads, with two barriers; tmp: a word a
+// wave.
+template <int T>
+__device__ __forceinline__ int workgroup_scan(int v, int *tmp, int *total) {
+    const int wid = threadIdx.x / kWave, incl = wave_inclusive_sum(v);
+    if (lane_id() == kWave - 1) tmp[wid] = incl;
+    __syncthreads();
+    int off = 0, all = 0;
+    for (int i = 0; i < T / kWave; ++i) {
+        off += i < wid ? tmp[i] : 0;
+        all += tmp[i];
+    }
+    __syncthreads();
+    *total = all;
+    return off + incl - v;
+}
+
+// The work item (edge region or run of vertex chunks) of workgroup b among
+// `grid`.  The dispatcher deals workgroups to the chip's 8 XCDs round-robin
+// (b on XCD b % 8), and each XCD has its own L2: mapping each XCD's
+// workgroups to one contiguous share of the items keeps neighbouring items,
+// e.g. the edges and vertices of one instance of a batch, on one L2 instead
+// of all eight.  A bijection of [0, grid).
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_item(int b, int grid) {
+    const int x = b % kXcds, q = b / kXcds;
+    const int per = grid / kXcds, rem = grid % kXcds;
+    return x * per + (x < rem ? x : rem) + q;
+}
+
 // Bits of m below this lane.
 __device__ __forceinline__ int bits_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -49,6 +72,17 @@ __device__ __forceinline__ int bits_below(uint64_t m) {
 __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
+
+// A wave's scratch for its chunk of 64 edges, the edges with pins numbered
+// 0, 1, ... in lane order.
+constexpr int kWindow = 2048;  // pins of a chunk flattened at a time
+struct WaveScratch {
+    uint64_t key[kWave];
+    int vb[kWave];                    // vertex base of the edge (batch)
+    int rel[kWave];                   // offset of the edge's pins less its start in the chunk
+    uint32_t flag[kWave];
+    uint32_t bits[kWindow / 32 + 2];  // a bit where an edge's pins start (or a pin is done)
+};
 
 // The pins of the wave's 64 edges (lane: n pins from base), flattened over
 // the lanes 64 at a time, so that a chunk costs its pins and not 64 times its
@@ -251,11 +285,10 @@ struct WaveLists {
 // copy of it behind every place that finds edges the kernel did not fit the
 // instruction cache: a round without an edge took 50 us instead of 4.)
 //
-// M: done_word(v), lower(v), peek(v), raise(v, key, peeked), key(e), again(e,
-// key) (the key of a listed edge this round), place(e, base, len, vb), sort(e,
-// w, k) / exact_sort(e, w) (weight or key that the thresholds are compared
-// with), defer(e, base, len, vb, key, listed) (true: the edge is left to the
-// caller), entered(len).
+// M: done_word(v), lower(v), peek(v), raise(v, key, peeked), key(e), place(e,
+// base, len, vb), sort(e, w, k) / exact_sort(e, w) (weight or key that the
+// thresholds are compared with), defer(e, base, len, vb, key, listed) (true: the
+// edge is left to the caller), lowering (whether lower does anything).
 // kFill: chunks of 64 edges looked at in one step, at most (a multiple of 4).
 constexpr uint8_t kNever = 255;  // step of an edge that was dropped
 constexpr int cand_size(int fill) { return (fill + 1) * kWave; }
@@ -415,7 +448,7 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
                     len = from.len[at];
                     if constexpr (kB) vb = from.vb[at];
                 }
-                key = m.again(e, from.key[at]);
+                key = from.key[at];
             }
             on = len > 0;  // an empty edge was matched by its test
             i0 += kWave;
@@ -465,7 +498,6 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
                     }
                     to.key[at] = key;
                 }
-                m.entered(live ? len : 0);
                 kept += __popcll(mask);
                 return key;
             },
@@ -473,14 +505,6 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
             [&](int v, uint64_t k, auto now) { m.raise(v, k, now); }, vb);
     }
     return kept;
-}
-
-// The work item of workgroup b among `grid`: the dispatcher deals workgroups
-// to the 8 XCDs in turn, and each XCD has its own L2, so each XCD's workgroups
-// take one contiguous share of the items.  A bijection of [0, grid).
-__device__ __forceinline__ int xcd_share(int b, int grid) {
-    const int x = b % 8, q = b / 8, per = grid / 8, rem = grid % 8;
-    return x * per + (x < rem ? x : rem) + q;
 }
 
 }  // namespace
