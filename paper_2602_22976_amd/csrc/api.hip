@@ -961,11 +961,22 @@ int run_rounds(const Graph &g, const Opts &o, const Layout &lay, const State &s,
 }
 
 
+// Most others that an edge may meet for the rounds over all live edges to be the
+// faster ones of a sparse instance (schedule.h, kSparseAsk); 0: they are not.
+double few_others(const Graph &g, const Opts &o) {
+    const bool vertex_form = o.variant == HGM_VARIANT_AUTO && o.have_vertex_side;
+    if (std::max<int64_t>(g.kappa, g.m) <= kSparseAsk) return 0.0;
+    if (vertex_form && g.n >= kSparseVerts && g.n > 4 * g.kappa) return 0.0;
+    if (g.kappa <= kSparseMiddle) return vertex_form ? kFewOthers : kFewOthersEdge;
+    return vertex_form ? kFewOthersLarge : 0.0;
+}
+
 // Rounds by admission (staged.hip): calls that want only the matching.
-// *recheck (one instance): v_off is not the transpose, in a way that the rounds
-// over all live edges may find or not: the call runs them.
+// *over_all (one instance): the call runs the rounds over all live edges instead,
+// because edges meet few others, or because v_off is not the transpose in a way
+// that those rounds may find or not.
 int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t seed,
-               uint32_t *bits, const BatchIn *batch, bool may_allocate, bool *recheck = nullptr) {
+               uint32_t *bits, const BatchIn *batch, bool may_allocate, bool *over_all = nullptr) {
     // Those rounds use automatic bins, and find one overflowing, only where
     // they expect n / 2 live pins.
     const bool check_bins = s.bin_nb > 0 && s.bin_auto && 2 * g.kappa >= (int64_t)g.n;
@@ -983,28 +994,65 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
     s.region = (int)((chunks + most - 1) / most * unit);
     s.grid = (int)((chunks * unit + s.region - 1) / s.region);
     if (batch) HGM_TRY(launch_batch_setup(L, g, *batch, s));
-    HGM_TRY(launch_staged_setup(L, g, s, seed, bits, batch, check_bins));
     // Round 0 admits up to the first threshold with at least kStagedFirstEdges
     // edges above it.
     const double part[kStagedSteps - 1] = {1.0 / 2700, 1.0 / 250, 1.0 / 33, 0.1, 0.2, 0.5};
     int first = 0;
     while (first < kStagedSteps - 1 && part[first] * (double)g.m < (double)kStagedFirstEdges)
         ++first;
-    const int admitted = kStagedSteps - first;  // rounds with an admission
     HostSlot slot(may_allocate);
     unsigned long long copy[kEndHeader] = {0};
     unsigned long long *report = (unsigned long long *)slot.get();
-    if (report)
-        memset(report, 0, sizeof(copy));
-    else
-        report = s.hot + kSub / 2;
+    if (!report) report = s.hot + kSub / 2;
+    auto read_report = [&]() -> hipError_t {
+        if (!slot.get()) {
+            const hipError_t rc = hipMemcpyAsync(copy, report, sizeof(copy),
+                                                 hipMemcpyDeviceToHost, L.stream);
+            if (rc != hipSuccess) return rc;
+        }
+        const hipError_t rc = hipStreamSynchronize(L.stream);
+        if (slot.get()) memcpy(copy, report, sizeof(copy));
+        return rc;
+    };
+    // Sparse instances: a sample says how many others an edge meets, and with it
+    // where round 1 goes on.  It is read here first where the rounds over all
+    // live edges may be the faster ones.
+    const double pins = (double)g.kappa, edges = (double)g.m;
+    const double met_by_means = pins * pins / (edges * std::max(1.0, (double)g.n));
+    const double most_met = g.kappa <= kSparseSmall    ? kSparseOthersSmall
+                            : g.kappa <= kSparseMiddle ? kSparseOthers
+                                                       : kSparseOthersLarge;
+    const bool sparse = g.kappa <= kSparseMean * g.m && std::max(pins, edges) >= kSparseSize &&
+                        met_by_means <= most_met;
+    const double few = sparse && over_all ? few_others(g, o) : 0.0;
+    int second = sparse ? -1 : first + 1;
+    if (few > 0.0 && met_by_means <= few) {
+        if (pins * pins > few * edges) {  // else there are not that many pins
+            HGM_TRY(launch_staged_sample(L, g, s, seed));
+            HGM_TRY(launch_staged_meet(L, g, s, first + 1, report));
+            HGM_TRY(read_report());
+        }
+        const uint32_t met_bits = (uint32_t)copy[1];
+        float met;
+        memcpy(&met, &met_bits, sizeof(met));
+        if (met <= few) {
+            *over_all = true;
+            return HGM_OK;
+        }
+        second = (int)copy[0];
+    }
+    HGM_TRY(launch_staged_setup(L, g, s, seed, bits, batch, check_bins, second < 0));
+    if (check_bins) HGM_TRY(launch_staged_check(L, g, s));
+    if (slot.get()) memset(report, 0, sizeof(copy));
+    const int admitted =  // rounds with an admission
+        1 + kStagedSteps - (second < 0 ? first + 1 : second);
     EndArgs end = end_args(s, report);
     for (int k = 0; k < 2; ++k) end.counts[k] = s.rec_c[k];
     end.check_bins = check_bins ? 1 : 0;
     end.run = o.ending || batch ? 1 : 0;  // tail_pins is hgm_match's
     end.lists = s.grid * (kBlock / kStagedWave);
     end.stride = s.region / (kBlock / kStagedWave);
-    HGM_TRY(launch_staged_join(L, g, s, 0, first, seed));
+    HGM_TRY(launch_staged_join(L, g, s, 0, first, second, seed));
     int launched = 0;
     // About 1 in 20 edges is live in the round of the last step and a tenth as
     // many in each round after it, so that the tail's bound is met in that
@@ -1017,7 +1065,9 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
         for (int b = 0; b < rounds; ++b) {
             HGM_TRY(launch_staged_test(L, g, s, launched, bits));
             launched += 1;
-            HGM_TRY(launch_staged_join(L, g, s, launched, first, seed));
+            if (second < 0 && launched == 1)
+                HGM_TRY(launch_staged_meet(L, g, s, first + 1, s.hot + kSub / 4));
+            HGM_TRY(launch_staged_join(L, g, s, launched, first, second, seed));
         }
         if (launched < admitted - 1) {  // a small rounds_per_sync
             plan -= rounds;
@@ -1026,13 +1076,10 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
         }
         end.round = launched;
         HGM_TRY(launch_end(L, g, s, end, bits));
-        if (!slot.get())
-            HGM_TRY(hipMemcpyAsync(copy, report, sizeof(copy), hipMemcpyDeviceToHost, L.stream));
-        HGM_TRY(hipStreamSynchronize(L.stream));
-        if (slot.get()) memcpy(copy, report, sizeof(copy));
+        HGM_TRY(read_report());
         if (copy[kEndOverflow] == 2) return HGM_E_CSR;
         if (copy[kEndOverflow]) {
-            *recheck = true;
+            *over_all = true;
             return HGM_OK;
         }
         if (copy[kEndFinished]) return HGM_OK;
@@ -1044,22 +1091,6 @@ int run_staged(const Graph &g, const Opts &o, State s, const Launch &L, uint32_t
 bool staged_call(const Opts &o, const hgm_stats *stats) {
     return !stats && !o.reseed && o.max_rounds == 0 && !o.validate &&
            o.variant != HGM_VARIANT_CREW && o.tail_pins <= 0 && o.bin_shift <= 0;
-}
-
-// Whether the rounds over all live edges are the faster ones (schedule.h,
-// kFewSize): edges are short and have few others at their pins, so that most
-// are matched in the first rounds whichever way they are looked at.
-bool few_conflicts(const Graph &g, const Opts &o) {
-    const int64_t size = std::max<int64_t>(g.kappa, g.m);
-    const bool vertex_form = o.variant == HGM_VARIANT_AUTO && o.have_vertex_side;
-    if (size < (g.vbase ? kFewBatch : kFewSize) || g.kappa > kFewMean * g.m) return false;
-    // The vertex form reads every vertex, batches set all of them up.
-    if (g.vbase ? g.n > 8 * g.kappa : vertex_form && g.n >= kFewVerts && g.n > 4 * g.kappa)
-        return false;
-    const double pins = (double)g.kappa, others = pins * pins / std::max(1.0, (double)g.n * g.m);
-    if (g.vbase) return others <= kFewBatchOthers;
-    const double most = size <= kFewMiddle ? 12.0 : size <= kFewLarge ? 6.0 : 2.0;
-    return others <= (vertex_form ? most : most / 2);
 }
 
 // Workspace of hgm_match_noalloc: one array per GPU in the library's device
@@ -1201,10 +1232,10 @@ int match_one(const hgm_csr *gin, uint32_t seed, uint32_t *matched_bits, void *w
     bool ran = false;
     rc = match_solo(g, o, lay, s, L.stream, seed, matched_bits, stats, may_allocate, &ran);
     if (rc != HGM_OK || ran) return rc;
-    if (g.m > 0 && staged_call(o, stats) && !few_conflicts(g, o)) {
-        bool recheck = false;
-        rc = run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate, &recheck);
-        if (rc != HGM_OK || !recheck) return rc;
+    if (g.m > 0 && staged_call(o, stats)) {
+        bool over_all = false;
+        rc = run_staged(g, o, s, L, seed, matched_bits, nullptr, may_allocate, &over_all);
+        if (rc != HGM_OK || !over_all) return rc;
     }
     return run_rounds(g, o, lay, s, L, seed, matched_bits, stats, nullptr, nullptr, may_allocate);
 }
@@ -1391,14 +1422,12 @@ int hgm_match_batch(const hgm_batch *b, uint32_t *matched_bits, void *workspace,
         HGM_TRY(hipStreamSynchronize(L.stream));
         if (slot.get()) memcpy(listed, J.report, sizeof(listed));
         if (listed[1] == 0) return HGM_OK;
-        if (listed[0] == 0 && few_conflicts(g, o))
-            return run_rounds(g, o, lay, s, L, 0, matched_bits, stats, &in, &sa);
         in.mark_done = listed[0] > 0;
         in.solo_max_size = J.max_size;
         in.solo_max_verts = J.max_verts;
         return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     }
-    if (admit && (!s.explicit0 || too_long) && !few_conflicts(g, o))
+    if (admit && (!s.explicit0 || too_long))
         return run_staged(g, o, s, L, 0, matched_bits, &in, true);
     return run_rounds(g, o, lay, s, L, 0, matched_bits, stats, &in, &sa);
 }

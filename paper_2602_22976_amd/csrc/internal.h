@@ -366,14 +366,25 @@ hipError_t launch_max0(const Launch &L, const Graph &g, const State &s, uint32_t
 constexpr int kClearNone = 0, kClearAll = 1, kClearPins = 2;
 hipError_t launch_test(const Launch &L, const Graph &g, const State &s, int round, int clear,
                        uint32_t *bits, uint32_t kseed);
-// Rounds by admission (staged.hip).  `first`: the admission step of round 0.
-// check_bins: the pins of every bin are counted for k_end (one instance with
-// automatic bins); what that finds of v_off is left in piece_count.
-constexpr int kBinsUnused = 0, kBinsCompare = 1, kBinsBadOffsets = 2;
+// Rounds by admission (staged.hip).  check_bins: of v_off, what
+// launch_staged_check needs; sparse: a sample of the edges, for
+// launch_staged_meet.
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
-                               uint32_t *bits, const BatchIn *batch, bool check_bins);
+                               uint32_t *bits, const BatchIn *batch, bool check_bins, bool sparse);
+// Counts the pins of every bin for k_end (one instance with automatic bins);
+// what it finds of v_off is left in piece_count.
+constexpr int kBinsUnused = 0, kBinsCompare = 1, kBinsBadOffsets = 2;
+hipError_t launch_staged_check(const Launch &L, const Graph &g, const State &s);
+// The sample alone (one instance), ahead of the setup.
+hipError_t launch_staged_sample(const Launch &L, const Graph &g, const State &s, uint32_t seed);
+// How many others an edge meets, by the sample: out (device or pinned host
+// memory) gets the step that round 1 should admit, `next` at least, and that
+// number as the bits of a float.
+hipError_t launch_staged_meet(const Launch &L, const Graph &g, const State &s, int next,
+                              unsigned long long *out);
+// `first`, `second`: the steps of rounds 0 and 1 (-1: as launch_staged_meet says).
 hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, int round,
-                              int first, uint32_t seed);
+                              int first, int second, uint32_t seed);
 hipError_t launch_staged_test(const Launch &L, const Graph &g, const State &s, int round,
                               uint32_t *bits);
 // The end of a batch of rounds (ending.hip): after the pass that formed the live

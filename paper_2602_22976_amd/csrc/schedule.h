@@ -78,30 +78,31 @@ constexpr int64_t kStagedLargeEdges = (int64_t)1 << 23;
 // them: 1,023 us with 64 edges a wave, 354 with 4,096 pins, 255 with 512; the
 // rounds over all edges 1,115).
 constexpr int64_t kStagedWavePins = 512;
-// Matching only, short edges (kFewMean pins) and few of them at each pin (pins a vertex times
-// pins an edge, the others that an edge meets): rounds over all edges up to 12
-// of them below kFewMiddle pins (or edges), 6 below kFewLarge, 2 beyond; half
-// as many where round 0 has no vertex form.  Admission has twice the launches
-// and passes to pay for, and little to leave out.  Admission / all edges, us, by
-// others met:
-//   graphs, 40,000 pins    1: 144 / 95   4: 143 / 94    8: 103 / 102
-//           1M             1: 252 / 190  8: 225 / 195  12: 214 / 210  16: 172 / 214
-//           4M             1: 514 / 404  4: 372 / 331   8: 305 / 324
-//           16M            1: 1995 / 1523  2: 1473 / 1233  4: 1010 / 1093
-//   edges of 4, 2M         2: 370 / 258  8: 311 / 270  16: 283 / 263  24: 272 / 288
-//           8M             2: 874 / 800  4: 661 / 712
-//   no vertex form, 1M     1: 248 / 203  4: 249 / 202   8: 219 / 224
-//           4M             2: 449 / 426  4: 370 / 418
-// Below kFewSize both are a chain of launches (20,000 pins: 82 / 98).  Longer
-// edges: 50,000 of 16 pins meeting 8, 208 / 183, but 2,000 of 64 136 / 326.  With
-// more than 4 vertices a pin, from kFewVerts on, the vertex form's pass over
-// them costs more (2M pins, 16M vertices 464 / 442, 33M 582 / 692).
-// Batches (rounds without the ending): 640,000 pins, 0.8 others 247 / 199;
-// 480,000, 2 192 / 184; 320,000, 2.7 173 / 174; 1.28M, 4 268 / 248; with 62
-// vertices a pin 213 / 225 and 419 / 649.
-constexpr int64_t kFewSize = 1 << 15, kFewMiddle = 1 << 21, kFewLarge = 6 << 20, kFewMean = 8;
-constexpr int64_t kFewVerts = 1 << 22, kFewBatch = 1 << 14;
-constexpr double kFewBatchOthers = 2.5;
+// Rounds by admission sample how many others an edge meets (staged.hip) where
+// edges are short and the means (pins a vertex times pins an edge) leave room
+// for few: kSparseOthersSmall up to kSparseSmall pins, where the sample costs
+// what it gains (20,000 edges of 2 pins meeting 8: 106 / 116, 4: 154 / 107),
+// kSparseOthers up to kSparseMiddle (500,000 edges meeting 12: 237 / 187),
+// kSparseOthersLarge beyond.  Below kSparseSize pins (or edges) every choice is
+// a chain of launches.
+constexpr int64_t kSparseMean = 8, kSparseSize = 1 << 14, kSparseSmall = 1 << 18,
+                  kSparseMiddle = 1 << 21;
+constexpr double kSparseOthersSmall = 6.0, kSparseOthers = 14.0, kSparseOthersLarge = 5.0;
+// Beyond kSparseAsk pins (or edges) the host waits for the sample (30 us) where
+// the means are below the same bounds, and
+// runs the rounds over all live edges up to kFewOthers, kFewOthersEdge where
+// round 0 has no vertex form, kFewOthersLarge beyond kSparseMiddle pins (none
+// without the vertex form).  Admission / over all, us, by others met, wait not
+// counted:
+//   graphs, 1M pins     1: 306 / 195  2: 291 / 187  4: 256 / 180  6: 248 / 195
+//           4M          1: 549 / 411  2: 476 / 368  4: 406 / 361
+//           16M         1: 2158 / 1593  2: 1682 / 1307  4: 1252 / 1192
+//   edges of 4, 2M      2: 374 / 264  4: 332 / 249  8: 275 / 267
+//   no vertex form, 1M  2: 291 / 205  4: 256 / 210; 4M 1: 549 / 476  2: 476 / 434
+// and with more than 4 vertices a pin, from kSparseVerts on, the vertex form's
+// pass over them costs more (2M pins, 33M vertices 582 / 692).
+constexpr int64_t kSparseAsk = 1 << 19, kSparseVerts = 1 << 22;
+constexpr double kFewOthers = 6.0, kFewOthersEdge = 4.0, kFewOthersLarge = 4.5;
 // Rounds by admission: round 0 starts with the first step expected to admit
 // at least this many edges (fewer leave the grid idle for a whole round).
 constexpr int64_t kStagedFirstEdges = 1024;

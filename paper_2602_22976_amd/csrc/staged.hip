@@ -28,6 +28,7 @@
 // of the lists: compaction is a ballot, with no barrier and no atomic.  Done
 // marks are bits (n / 8 bytes stay in every XCD's L2 beside the streams).
 #include "internal.h"
+#include "schedule.h"
 #include "wave.h"
 
 namespace hgm {
@@ -96,11 +97,121 @@ __device__ __forceinline__ VOffPart *v_off_parts(const State &s) {
     return reinterpret_cast<VOffPart *>(s.bin_key);
 }
 
+// Sparse instances.  Where an edge meets few others, most are matched in the
+// first rounds whichever way they are looked at, and the steps cost more than
+// they leave out: round 1 then goes on with a later one.  A sample says how many
+// others an edge meets (the means do not: with popular vertices the same means
+// want every step): the setup reads two pins of up to kMeetEdges edges, one
+// from every stretch of ids, and one workgroup puts them in a hash table, where a
+// pin that finds its vertex is a hit.  The gathers are spread over workgroups: a
+// single one took 28 us for them.
+constexpr int kMeetEdges = 4096, kMeetSlots = 12288, kMeetProbes = 8;
+constexpr int kFirstWord = 8;  // of hot: the step of round 1
+
+// {two pins} of sampled edge i, -1 where it has fewer.
+__device__ __forceinline__ int2 *met_pins(const State &s) {
+    return reinterpret_cast<int2 *>(s.rec_key[1]);  // free until round 1's lists
+}
+__device__ __forceinline__ int met_edges(const Graph &g) {
+    return g.m < kMeetEdges ? g.m : kMeetEdges;
+}
+template <bool kB>
+__device__ __forceinline__ void sample_edge(const Graph &g, const State &s, uint32_t seed, int i) {
+    const int n = met_edges(g);
+    if (i >= n) return;
+    const int64_t lo = (int64_t)g.m * i / n, hi = (int64_t)g.m * (i + 1) / n;
+    const uint32_t x = priority_hash(seed, 0xedceu + (uint32_t)i);
+    const int64_t e = lo + x % (uint32_t)(hi - lo);
+    const int64_t base = g.pairs ? 2 * e : g.e_off[e];
+    const int len = g.pairs ? 2 : (int)(g.e_off[e + 1] - base);
+    const int vb = kB ? g.vbase[e] : 0;
+    const uint32_t j = len > 0 ? (x >> 7) % (uint32_t)len : 0;
+    int2 v = make_int2(-1, -1);
+    if (len > 0) v.x = g.e_pins[base + j] + vb;
+    if (len > 1) v.y = g.e_pins[base + ((int)j + 1 < len ? j + 1 : 0)] + vb;
+    met_pins(s)[i] = v;
+}
+
+// The step of round 1 for `others` met by an edge on average: all edges, half of
+// them, a fifth, or the next.  Measured with round 0 at that step, us, graphs of
+// 500,000 edges, next step / 4 / 5 / 6 (rounds over all edges): 2 others 291 / 241
+// / 219 / 206 (187), 4 256 / 216 / 199 / 205 (180), 8 234 / 193 / 201 / 209 (193);
+// of 2M edges 2 476 / 425 / 413 / 474 (368), 4 406 / 355 / 429 / 457, 12 296 / 325 /
+// 389; popularity by rank^-0.7, 500,000 edges, 173 others 197 / 254 / 262 / 261.
+// With the sample and from round 1 on, without a vertex side: 500,000 edges 2
+// others 216, 4 208, 8 194; 2M 2 455, 4 396; 173 others 210 (no step left out,
+// 8 to 12 us for the sample).
+__device__ __forceinline__ int next_step(float others, int64_t kappa, int next) {
+    int step = next;
+    if (kappa <= kSparseMiddle)
+        step = others <= 1.5f                                ? 6
+               : others <= 5.f                               ? 5
+               : others <= 14.f || kappa <= kSparseSmall ? 4
+                                                              : next;
+    else
+        step = others <= 3.f ? 5 : others <= 5.f ? 4 : next;
+    static_assert(kThresholds == 6, "the steps above");
+    return step > next ? step : next;
+}
+
+constexpr int kSampleGrid = kMeetEdges / kWave;
+__global__ void __launch_bounds__(kWave) k_staged_sample(Graph g, State s, uint32_t seed) {
+    sample_edge<false>(g, s, seed, blockIdx.x * kWave + threadIdx.x);
+}
+
+// Hashes the sample: one workgroup, between round 0 and the join of round 1 or
+// before round 0.  out: {the step, the others met as a float's bits}.
+__global__ void __launch_bounds__(kSetupThreads) k_staged_meet(Graph g, State s, int next,
+                                                               unsigned long long *out) {
+    __shared__ int ids[kMeetSlots];
+    __shared__ unsigned int hits;
+    constexpr int kOwn = kMeetEdges / kSetupThreads;
+    const int tid = threadIdx.x, n = met_edges(g);
+    int2 v[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const int i = q * kSetupThreads + tid;
+        v[q] = i < n ? met_pins(s)[i] : make_int2(-1, -1);
+    }
+    for (int j = tid; j < kMeetSlots; j += kSetupThreads) ids[j] = -1;
+    if (tid == 0) hits = 0;
+    __syncthreads();
+    unsigned int mine = 0;
+    auto put = [&](int x) {
+        if (x < 0) return;
+        uint32_t h = __umulhi((uint32_t)x * 0x9E3779B1u, (uint32_t)kMeetSlots);
+        for (int p = 0; p < kMeetProbes; ++p) {
+            const int id = atomicCAS(&ids[h], -1, x);
+            if (id == x) ++mine;
+            if (id == -1 || id == x) return;
+            h = h + 1 < (uint32_t)kMeetSlots ? h + 1 : 0;
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        put(v[q].x);
+        put(v[q].y);
+    }
+    if (mine) atomicAdd(&hits, mine);
+    __syncthreads();
+    if (tid == 0) {
+        // Two edges share others / m vertices on average, and a shared one is
+        // among the sampled pins of both with (2 / size)^2.
+        const float size = (float)g.kappa / (float)g.m, over = size > 2.f ? size / 2.f : 1.f;
+        const float pairs = 0.5f * (float)n * (float)n;
+        const float others = (float)hits / pairs * (float)g.m * over * over;
+        const unsigned long long step = (unsigned long long)next_step(others, g.kappa, next);
+        s.hot[kFirstWord] = step;
+        out[0] = step;
+        out[1] = __float_as_uint(others);
+    }
+}
+
 // Clears the state; workgroup 0 clears the counters and draws the thresholds.
 template <bool kB>
 __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s, uint32_t seed,
                                                                 uint32_t *bits, int keep_bits,
-                                                                int check_bins) {
+                                                                int check_bins, int sparse) {
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
         for (int j = tid; check_bins && j < s.bin_nb; j += kSetupThreads) s.bin_cursor[j] = 0;
@@ -137,6 +248,9 @@ __global__ void __launch_bounds__(kSetupThreads) k_staged_setup(Graph g, State s
                 s.hot[q] = q < kFromMaxima ? top[i] : one[i];
         return;
     }
+    if (sparse && tid < kWave)
+        for (int i = (blockIdx.x - 1) * kWave + tid; i < kMeetEdges; i += (gridDim.x - 1) * kWave)
+            sample_edge<kB>(g, s, seed, i);
     const int64_t stride = (int64_t)(gridDim.x - 1) * kSetupThreads;
     const int64_t at = (int64_t)(blockIdx.x - 1) * kSetupThreads + tid;
     // The arrays start at 256-byte boundaries and are padded to them.
@@ -411,10 +525,11 @@ __device__ __forceinline__ WaveLists lists(const State &s, int k) {
     return {s.list[k], s.rec_a[k], s.rec_b[k], s.rec_vb[k], s.rec_key[k]};
 }
 
-// Round `round` admits step first + round.
+// Round 0 admits step `first`, round 1 step `second` (-1: as k_staged_meet says),
+// and so on.
 template <bool kPairs, bool kB>
 __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int round, int first,
-                                                        uint32_t seed) {
+                                                        int second, uint32_t seed) {
     __shared__ WaveScratch scratch[kWaves];
     __shared__ int queue[kWaves][cand_size(kFill)];
     __shared__ LongEdges longs;
@@ -433,10 +548,13 @@ __global__ void __launch_bounds__(kBlock) k_staged_join(Graph g, State s, int ro
             all[i] = make_ulonglong2(0, 0);
     }
     const int64_t end = range.lo + range.per < g.m ? range.lo + range.per : g.m;
+    if (second < 0 && round > 0) second = (int)s.hot[kFirstWord];
+    const int step = round == 0 ? first : second + round - 1;
+    const int before = round == 1 ? first : step - 1;  // steps up to it are admitted
+    const bool sweep = round > 0 && step >= kSweep && (before < kSweep || round == 1);
     const int kept = join_wave<kPairs, kB, kKeepPins, kStagedSteps, kFill>(
         m, scratch[wid], queue[wid], g.e_pins, lists(s, from), lists(s, to), range.lo, end,
-        round > 0 ? s.rec_c[from][range.wave] : 0, round == 0,
-        first + round == (first < kSweep ? kSweep : first + 1), first + round, step_bytes(s),
+        round > 0 ? s.rec_c[from][range.wave] : 0, round == 0, sweep, before, step, step_bytes(s),
         reinterpret_cast<const uint64_t *>(s.hot));
     // Before the barrier, which waits for what the wave has in flight.
     if (lane_id() == 0) {
@@ -557,36 +675,54 @@ __global__ void __launch_bounds__(kBlock) k_staged_test(Graph g, State s, int ro
 
 }  // namespace
 
+static int setup_grid(const Launch &L) { return L.grid / 4 + 2; }
+
 hipError_t launch_staged_setup(const Launch &L, const Graph &g, const State &s, uint32_t seed,
-                               uint32_t *bits, const BatchIn *batch, bool check_bins) {
-    const dim3 grid(L.grid / 4 + 2), block(kSetupThreads);
+                               uint32_t *bits, const BatchIn *batch, bool check_bins, bool sparse) {
+    const dim3 grid(setup_grid(L)), block(kSetupThreads);
     const int keep = batch && batch->mark_done, check = check_bins ? 1 : 0;
+    const int meet = sparse ? 1 : 0;
     if (g.vbase)
         hipLaunchKernelGGL(k_staged_setup<true>, grid, block, 0, L.stream, g, s, seed, bits, keep,
-                           0);
+                           0, meet);
     else
         hipLaunchKernelGGL(k_staged_setup<false>, grid, block, 0, L.stream, g, s, seed, bits, keep,
-                           check);
-    if (check)
-        hipLaunchKernelGGL(k_staged_check, dim3(kCheckGrid), dim3(kCheckThreads), 0, L.stream, g, s,
-                           (int)grid.x - 1);
+                           check, meet);
     if (keep)
         hipLaunchKernelGGL(k_staged_mark_solo, dim3(L.grid), dim3(kBlock), 0, L.stream, s, *batch);
     return hipGetLastError();
 }
 
+hipError_t launch_staged_check(const Launch &L, const Graph &g, const State &s) {
+    hipLaunchKernelGGL(k_staged_check, dim3(kCheckGrid), dim3(kCheckThreads), 0, L.stream, g, s,
+                       setup_grid(L) - 1);
+    return hipGetLastError();
+}
+
+hipError_t launch_staged_sample(const Launch &L, const Graph &g, const State &s, uint32_t seed) {
+    if (g.vbase) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_staged_sample, dim3(kSampleGrid), dim3(kWave), 0, L.stream, g, s, seed);
+    return hipGetLastError();
+}
+
+hipError_t launch_staged_meet(const Launch &L, const Graph &g, const State &s, int next,
+                              unsigned long long *out) {
+    hipLaunchKernelGGL(k_staged_meet, dim3(1), dim3(kSetupThreads), 0, L.stream, g, s, next, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_staged_join(const Launch &L, const Graph &g, const State &s, int round,
-                              int first, uint32_t seed) {
+                              int first, int second, uint32_t seed) {
     const dim3 grid(s.grid), block(kBlock);
     if (g.pairs)
         hipLaunchKernelGGL((k_staged_join<true, false>), grid, block, 0, L.stream, g, s, round,
-                           first, seed);
+                           first, second, seed);
     else if (g.vbase)
         hipLaunchKernelGGL((k_staged_join<false, true>), grid, block, 0, L.stream, g, s, round,
-                           first, seed);
+                           first, second, seed);
     else
         hipLaunchKernelGGL((k_staged_join<false, false>), grid, block, 0, L.stream, g, s, round,
-                           first, seed);
+                           first, second, seed);
     return hipGetLastError();
 }
 

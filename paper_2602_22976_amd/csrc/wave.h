@@ -272,7 +272,8 @@ struct WaveLists {
 // the edges of its range admitted this round enter the list `to` and raise the
 // maxima at their pins.  Returns how many entered.
 //
-// `step`: the part of the order admitted (kSteps: none).  In the first round
+// `step`: the part of the order admitted (kSteps: none), with those behind
+// `before`.  In the first round
 // the join writes each edge's step, the number of thresholds above its key (so
 // that a lower key never has an earlier step, whatever the thresholds), and
 // admits the steps up to `step`; later rounds read that byte instead of the
@@ -296,7 +297,8 @@ template <bool kPairs, bool kB, int kKeep, int kSteps, int kFill, class M>
 __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const int32_t *e_pins,
                                          const WaveLists &from, const WaveLists &to, int64_t lo,
                                          int64_t end, int listed, bool first_round, bool sweep,
-                                         int step, uint8_t *steps, const uint64_t *thresholds) {
+                                         int before, int step, uint8_t *steps,
+                                         const uint64_t *thresholds) {
     const int lane = lane_id();
     int queued = 0;
     auto push = [&](int64_t e, bool on) {
@@ -358,7 +360,8 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int64_t at = c0 + 4 * (u * kWave + lane) + q;
-                push(at, at < end && (int)(x[u] >> 8 * q & 255) == step);
+                const int part = (int)(x[u] >> 8 * q & 255);
+                push(at, at < end && part > before && part <= step);
             }
         return 4 * kU * kWave;
     };
@@ -372,7 +375,7 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
         for (int u = 0; u < kU; ++u) {
             const int64_t at = c0 + u * kWave + lane;
             part[u] = at < end ? steps[at] : 0;
-            on[u] = part[u] >= step;
+            on[u] = part[u] > before;
             base[u] = len[u] = vb[u] = 0;
             if (at < end) m.place((int)at, base[u], len[u], vb[u]);
         }
@@ -422,7 +425,7 @@ __device__ __forceinline__ int join_wave(M &m, WaveScratch &W, int *cand, const 
         for (int u = 0; u < kU; ++u) {
             const int64_t at = c0 + u * kWave + lane;
             if (part[u] > step && !on[u]) steps[at] = kNever;
-            push(at, on[u] && part[u] == step);
+            push(at, on[u] && part[u] <= step);
         }
         return kU * kWave;
     };
