@@ -27,8 +27,9 @@
  * visited.  Its rounds are edge-centric and read only the edge side; where the
  * other rounds would use automatic bins (bin_shift), the pins of each bin are
  * counted, and unless they are v_off's degree sums the call goes on with those
- * rounds and returns what they return.  Every other call runs its rounds over
- * all live edges, as the paper counts them.
+ * rounds and returns what they return.  Every other call, and one on a larger
+ * instance whose edges meet few others by a sample, runs its rounds over all
+ * live edges, as the paper counts them.
  *
  * Conventions for every entry point:
  *  - All array pointers inside hgm_csr, the output bitmap and the workspace

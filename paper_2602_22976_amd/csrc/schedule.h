@@ -67,8 +67,8 @@ constexpr double kEndingPins = 5000.0;
 constexpr double kEndingEdges = 1400.0;
 // Rounds by admission: workgroups of the join and the test.  A wave's work
 // between two waits grows with its range, and the chip is full with 8 waves a
-// compute unit (1024 against 512: 600,000 edges 222 / 208 us, RGG, 6.9M, 404 /
-// 385, hub-stress, 4M, 470 / 455, power-law, 5M, the same); from about 8M edges
+// compute unit (1024 against 512: 600,000 edges 222 / 208 us, hub-stress, 4M, 470
+// / 455, power-law, 5M, and RGG, 6.9M, within 5%); from about 8M edges
 // on 16 waves hide more (10M 1,215 / 1,240, 20M 1,750 / 1,805).  At 256 or 1536
 // all take longer.
 constexpr int kStagedGrid = 512, kStagedGridLarge = 1024;

@@ -17,7 +17,7 @@
 // visits stay those of unshared maxima (50,000 vertices on 16,384 slots: 24
 // rounds instead of 9, 18 thousand edge visits either way).  Maxima outside LDS
 // are no choice: even workgroup-scope atomics are performed at the memory side
-// here, at 20 to 30 G/s for the whole chip (the batch of 4,096 took 5.2 ms).
+// here, at 27 G/s for the whole chip (the batch of 4,096 took 5.2 ms).
 //
 // Calls whose result or counts depend on the round an edge is matched in
 // (per-round counts, priorities redrawn every round) have at most one edge per
@@ -260,11 +260,11 @@ __device__ __forceinline__ void head_act(const int32_t *e_pins, const EdgeHead (
 //
 // Bound by memory.  A part's edges lie far apart: gathered by id as they are
 // admitted, each costs a line for its offsets, its weight and its pins.  The
-// batch of 4,096 instances with 4.6e8 pins: 3.75 ms so, 1.15e8 requests that
-// leave L2; 2.91 ms with a record of every edge sorted first; 2.53 ms in two
-// phases; 2.44 ms with places sorted instead of records, by halving.  Half of
-// it is now the pass over the pins (3.9 TB/s), the rest the rounds, 20 to 30 us
-// each for the largest instances, a chain of memory accesses.
+// batch of 4,096 instances with 4.6e8 pins: 3.75 ms so; 2.91 ms with a record of
+// every edge sorted first; 2.53 ms in two phases; 2.44 ms with places sorted
+// instead of records, by halving (6.6e7 reads and 1.6e7 writes leave L2; the
+// pins alone are 1.4e7 lines).  What is left is the pass over the pins and the
+// rounds, a chain of memory accesses.
 template <int T>
 __device__ __forceinline__ int solo_lists(const Inst &I, const SoloJob &J, SoloShared<T> &S,
                                           SoloSide<false> &m, int per, int *kept_out) {

@@ -9,10 +9,10 @@
 // admits the next part of the order; by the time most edges are admitted one
 // of their pins is done, which the edge's first pins show.  What reaches the
 // maximum, and with it the random reads and device atomics that bound the
-// rounds over all edges, falls from 38M incidences to 0.6M on the power-law
-// instance (29.8M pins) and from 52M to 1.8M on the hub-stress one (36M), at
-// the same number of rounds; the passes over the weights and the first pins
-// that remain are streams.  Per-round counts, priorities redrawn every round
+// rounds over all edges, falls to 0.29M atomics in the joins of the power-law
+// instance (29.8M pins) and 1.6M on the hub-stress one (36M), at the same number
+// of rounds; the passes over the weights and the first pins that remain are
+// streams.  Per-round counts, priorities redrawn every round
 // and a round limit depend on the round an edge is matched in: those calls
 // run the rounds of kernels.hip.
 //
@@ -399,8 +399,8 @@ __device__ __forceinline__ int64_t live_edges(const State &s, int r) {
 
 // How best[r & 1] goes back to zero before round r + 2 raises it: a round with
 // many live edges by one pass over the array, one with few by a store at each
-// of its pins; either in the join of round r + 1.  Scattered stores run at
-// about 30 G/s.  A long edge adds kLongWeight times its pins to the round's
+// of its pins; either in the join of round r + 1.  Scattered stores cost as much
+// as device atomics (27 G/s).  A long edge adds kLongWeight times its pins to the round's
 // count of live edges, instead of 1: a workgroup lowers 2,048 pins in the time
 // that the pass takes for about 500 times as many vertices.  (The last rounds'
 // workgroup, which also reads the count, leaves such rounds to the grid.)
